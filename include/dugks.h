@@ -151,7 +151,10 @@ typedef struct {
   int32_t vel_kind;        /* dugks_vel_kind                                     */
   int32_t flags;           /* DUGKS_FLAG_*                                       */
   double vel_param[6];     /* p0.. of the velocity kind; finite                  */
-  int32_t tile_rows;       /* rows one wavefront marches; 0 = library default    */
+  int32_t tile_rows;       /* rows of a tile; 0 = library default.  Up to 8: a block
+                              of wavefronts takes the tile's rows side by side (the
+                              default for small grids); more: one wavefront marches
+                              them.  Results do not depend on it. */
   int32_t scheme;          /* dugks_scheme                                       */
 } dugks_params;
 
@@ -194,7 +197,7 @@ int dugks_step(const dugks_plan *plan, void *state, int64_t step,
 
 /* Autotuner of the tile height (rows one wavefront marches; results do not
  * depend on it).  For the library default and every height 16..256 (steps of
- * 8, at most ny), times `reps` launches of the step's kernels on `state` at
+ * 8, at most ny; 8 in rows_out: the block tiles of small grids), times `reps` launches of the step's kernels on `state` at
  * `step` (the state of the plan built from `params`, any tile_rows) -- after
  * 20 warm-up launches, twice per height, the better kept -- and writes the
  * fastest height to rows_out; the caller builds its plan with it.

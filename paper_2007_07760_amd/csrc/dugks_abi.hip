@@ -248,34 +248,47 @@ int default_tile_rows(const dugks_params& p, int nstrips) {
   return best;
 }
 
-// ------------------------------------------------------------ launches
-// fix = false leaves out the fused mass correction's reduction (tile timing:
-// the header then keeps the correction the next real step applies)
-template <typename T, bool MFIX, int STAGE>
-int launch_stage(const dugks_plan* P, void* state, int64_t n, hipStream_t s, bool fix = true) {
-  const Layout& L = P->L;
-  StepArgs<T> a = step_args<T>(P, STAGE);
-  StepBufs<T> q = step_bufs<T>(P, state, n);
-  T* dst2 = nullptr;
-  const T* aux = nullptr;
-  if (STAGE == STAGE_A) {           // f^^n -> f~(t'), Q
-    q.dst = at<T>(state, L.off_mid);
-    dst2 = at<T>(state, L.off_q);
-  } else if (STAGE == STAGE_B) {    // f~(t'), Q -> f^^{n+1}
-    q.src = at<T>(state, L.off_mid);
-    aux = at<T>(state, L.off_q);
-    q.cf = at<T>(state, L.off_coef2);
+// Rows of the tile kernel's tiles, or 0 where the march runs: heights up to
+// TILE_MAX_ROWS ask for it, and by default grids too small to fill the chip
+// with marching wavefronts take it.  A marching wavefront needs ~35 us (FP64
+// upwind-3; 57 us central-4, 78 us upwind-5) for a 16-row tile however few
+// there are, the tile kernel 6.6 us (7.5, 9.4) for a grid of up to 256 tiles,
+// but it forms the cell terms of 8 rows for every 4.  The line lies at the
+// number of 16-row marching tiles where the two meet, measured on square
+// grids (us per step, tile / march): FP64 upwind-3 768^2 38.0 / 41.9, 896^2
+// 48.7 / 43.6; central-4 1024^2 71 / 77, 1280^2 108 / 110; velocity arrays
+// 1024^2 65 / 63; T3S3 640^2 80 / 87, 768^2 105 / 95; upwind-5 (8-row tiles)
+// 1024^2 105 / 124, 1280^2 170 / 160; FP32 corrected 1024^2 43.4 / 46.8,
+// 1280^2 63 / 52.
+int tile_kernel_rows(const dugks_params& p, int nstrips) {
+  if (p.tile_rows > TILE_MAX_ROWS) return 0;
+  if (p.tile_rows == 0) {
+    const bool slow_march = p.recon == DUGKS_CENTRAL4 || p.recon == DUGKS_UPWIND5;
+    const long limit = p.precision == DUGKS_F32 ? (p.recon == DUGKS_UPWIND5 ? 1000 : 1250)
+                       : slow_march             ? 1650
+                       : p.vel_kind == DUGKS_VEL_ARRAYS ? 1100
+                       : p.scheme == DUGKS_T3S3         ? 600
+                                                        : 760;
+    if ((long)nstrips * ((p.ny + 15) / 16) > limit) return 0;
   }
-  double* part = at<double>(state, L.off_groups);
-  StateHeader* hd = at<StateHeader>(state, 0);
+  // a tile of a corrected plan is one mass group; upwind-5 forms 10 cell rows
+  // for 4 of its own, so it takes 8-row tiles (256^2: 12.2 us against 16.7)
+  // unless the 4-row ones leave compute units idle (64^2: 9.4 against 11.8)
+  if (p.flags & DUGKS_FLAG_MASS_FIX) return MASS_GROUP;
+  return p.recon == DUGKS_UPWIND5 && (long)nstrips * ((p.ny + 3) / 4) > 256 ? 8 : 4;
+}
+
+// ------------------------------------------------------------ launches
+template <typename T, bool MFIX, int STAGE>
+void launch_march(const dugks_plan* P, const StageBufs<T>& q, int64_t n, hipStream_t s) {
+  StepArgs<T> a = step_args<T>(P, STAGE);
   // blocks per XCD (see step_kernel's tile order)
   const int per = a.ileave > 1 ? a.ileave * a.clen * a.nstrips : (a.nlogical + 7) / 8;
   dim3 grid(per * 8), block(LANES);
   const bool varr = P->p.vel_kind == DUGKS_VEL_ARRAYS;
-  const T* uv = varr ? at<T>(state, L.off_vel) : nullptr;
 #define DUGKS_LAUNCH(RR, VA)                                                                   \
   hipLaunchKernelGGL((step_kernel<T, RR, MFIX, STAGE, VA>), grid, block, 0, s, a, n, q.src,    \
-                     q.dst, dst2, aux, q.cf, q.tabx, q.taby, uv, part, hd)
+                     q.dst, q.dst2, q.aux, q.cf, q.tabx, q.taby, q.uv, q.part, q.hdr)
   switch (P->p.recon) {
     case DUGKS_CENTRAL2:
       if (varr) DUGKS_LAUNCH(DUGKS_CENTRAL2, true); else DUGKS_LAUNCH(DUGKS_CENTRAL2, false);
@@ -291,9 +304,21 @@ int launch_stage(const dugks_plan* P, void* state, int64_t n, hipStream_t s, boo
       break;
   }
 #undef DUGKS_LAUNCH
+}
+
+// fix = false leaves out the fused mass correction's reduction (tile timing:
+// the header then keeps the correction the next real step applies)
+template <typename T, bool MFIX, int STAGE>
+int launch_stage(const dugks_plan* P, void* state, int64_t n, hipStream_t s, bool fix = true) {
+  const Layout& L = P->L;
+  const StageBufs<T> q = stage_bufs<T>(P, state, n, STAGE);
+  if (P->tile)
+    launch_tile<T>(P, STAGE, q, n, s);
+  else
+    launch_march<T, MFIX, STAGE>(P, q, n, s);
   if (MFIX && fix)
     hipLaunchKernelGGL(mass_fix_strips_kernel, dim3(L.tl.nstrips), dim3(LANES), 0, s,
-                       part, L.ngroups, L.tl.nstrips, at<double>(state, L.off_strips), hd,
+                       q.part, L.ngroups, L.tl.nstrips, at<double>(state, L.off_strips), q.hdr,
                        (double)P->p.nx * (double)P->p.ny);
   return hip_status(hipGetLastError());
 }
@@ -517,7 +542,10 @@ int dugks_plan_create(const dugks_params* p, dugks_plan** out) {
   }
   make_tables(P);
   P->nstrips = (p->nx + OWN - 1) / OWN;
-  P->seg_rows = p->tile_rows > 0 ? p->tile_rows : default_tile_rows(*p, P->nstrips);
+  P->tile = tile_kernel_rows(*p, P->nstrips);
+  P->seg_rows = p->tile_rows > TILE_MAX_ROWS
+                    ? p->tile_rows
+                    : (p->tile_rows > 0 ? 16 : default_tile_rows(*p, P->nstrips));
   if (p->flags & DUGKS_FLAG_MASS_FIX)   // whole mass groups per segment
     P->seg_rows = (P->seg_rows + MASS_GROUP - 1) / MASS_GROUP * MASS_GROUP;
   if (P->seg_rows > p->ny) P->seg_rows = p->ny;
@@ -572,7 +600,8 @@ int dugks_tune(const dugks_params* params, void* state, int64_t step, int32_t re
     dugks_plan* P = nullptr;
     if ((rc = dugks_plan_create(&q, &P))) break;
     bool dup = false;
-    for (dugks_plan* o : plans) dup = dup || o->seg_rows == P->seg_rows;
+    for (dugks_plan* o : plans)
+      dup = dup || (o->tile == P->tile && (P->tile || o->seg_rows == P->seg_rows));
     if (dup)
       dugks_plan_destroy(P);
     else
@@ -609,7 +638,7 @@ int dugks_tune(const dugks_params* params, void* state, int64_t step, int32_t re
     size_t b = 0;
     for (size_t i = 1; i < plans.size(); i++)
       if (best[i] < best[b]) b = i;
-    *rows_out = plans[b]->seg_rows;
+    *rows_out = plans[b]->tile ? TILE_MAX_ROWS : plans[b]->seg_rows;
   }
   for (dugks_plan* P : plans) dugks_plan_destroy(P);
   return rc;

@@ -133,6 +133,15 @@ __host__ __device__ constexpr int step_waves(int esize, int recon, bool mfix) {
                      : (esize == 8 ? 2 : ((recon == DUGKS_CENTRAL4 || mfix) ? 3 : 4));
 }
 
+// The tile kernel (dugks_tile.h) takes tiles of up to this many rows; the
+// register budgets of its variants, in wavefronts per SIMD.
+constexpr int TILE_MAX_ROWS = 8;
+__host__ __device__ constexpr int tile_waves(int esize, int recon, int TR) {
+  return wide(recon) ? (esize == 8 ? 4 : 6)
+                     : (esize == 8 ? (recon == DUGKS_CENTRAL4 ? 4 : (TR == 4 ? 5 : 6))
+                                   : (TR == 4 ? 8 : 6));
+}
+
 // ------------------------------------------------------------- state layout
 // The distributions live in strip chunks: the grid is cut into strips of OWN
 // columns (the columns one wavefront owns), and row y of strip s holds the 9

@@ -24,11 +24,13 @@
 // never cover stores.
 #pragma once
 
+#include <type_traits>
+
 #include "dugks_common.h"
 
 namespace dugks {
 
-// Scalars of one grid.  The buffers go to the kernel as separate __restrict__
+// Scalars of one grid.  The buffers go to the kernels as separate __restrict__
 // parameters: only there does the compiler take them as non-aliasing, which
 // lets the uniform coefficient and table reads use the scalar cache.
 template <typename T>
@@ -60,15 +62,6 @@ struct StepArgs {
 // reads f~ at t_n + dt/3, builds fbar+ with the half step 5 dt/12 (Eq. 34) and
 // writes f^^{n+1} = Q + (3/4) dt (Omega + S) + (4/7) dt L(f**) (Eqs. 16, 29).
 enum Stage { STAGE_T2 = 0, STAGE_A = 1, STAGE_B = 2 };
-
-template <typename T>
-struct StepBufs {
-  const T* __restrict__ src;     // f~^n and phi^{n-1} (strip chunks)
-  T* __restrict__ dst;           // f~^{n+1} and phi^n
-  const T* __restrict__ cf;      // compact face-stencil table [NCOMPACT]
-  const T* __restrict__ tabx;    // UX[2nx+2], VX[2nx+2]
-  const T* __restrict__ taby;    // UY[2ny+2], VY[2ny+2]
-};
 
 // Read-only tables that every lane of a wavefront reads at the same index
 // (the face stencil, the y velocity factors): read through the constant
@@ -153,6 +146,15 @@ __device__ __forceinline__ void bstore(double v, rsrc_t r, unsigned off) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, 2);
 }
 
+// f(0), f(1), .. f(N - 1) with compile-time arguments
+template <int N, typename F>
+__device__ __forceinline__ void unroll(F&& f) {
+  if constexpr (N > 0) {
+    unroll<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
+}
+
 // Ordering point for LDS traffic inside the (single-wavefront) workgroup: a
 // wavefront's LDS operations execute in program order, so only the compiler
 // must not move them across this point; no wait for outstanding operations.
@@ -190,7 +192,10 @@ __device__ __forceinline__ T over_norm(T theta, T gx, T gy) {
 
 // VARR: the velocity comes from caller-supplied cell arrays (steady; a face
 // takes the mean of its two cells) instead of the separable tables.
-template <typename T, int R, bool MFIX, int STAGE = STAGE_T2, bool VARR = false>
+// RING_ROWS > 0: the fbar+ rows of a whole tile are in LDS, without pads (the
+// neighbour columns come from lane shifts, see recon_pair).
+template <typename T, int R, bool MFIX, int STAGE = STAGE_T2, bool VARR = false,
+          int RING_ROWS = 0>
 struct Marcher {
   // the wide (upwind-5) patch reaches 2 rows below and 3 above the face row
   // and 3 columns beyond a lane: a 6-row ring, faces 3 rows behind the cell
@@ -198,10 +203,10 @@ struct Marcher {
   // (so that fbar+ is right on every lane); the narrow patches: a 4-row ring
   // (5 for central-4), faces 2 rows behind
   static constexpr bool WIDE = wide(R);
-  static constexpr int RB = WIDE ? 6 : ((R == DUGKS_CENTRAL4) ? 5 : 4);
+  static constexpr int RB = RING_ROWS ? RING_ROWS : (WIDE ? 6 : ((R == DUGKS_CENTRAL4) ? 5 : 4));
   static constexpr int LAG = WIDE ? 3 : 2;
-  static constexpr int LP = lpad(R);
-  static constexpr int LR = lrow(R);
+  static constexpr int LP = RING_ROWS ? 0 : lpad(R);
+  static constexpr int LR = RING_ROWS ? LANES : lrow(R);
   // FP32: the relaxation increments X_i - g_i are made to sum to zero in the
   // rest direction (see cell_stage); FP64 rounds phi to 1e-16 and keeps the
   // plain increments, as the oracle writes them
@@ -250,6 +255,81 @@ struct Marcher {
   double* part_row;
 
 
+  // the wavefront's place: its lane, strip and rows [first, first + rows), the
+  // output buffers, and the mass correction still to apply
+  __device__ __forceinline__ void place(int lane_, int strip, int first, int rows,
+                                        T* __restrict__ dst, T* __restrict__ dst2,
+                                        const T* __restrict__ aux, double* __restrict__ part,
+                                        double pend, double fitmax_) {
+    lane = lane_;
+    const int x0 = strip * OWN;
+    const int c0 = (x0 - HALO + lane) % a.nx;
+    col = c0 < 0 ? c0 + a.nx : c0;
+    {
+      const int cs = col / OWN;
+      loff = (int64_t)cs * a.ny * a.CH + (col - cs * OWN);
+    }
+    loffx = loff;
+    if (WIDE && (lane == 0 || lane == LANES - 1)) {
+      // the column beyond the lane, outwards (wrapped)
+      int cx = lane == 0 ? col - 1 : col + 1;
+      cx = cx < 0 ? cx + a.nx : (cx >= a.nx ? cx - a.nx : cx);
+      const int cs = cx / OWN;
+      loffx = (int64_t)cs * a.ny * a.CH + (cx - cs * OWN);
+    }
+    const int nown = min(OWN, a.nx - x0);
+    owned = lane >= HALO && lane < HALO + nown;
+    ocol = lane - HALO;
+    {
+      // the strip's own chunk column: ny rows of CH elements
+      const int64_t o = (int64_t)strip * a.ny * a.CH;
+      const unsigned nb = (unsigned)((int64_t)a.ny * a.CH * (int64_t)sizeof(T));
+      rdst = make_rsrc(dst + o, nb);
+      rdst2 = make_rsrc((STAGE == STAGE_A ? dst2 : dst) + o, nb);
+      raux = make_rsrc((STAGE == STAGE_B ? aux : src) + o, nb);   // used by stage B
+      rin = make_rsrc(src + o, nb);
+    }
+    y0 = first;
+    y1 = min(first + rows, a.ny);
+    base = y0 - LAG - 1;   // at or below every ring row the march touches
+    if (MFIX) {
+      cw0 = T(wq(0) * pend);
+      cw1 = T(wq(1) * pend);
+      cw2 = T(wq(2) * pend);
+      fitmax = T(fitmax_);
+      part_row = part + 2 * (int64_t)strip * a.ngroups;
+      rpart = make_rsrc(part_row, (unsigned)(16 * a.ngroups));
+    }
+  }
+
+  // the velocity at the lane's columns and the time factors of step n
+  __device__ __forceinline__ void flow(int64_t n) {
+    if (!VARR) {
+      const int ce = col + 1;  // east face of the column (x + 1), unwrapped
+      UXc = tabx[2 * col + 1];
+      VXc = tabx[(2 * a.nx + 2) + 2 * col + 1];
+      UXe = tabx[2 * ce];
+      VXe = tabx[(2 * a.nx + 2) + 2 * ce];
+    }
+    // time factors of the velocity at the stage's base time and at the time of
+    // the earlier phi (cells), and at base + its half step (faces); lanes 0, 1
+    // and 2 evaluate one of the three cosines each
+    const double tn = (double)n * a.dtd;
+    const double tb = tn + a.toff;
+    double gn = 1.0, gp = 1.0, gh = 1.0;
+    if (a.period > 0.0) {
+      const double t = lane == 0 ? tb : (lane == 1 ? tn + a.troff : tb + a.hd);
+      const double g = cos(M_PI * t / a.period);
+      gn = __shfl(g, 0);
+      gp = __shfl(g, 1);
+      gh = __shfl(g, 2);
+    }
+    gN = T(gn);
+    gP = T(gp);
+    gH = T(gh);
+    jscale = ((n == 0 && a.jfirst) || a.jzero) ? T(0) : a.jinv;
+  }
+
   // VARR: component c (0: u, 1: v) at the lane's cell of (wrapped) row rr;
   // rows are read again at the faces two rows later, from the caches
   __device__ __forceinline__ T uv_at(int c, int rr) const {
@@ -292,9 +372,9 @@ struct Marcher {
   }
 
   // phi = sum_i f~_i (Eq. 30, pairwise) of a new row and its horizontal
-  // differences
-  __device__ __forceinline__ void phi_push(const RowRegs<T>& d) {
-    const T p = (((d.f[0] + d.f[1]) + (d.f[2] + d.f[3])) +
+  // differences phi(x+1) - phi(x-1) and phi(x-1) + 4 phi(x) + phi(x+1)
+  __device__ __forceinline__ void phi_row(const RowRegs<T>& d, T& p, T& D, T& A) const {
+    p = (((d.f[0] + d.f[1]) + (d.f[2] + d.f[3])) +
                  ((d.f[4] + d.f[5]) + (d.f[6] + d.f[7]))) + d.f[8];
     T pE = from_right(p), pW = from_left(p);
     if (WIDE) {
@@ -304,11 +384,16 @@ struct Marcher {
       pW = lane == 0 ? px : pW;
       pE = lane == LANES - 1 ? px : pE;
     }
+    D = pE - pW;
+    A = fma(T(4), p, pW + pE);
+  }
+
+  __device__ __forceinline__ void phi_push(const RowRegs<T>& d) {
 #pragma unroll
     for (int j = 0; j < LAG + 1; j++) ph[j] = ph[j + 1];
-    ph[LAG + 1] = p;
-    D0 = D1; D1 = D2; D2 = pE - pW;
-    A0 = A1; A1 = A2; A2 = fma(T(4), p, pW + pE);
+    D0 = D1; D1 = D2;
+    A0 = A1; A1 = A2;
+    phi_row(d, ph[LAG + 1], D2, A2);
   }
 
   // cell-centred terms of row r: isotropic normal, theta (Eqs. 2, 4),
@@ -378,6 +463,59 @@ struct Marcher {
     return v;
   }
 
+  // the columns (lo <= dx <= hi) of ring row k + dy that the face values of
+  // velocity I read; lo > hi: none
+  struct Span {
+    int lo, hi;
+  };
+  template <int I, bool EAST>
+  static constexpr Span tap_span(int dy) {
+    Span s{1, -1};
+    for (int o = EAST ? 0 : 1; o < 2; o++)
+      for (int t = 0; t < ntap(R); t++)
+        if (tap_used(R, o, I, t) && tap_dy(R, o, t) == dy) {
+          const int dx = tap_dx(R, o, t);
+          if (s.lo > s.hi) s = Span{0, 0};
+          s.lo = dx < s.lo ? dx : s.lo;
+          s.hi = dx > s.hi ? dx : s.hi;
+        }
+    return s;
+  }
+
+  // the north and (EAST) the east face value of velocity I at row k, as recon
+  // forms them, from one LDS read per ring row: the neighbour columns are lane
+  // shifts of it (0 beyond the edge lanes, where nothing owned comes from)
+  template <int I, bool EAST>
+  __device__ __forceinline__ void recon_pair(int k, T& pn, T& pe) const {
+    constexpr int D = 3;                 // offsets -D .. D
+    T f[2 * D + 1][2 * D + 1];           // [dy + D][dx + D]; only the used ones are formed
+    unroll<2 * D + 1>([&](auto Y) {
+      constexpr int y = decltype(Y)::value;
+      constexpr Span sp = tap_span<I, EAST>(y - D);
+      if constexpr (sp.lo <= sp.hi) {
+        f[y][D] = bfp[slotB(k + y - D)][I][LP + lane];
+        unroll<D>([&](auto X) {
+          constexpr int dx = decltype(X)::value + 1;
+          if constexpr (dx <= sp.hi) f[y][D + dx] = from_right(f[y][D + dx - 1]);
+          if constexpr (-dx >= sp.lo) f[y][D - dx] = from_left(f[y][D - dx + 1]);
+        });
+      }
+    });
+    pn = pe = T(0);
+    unroll<ntap(R)>([&](auto U) {
+      constexpr int t = decltype(U)::value;
+      if constexpr (tap_used(R, 1, I, t))
+        pn = fma(cf[compact_index(R, 1, I, t)], f[tap_dy(R, 1, t) + D][tap_dx(R, 1, t) + D], pn);
+    });
+    if constexpr (EAST)
+      unroll<ntap(R)>([&](auto U) {
+        constexpr int t = decltype(U)::value;
+        if constexpr (tap_used(R, 0, I, t))
+          pe = fma(cf[compact_index(R, 0, I, t)], f[tap_dy(R, 0, t) + D][tap_dx(R, 0, t) + D],
+                   pe);
+      });
+  }
+
   // Faces of row k and the update of its cells.  With phi_b = sum_i fbar_i,
   // Eq. (27) gives dt f_b,i = dt*alpha*fbar_i + dt w_i (P + e_i . Q),
   // P = beta phi_b, Q = 3 P u_b + gamma S_b/w-part, so the flux differences
@@ -385,19 +523,9 @@ struct Marcher {
   // a collision part in the 3 numbers (P, Qx, Qy) of each face.
   template <bool upd>
   __device__ __forceinline__ void face_stage(int k) {
-    const int L = LP + lane;
     const int kk = wrapi(k, a.ny);
-    // stage B: Q of the row (Eq. 32 value) and phi^n, the history plane of
-    // stage A's f~(t') (the input), read before the face work so that the
-    // loads are in flight meanwhile; lanes outside the owned columns read
-    // nothing (out-of-range offsets read 0)
     T qv[10];
-    if (STAGE == STAGE_B && upd) {
-      const unsigned oq = owned ? (unsigned)((kk * a.CH + ocol) * (int)sizeof(T)) : OFF_NONE;
-#pragma unroll
-      for (int i = 0; i < 9; i++) qv[i] = bload(raux, oq + i * (unsigned)(OWN * sizeof(T)), T(0));
-      qv[9] = bload(rin, oq + 9 * (unsigned)(OWN * sizeof(T)), T(0));
-    }
+    if (STAGE == STAGE_B && upd) load_q(kk, qv);
     T out[9];
     T phN = T(0), phE = T(0);
 #pragma unroll
@@ -422,29 +550,114 @@ struct Marcher {
       // LDS latency
       __builtin_amdgcn_sched_barrier(0);
     }
+    T PN, QNx, QNy, eP, eQx, eQy;
+    north_moments(kk, phN, sxp[0], syp[0], sxp[1], syp[1], PN, QNx, QNy);
+    const T dP = PN - PS, dQx = QNx - QSx, dQy = QNy - QSy;
+    PS = PN; QSx = QNx; QSy = QNy;
+    if (!upd) return;
+    east_moments(kk, phE, sxp[0], syp[0], eP, eQx, eQy);
+    double cs = 0.0, cf0 = 0.0;
+    T bp[9];
+#pragma unroll
+    for (int i = 0; i < 9; i++) bp[i] = bfp[slotB(k)][i][LP + lane];
+    update_cells(kk, bp, out, dP, dQx, dQy, eP, eQx, eQy, cp[0], cx[0], cy[0], ph[0], qv, cs, cf0);
+    if (FIX_SUM) {
+      // phi^{n+1} of the row (owned lanes) into the group total; a group
+      // never straddles two segments (segments are whole groups), so its sum
+      // -- lanes in a fixed butterfly after rows in order -- does not depend
+      // on the tiling
+      macc += owned ? cs : 0.0;
+      mcnt += cf0;
+      const bool gend = (k & (MASS_GROUP - 1)) == MASS_GROUP - 1 || k == a.ny - 1;
+      double v = 0.0, w = 0.0;
+      if (gend) {
+        v = macc;
+        w = mcnt;
+        lane_totals(v, w);
+        macc = 0.0;
+        mcnt = 0.0;
+      }
+      // issued on every row; only lane 0 at the end of a group writes
+      const unsigned po = (gend && lane == 0) ? (unsigned)(16 * (k / MASS_GROUP)) : OFF_NONE;
+      bstore(v, rpart, po);
+      bstore(w, rpart, po + 8);
+    }
+  }
+
+  // sums over the lanes, in a fixed butterfly
+  static __device__ __forceinline__ void lane_totals(double& v, double& w) {
+#pragma unroll
+    for (int m = 1; m < LANES; m <<= 1) {
+      v += __shfl_xor(v, m);
+      w += __shfl_xor(w, m);
+    }
+  }
+
+  // stage B: Q of the row (Eq. 32 value) and phi^n, the history plane of
+  // stage A's f~(t') (the input), read before the face work so that the
+  // loads are in flight meanwhile; lanes outside the owned columns read
+  // nothing (out-of-range offsets read 0)
+  __device__ __forceinline__ void load_q(int kk, T (&qv)[10]) const {
+    const unsigned oq = owned ? (unsigned)((kk * a.CH + ocol) * (int)sizeof(T)) : OFF_NONE;
+#pragma unroll
+    for (int i = 0; i < 9; i++) qv[i] = bload(raux, oq + i * (unsigned)(OWN * sizeof(T)), T(0));
+    qv[9] = bload(rin, oq + 9 * (unsigned)(OWN * sizeof(T)), T(0));
+  }
+
+  // collision part of the north faces of (wrapped) row kk: phN = dt*alpha*phi_b
+  // there, (sx0, sy0) and (sx1, sy1) s of the rows kk and kk + 1
+  __device__ __forceinline__ void north_moments(int kk, T phN, T sx0, T sy0, T sx1, T sy1, T& PN,
+                                                T& QNx, T& QNy) const {
     const cptr<T> UY = taby;
     const cptr<T> VY = taby + (2 * a.ny + 2);
     // north face (x + 1/2, y + 1): S_b = mean of the two cells; a velocity
     // array gives the mean of the two cells' velocities (steady)
-    T ubN, vbN, uk = T(0), vk = T(0);
+    T ubN, vbN;
     if (VARR) {
-      const int k1 = wrapi(k + 1, a.ny);
-      uk = uv_at(0, kk);
-      vk = uv_at(1, kk);
-      ubN = T(0.5) * (uk + uv_at(0, k1));
-      vbN = T(0.5) * (vk + uv_at(1, k1));
+      const int k1 = wrapi(kk + 1, a.ny);
+      ubN = T(0.5) * (uv_at(0, kk) + uv_at(0, k1));
+      vbN = T(0.5) * (uv_at(1, kk) + uv_at(1, k1));
     } else {
       ubN = gH * (UXc * UY[2 * kk + 2]);
       vbN = gH * (VXc * VY[2 * kk + 2]);
     }
     // phN = dt*alpha*phi_b; P = beta phi_b, Q = 3 P u_b + gamma s_b, all
     // carried pre-multiplied by dt so that dt f_b,i = pn_i + w_i (P + e_i.Q)
-    const T PN = a.pscale * phN;
-    const T QNx = fma(T(3) * PN, ubN, a.gdt * (sxp[0] + sxp[1]));
-    const T QNy = fma(T(3) * PN, vbN, a.gdt * (syp[0] + syp[1]));
-    const T dP = PN - PS, dQx = QNx - QSx, dQy = QNy - QSy;
-    PS = PN; QSx = QNx; QSy = QNy;
-    if (!upd) return;
+    PN = a.pscale * phN;
+    QNx = fma(T(3) * PN, ubN, a.gdt * (sx0 + sx1));
+    QNy = fma(T(3) * PN, vbN, a.gdt * (sy0 + sy1));
+  }
+
+  // collision part of the east faces of (wrapped) row kk, less that of the
+  // west faces: phE = dt*alpha*phi_b of the east faces, (sx0, sy0) s of the row
+  __device__ __forceinline__ void east_moments(int kk, T phE, T sx0, T sy0, T& eP, T& eQx,
+                                               T& eQy) const {
+    const cptr<T> UY = taby;
+    const cptr<T> VY = taby + (2 * a.ny + 2);
+    T uk = T(0), vk = T(0);
+    if (VARR) {
+      uk = uv_at(0, kk);
+      vk = uv_at(1, kk);
+    }
+    // east face (x + 1, y + 1/2): S_b = mean of own and east cell
+    const T ubE = VARR ? T(0.5) * (uk + from_right(uk)) : gH * (UXe * UY[2 * kk + 1]);
+    const T vbE = VARR ? T(0.5) * (vk + from_right(vk)) : gH * (VXe * VY[2 * kk + 1]);
+    const T PE = a.pscale * phE;
+    const T QEx = fma(T(3) * PE, ubE, a.gdt * (sx0 + from_right(sx0)));
+    const T QEy = fma(T(3) * PE, vbE, a.gdt * (sy0 + from_right(sy0)));
+    eP = PE - from_left(PE);
+    eQx = QEx - from_left(QEx);
+    eQy = QEy - from_left(QEy);
+  }
+
+  // The rest of the update of (wrapped) row kk and its stores: bp = fbar+ of the
+  // row, out = the per-velocity flux differences, (dP, dQ) the collision part of the
+  // north less the south faces, (eP, eQ) of the east less the west ones,
+  // (pC, mx, my) phi and m of the cells, pN phi^n; cs, cf0: the cell's new phi
+  // and whether it takes the next mass correction (FIX_SUM).
+  __device__ __forceinline__ void update_cells(int kk, const T (&bp)[9], T (&out)[9], T dP, T dQx, T dQy,
+                                               T eP, T eQx, T eQy, T pC, T mx, T my, T pN,
+                                               const T (&qv)[10], double& cs, double& cf0) const {
     {
       // i = 3, 7 (axis, w = 1/9) and 2, 4, 6, 8 (diagonal, w = 1/36)
       const T a1 = T(1.0 / 9.0) * dP, ay1 = T(1.0 / 9.0) * dQy;
@@ -456,13 +669,6 @@ struct Marcher {
       out[6] += (a2 - ax2) - ay2;
       out[8] += (a2 + ax2) - ay2;
     }
-    // east face (x + 1, y + 1/2): S_b = mean of own and east cell
-    const T ubE = VARR ? T(0.5) * (uk + from_right(uk)) : gH * (UXe * UY[2 * kk + 1]);
-    const T vbE = VARR ? T(0.5) * (vk + from_right(vk)) : gH * (VXe * VY[2 * kk + 1]);
-    const T PE = a.pscale * phE;
-    const T QEx = fma(T(3) * PE, ubE, a.gdt * (sxp[0] + from_right(sxp[0])));
-    const T QEy = fma(T(3) * PE, vbE, a.gdt * (syp[0] + from_right(syp[0])));
-    const T eP = PE - from_left(PE), eQx = QEx - from_left(QEx), eQy = QEy - from_left(QEy);
     {
       // i = 1, 5 (axis) and 2, 4, 6, 8 (diagonal)
       const T a1 = T(1.0 / 9.0) * eP, ax1 = T(1.0 / 9.0) * eQx;
@@ -479,10 +685,9 @@ struct Marcher {
     // (held since its cell stage) instead of reading f~ of the row again.
     // Then f~^{n+1} = f~+ + dt L (Eq. 21).  The T3S3 stages write their
     // outputs in the same form (see Stage).
-    double cs = 0.0, cf0 = 0.0;
     {
       T x[9];
-      collision_target(cp[0], cx[0], cy[0], x);
+      collision_target(pC, mx, my, x);
       // the new row is not read again by this launch: stream it past the
       // caches; lanes outside the owned columns store nothing
       const unsigned ob = owned ? (unsigned)((kk * a.CH + ocol) * (int)sizeof(T)) : OFF_NONE;
@@ -494,12 +699,11 @@ struct Marcher {
 #pragma unroll
         for (int j = 0; j < 9; j++) {
           const int i = j < 8 ? j + 1 : 0;
-          const T bp = bfp[slotB(k)][i][L];
-          T dx = x[i] - bp;
+          T dx = x[i] - bp[i];
           if (ZSUM) {
             if (i != 0) dsum += dx; else dx = -dsum;
           }
-          const T tfp = fma(a.kap, dx, bp);
+          const T tfp = fma(a.kap, dx, bp[i]);
           const T v = tfp + out[i];
           bstore(v, rdst, ob + i * PL);
           if (FIX_SUM) {
@@ -507,30 +711,28 @@ struct Marcher {
             if (i == 0 && owned && v < T(MASS_FIT_MAX)) cf0 = 1.0;
           }
         }
-        bstore(ph[0], rdst, ob + 9 * PL);
+        bstore(pN, rdst, ob + 9 * PL);
       } else if (STAGE == STAGE_A) {
         // f~(t') = f~+ + (1/3) dt L* and Q = f^n + (3/7) dt L*, with
         // f~+ = fbar+ + kap (X - fbar+) and f^n = fbar+ - kap (X - fbar+)
 #pragma unroll
         for (int j = 0; j < 9; j++) {
           const int i = j < 8 ? j + 1 : 0;
-          const T bp = bfp[slotB(k)][i][L];
-          T d = x[i] - bp;
+          T d = x[i] - bp[i];
           if (ZSUM) {
             if (i != 0) dsum += d; else d = -dsum;
           }
-          bstore(fma(a.wo1, out[i], fma(a.kap, d, bp)), rdst, ob + i * PL);
-          bstore(fma(a.wo2, out[i], fma(-a.kap, d, bp)), rdst2, ob + i * PL);
+          bstore(fma(a.wo1, out[i], fma(a.kap, d, bp[i])), rdst, ob + i * PL);
+          bstore(fma(a.wo2, out[i], fma(-a.kap, d, bp[i])), rdst2, ob + i * PL);
         }
-        bstore(ph[0], rdst, ob + 9 * PL);   // Q needs no history plane: stage B reads this one
+        bstore(pN, rdst, ob + 9 * PL);   // Q needs no history plane: stage B reads this one
       } else {
         // f^^{n+1} = Q + kap (X' - fbar+) + (4/7) dt L**, kap (X' - fbar+)
         // being (3/4) dt (Omega + S) at t'; phi^n goes on as the history
 #pragma unroll
         for (int j = 0; j < 9; j++) {
           const int i = j < 8 ? j + 1 : 0;
-          const T bp = bfp[slotB(k)][i][L];
-          T dx = x[i] - bp;
+          T dx = x[i] - bp[i];
           if (ZSUM) {
             if (i != 0) dsum += dx; else dx = -dsum;
           }
@@ -543,31 +745,6 @@ struct Marcher {
         }
         bstore(qv[9], rdst, ob + 9 * PL);
       }
-    }
-    if (FIX_SUM) {
-      // phi^{n+1} of the row (owned lanes) into the group total; a group
-      // never straddles two segments (segments are whole groups), so its sum
-      // -- lanes in a fixed butterfly after rows in order -- does not depend
-      // on the tiling
-      macc += owned ? cs : 0.0;
-      mcnt += cf0;
-      const bool gend = (k & (MASS_GROUP - 1)) == MASS_GROUP - 1 || k == a.ny - 1;
-      double v = 0.0, w = 0.0;
-      if (gend) {
-        v = macc;
-        w = mcnt;
-#pragma unroll
-        for (int m = 1; m < LANES; m <<= 1) {
-          v += __shfl_xor(v, m);
-          w += __shfl_xor(w, m);
-        }
-        macc = 0.0;
-        mcnt = 0.0;
-      }
-      // issued on every row; only lane 0 at the end of a group writes
-      const unsigned po = (gend && lane == 0) ? (unsigned)(16 * (k / MASS_GROUP)) : OFF_NONE;
-      bstore(v, rpart, po);
-      bstore(w, rpart, po + 8);
     }
   }
 
@@ -643,67 +820,9 @@ __device__ __forceinline__ void march_tile(const StepArgs<T>& a, int64_t n,
                                            int seg, T (*s_bfp)[9][lrow(R)]) {
   using M = Marcher<T, R, MFIX, STAGE, VARR>;
   M m{a, src, as_const(cf), tabx, as_const(taby), uv, s_bfp};
-  const int lane = threadIdx.x;
-  const int x0 = strip * OWN;
-  m.lane = lane;
-  const int c0 = (x0 - HALO + lane) % a.nx;
-  m.col = c0 < 0 ? c0 + a.nx : c0;
-  {
-    const int cs = m.col / OWN;
-    m.loff = (int64_t)cs * a.ny * a.CH + (m.col - cs * OWN);
-  }
-  m.loffx = m.loff;
-  if (M::WIDE && (lane == 0 || lane == LANES - 1)) {
-    // the column beyond the lane, outwards (wrapped)
-    int cx = lane == 0 ? m.col - 1 : m.col + 1;
-    cx = cx < 0 ? cx + a.nx : (cx >= a.nx ? cx - a.nx : cx);
-    const int cs = cx / OWN;
-    m.loffx = (int64_t)cs * a.ny * a.CH + (cx - cs * OWN);
-  }
-  const int nown = min(OWN, a.nx - x0);
-  m.owned = lane >= HALO && lane < HALO + nown;
-  m.ocol = lane - HALO;
-  {
-    // the strip's own chunk column: ny rows of CH elements
-    const int64_t c0 = (int64_t)strip * a.ny * a.CH;
-    const unsigned nb = (unsigned)((int64_t)a.ny * a.CH * (int64_t)sizeof(T));
-    m.rdst = make_rsrc(dst + c0, nb);
-    m.rdst2 = make_rsrc((STAGE == STAGE_A ? dst2 : dst) + c0, nb);
-    m.raux = make_rsrc((STAGE == STAGE_B ? aux : src) + c0, nb);   // used by stage B
-    m.rin = make_rsrc(src + c0, nb);
-  }
-  m.y0 = seg * a.seg_rows;
-  m.y1 = min(m.y0 + a.seg_rows, a.ny);
-  m.base = m.y0 - M::LAG - 1;   // at or below every ring row the tile touches
-  if (!VARR) {
-    const int ce = m.col + 1;  // east face of the column (x + 1), unwrapped
-    m.UXc = tabx[2 * m.col + 1];
-    m.VXc = tabx[(2 * a.nx + 2) + 2 * m.col + 1];
-    m.UXe = tabx[2 * ce];
-    m.VXe = tabx[(2 * a.nx + 2) + 2 * ce];
-  }
-  // time factors of the velocity at the stage's base time and at the time of
-  // the earlier phi (cells), and at base + its half step (faces)
-  const double tn = (double)n * a.dtd;
-  const double tb = tn + a.toff;
-  double gn = 1.0, gp = 1.0, gh = 1.0;
-  if (a.period > 0.0) {
-    gn = cos(M_PI * tb / a.period);
-    gp = cos(M_PI * (tn + a.troff) / a.period);
-    gh = cos(M_PI * (tb + a.hd) / a.period);
-  }
-  m.gN = T(gn);
-  m.gP = T(gp);
-  m.gH = T(gh);
-  m.jscale = ((n == 0 && a.jfirst) || a.jzero) ? T(0) : a.jinv;
-  if (MFIX) {
-    m.cw0 = T(wq(0) * pend);
-    m.cw1 = T(wq(1) * pend);
-    m.cw2 = T(wq(2) * pend);
-    m.fitmax = T(fitmax);
-    m.part_row = part + 2 * (int64_t)strip * a.ngroups;
-    m.rpart = make_rsrc(m.part_row, (unsigned)(16 * a.ngroups));
-  }
+  m.place((int)threadIdx.x, strip, seg * a.seg_rows, a.seg_rows, dst, dst2, aux, part, pend,
+          fitmax);
+  m.flow(n);
   m.run();
 }
 

@@ -27,7 +27,8 @@ struct dugks_plan {
     int jfirst;
   } st[3];
   double compact2[dugks::NCOMPACT];  // T3S3 stage B stencil (compact: stage A)
-  int seg_rows, nstrips, nsegs;
+  int seg_rows, nstrips, nsegs;   // of the march
+  int tile;                  // rows of the tile kernel's tiles (4 or 8); 0: the march
   std::vector<double> tabx, taby;
   // the constant head of every state of this plan (header, coefficient and
   // velocity tables in the plan's precision), staged once in pinned host memory
@@ -53,18 +54,51 @@ inline const T* at(const void* state, size_t off) {
 inline bool aligned(const void* ptr) { return ((uintptr_t)ptr & 255u) == 0; }
 
 
+// the buffers of one launch (see Stage)
 template <typename T>
-inline StepBufs<T> step_bufs(const dugks_plan* P, void* state, int64_t n) {
+struct StageBufs {
+  const T* src;
+  T* dst;
+  T* dst2;
+  const T* aux;
+  const T* cf;
+  const T* tabx;
+  const T* taby;
+  const T* uv;
+  double* part;
+  StateHeader* hdr;
+};
+
+template <typename T>
+inline StageBufs<T> stage_bufs(const dugks_plan* P, void* state, int64_t n, int stage) {
   const Layout& L = P->L;
   const int b = (int)(n & 1);
-  StepBufs<T> q;
+  StageBufs<T> q;
   q.src = at<T>(state, L.off_buf[b]);
   q.dst = at<T>(state, L.off_buf[b ^ 1]);
+  q.dst2 = nullptr;
+  q.aux = nullptr;
   q.cf = at<T>(state, L.off_coef);
+  if (stage == STAGE_A) {           // f^^n -> f~(t'), Q
+    q.dst = at<T>(state, L.off_mid);
+    q.dst2 = at<T>(state, L.off_q);
+  } else if (stage == STAGE_B) {    // f~(t'), Q -> f^^{n+1}
+    q.src = at<T>(state, L.off_mid);
+    q.aux = at<T>(state, L.off_q);
+    q.cf = at<T>(state, L.off_coef2);
+  }
   q.tabx = at<T>(state, L.off_tabx);
   q.taby = at<T>(state, L.off_taby);
+  q.uv = P->p.vel_kind == DUGKS_VEL_ARRAYS ? at<T>(state, L.off_vel) : nullptr;
+  q.part = at<double>(state, L.off_groups);
+  q.hdr = at<StateHeader>(state, 0);
   return q;
 }
+
+// One launch of the tile kernel (plans with P->tile != 0).
+template <typename T>
+void launch_tile(const dugks_plan* P, int stage, const StageBufs<T>& q, int64_t n,
+                 hipStream_t s);
 
 template <typename T>
 inline StepArgs<T> step_args(const dugks_plan* P, int stage = STAGE_T2) {
