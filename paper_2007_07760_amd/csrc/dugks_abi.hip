@@ -224,16 +224,21 @@ int validate(const dugks_params* p) {
   return DUGKS_OK;
 }
 
-// Default rows per wavefront.  Resident wavefronts of the step kernel on one
-// MI355X: 256 CUs, each 4 SIMDs x step_waves (the register budget the kernel
-// variant is built for; the LDS ring fits that many).  A wavefront marches
-// seg + 4 rows of work; the launch runs in ceil(tiles / resident) rounds, so
-// pick the segment that minimises rounds * (seg + 4): whole rounds, little
+// Wavefronts of the step kernel resident on one MI355X: 256 CUs, each 4 SIMDs x
+// step_waves (the register budget of the kernel variant), as many as their
+// fbar+ rings leave room for in 160 KB of LDS.
+long resident_wavefronts(const dugks_params& p) {
+  const size_t esize = p.precision == DUGKS_F64 ? 8 : 4;
+  const int waves = 4 * step_waves((int)esize, p.recon, (p.flags & DUGKS_FLAG_MASS_FIX) != 0);
+  return 256L * std::min(waves, (int)(160 * 1024 / (ring_rows(p.recon) * 9 * lrow(p.recon) * esize)));
+}
+
+// The height that minimises rounds * (seg + 4), a launch running in
+// ceil(tiles / resident) rounds of seg + 4 rows of work: whole rounds, little
 // halo.  Segments are whole mass groups (multiples of MASS_GROUP rows).
-int default_tile_rows(const dugks_params& p, int nstrips) {
-  const int per_cu = 4 * step_waves(p.precision == DUGKS_F64 ? 8 : 4, p.recon,
-                                    (p.flags & DUGKS_FLAG_MASS_FIX) != 0);
-  const long resident = 256L * per_cu;
+int whole_round_rows(const dugks_params& p, int nstrips) {
+  const long resident = 256L * 4 * step_waves(p.precision == DUGKS_F64 ? 8 : 4, p.recon,
+                                              (p.flags & DUGKS_FLAG_MASS_FIX) != 0);
   int best = 64;
   long best_cost = -1;
   for (int seg = 16; seg <= 256; seg += MASS_GROUP) {
@@ -246,6 +251,27 @@ int default_tile_rows(const dugks_params& p, int nstrips) {
     }
   }
   return best;
+}
+
+// Default rows per marching wavefront.  16, the shortest: although its halo
+// rows cost a fifth of the arithmetic, the wavefronts of neighbouring strips
+// stay in step, so the lines they share are still cached, and the last round
+// is short.  us per step at 16 / 72-128 rows (the whole-round heights): 4096^2
+// FP64 upwind-3 602 / 692, FP32 corrected 367 / 469, velocity arrays 715 / 821,
+// T3S3 1779 / 2006; 2900^2 FP64 309 / 325, FP32 corrected 194 / 244.  Only
+// where 16-row tiles make a second round that is not full, the shortest height
+// that makes one round: 1536^2 FP64 97 at 24 rows against 105 at 16, central-4
+// 1280^2 110 at 24 against 136, FP32 corrected T3S3 2048^2 277 at 32 against
+// 288.  Upwind-5, one wavefront per SIMD in FP64, keeps whole rounds (2048^2
+// 377 against 432 at 16).
+int default_tile_rows(const dugks_params& p, int nstrips) {
+  if (p.recon == DUGKS_UPWIND5) return whole_round_rows(p, nstrips);
+  const long resident = resident_wavefronts(p);
+  auto tiles = [&](int seg) { return (long)nstrips * ((p.ny + seg - 1) / seg); };
+  if (tiles(16) <= resident || tiles(16) >= 2 * resident) return 16;
+  int seg = 24;
+  while (tiles(seg) > resident) seg += MASS_GROUP;
+  return seg;
 }
 
 // Rows of the tile kernel's tiles, or 0 where the march runs: heights up to
@@ -543,13 +569,19 @@ int dugks_plan_create(const dugks_params* p, dugks_plan** out) {
   make_tables(P);
   P->nstrips = (p->nx + OWN - 1) / OWN;
   P->tile = tile_kernel_rows(*p, P->nstrips);
-  P->seg_rows = p->tile_rows > TILE_MAX_ROWS
-                    ? p->tile_rows
-                    : (p->tile_rows > 0 ? 16 : default_tile_rows(*p, P->nstrips));
-  if (p->flags & DUGKS_FLAG_MASS_FIX)   // whole mass groups per segment
-    P->seg_rows = (P->seg_rows + MASS_GROUP - 1) / MASS_GROUP * MASS_GROUP;
-  if (P->seg_rows > p->ny) P->seg_rows = p->ny;
+  auto rows = [p](int r) {
+    if (p->flags & DUGKS_FLAG_MASS_FIX)   // whole mass groups per segment
+      r = (r + MASS_GROUP - 1) / MASS_GROUP * MASS_GROUP;
+    return std::min(r, p->ny);
+  };
+  P->seg_rows = rows(p->tile_rows > 0 ? p->tile_rows : default_tile_rows(*p, P->nstrips));
   P->nsegs = (p->ny + P->seg_rows - 1) / P->seg_rows;
+  // dugks_step_many_noalloc: its work list is of a fixed length, so large
+  // grids keep the taller tiles of whole rounds, and short ones are not shorter
+  // than 16 rows
+  P->many_rows = rows(p->tile_rows > 0 ? std::max(16, p->tile_rows)
+                                       : whole_round_rows(*p, P->nstrips));
+  P->many_segs = (p->ny + P->many_rows - 1) / P->many_rows;
   *out = P;
   return DUGKS_OK;
 }

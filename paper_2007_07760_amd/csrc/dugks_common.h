@@ -122,6 +122,11 @@ __host__ __device__ constexpr int lpad(int recon) { return wide(recon) ? 3 : 2; 
 __host__ __device__ constexpr int lrow(int recon) { return LANES + 2 * lpad(recon); }
 
 
+// Rows of the march's fbar+ ring in LDS.
+__host__ __device__ constexpr int ring_rows(int recon) {
+  return wide(recon) ? 6 : (recon == DUGKS_CENTRAL4 ? 5 : 4);
+}
+
 // Wavefronts per SIMD the step kernels are built for (the register budget of
 // each variant: 512 / waves VGPRs), and so resident per CU (x 4 SIMDs).  The
 // FP32 variants with the fused mass correction or the 5-row ring of central-4

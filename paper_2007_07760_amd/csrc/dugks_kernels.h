@@ -203,7 +203,7 @@ struct Marcher {
   // (so that fbar+ is right on every lane); the narrow patches: a 4-row ring
   // (5 for central-4), faces 2 rows behind
   static constexpr bool WIDE = wide(R);
-  static constexpr int RB = RING_ROWS ? RING_ROWS : (WIDE ? 6 : ((R == DUGKS_CENTRAL4) ? 5 : 4));
+  static constexpr int RB = RING_ROWS ? RING_ROWS : ring_rows(R);
   static constexpr int LAG = WIDE ? 3 : 2;
   static constexpr int LP = RING_ROWS ? 0 : lpad(R);
   static constexpr int LR = RING_ROWS ? LANES : lrow(R);

@@ -132,7 +132,7 @@ int noalloc_setup(const dugks_plan* const* plans, void* const* states, const int
     c.count = std::min(DESC_CHUNK, n - first);
     for (int k = 0; k < c.count; k++) {
       const dugks_plan* P = plans[first + k];
-      c.d[k] = make_grid_desc<T>(P, states[first + k], P->seg_rows);
+      c.d[k] = make_grid_desc<T>(P, states[first + k], P->many_rows);
       c.st[k].n = steps[first + k];
       c.st[k].target = steps[first + k] + nsteps;
     }
@@ -177,7 +177,7 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
   // rows a grid's tiles march in all
   auto work = [plans](int j) {
     const dugks_plan* P = plans[j];
-    return (int64_t)P->nstrips * ((int64_t)P->p.ny + 5 * (int64_t)P->nsegs);
+    return (int64_t)P->nstrips * ((int64_t)P->p.ny + 5 * (int64_t)P->many_segs);
   };
   std::stable_sort(order, order + n, [&](int a, int b) { return work(a) > work(b); });
   int queue_of[NOALLOC_GRIDS];
@@ -191,7 +191,7 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
   }
   std::stable_sort(order, order + n, [&](int a, int b) {
     if (queue_of[a] != queue_of[b]) return queue_of[a] < queue_of[b];
-    return plans[a]->seg_rows > plans[b]->seg_rows;
+    return plans[a]->many_rows > plans[b]->many_rows;
   });
   starts.nq = NQUEUE;
   int64_t total = 0;
@@ -201,7 +201,7 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
     while (q <= queue_of[order[k]]) starts.qstart[q++] = (int32_t)total;
     starts.start[k] = (int32_t)total;
     starts.grid[k] = order[k];
-    total += (int64_t)P->nstrips * P->nsegs;
+    total += (int64_t)P->nstrips * P->many_segs;
     if (total > NOALLOC_ITEMS) return DUGKS_EINVAL;   // beyond the array's work list
   }
   while (q <= NQUEUE) starts.qstart[q++] = (int32_t)total;
