@@ -326,14 +326,18 @@ int dugks_batch_steps(const dugks_batch *batch, int64_t *out, void *stream);
  * `stream` when `out` is pinned or on the device).  Errors: EINVAL, EDEVICE. */
 int dugks_batch_status(const dugks_batch *batch, int32_t *out, void *stream);
 
-/* Rows per tile of every grid (a multiple of 8; grids shorter than that are
- * one tile high).  Default 64.  set: EINVAL unless 8 <= rows <= 65536 and
- * rows % 8 == 0; takes effect at the next commit. */
+/* Rows per marching tile of every grid (a multiple of 8; grids shorter than
+ * that are one tile high).  Until it is set each commit chooses it, and whether
+ * block tiles of up to 8 rows are taken instead (batches too small to fill the
+ * chip with marching wavefronts).  set: EINVAL unless 8 <= rows <= 65536 and
+ * rows % 8 == 0 (8: block tiles); takes effect at the next commit. */
 int dugks_batch_tile_rows(const dugks_batch *batch);
 int dugks_batch_set_tile_rows(dugks_batch *batch, int32_t rows);
 /* Autotuner: time the persistent step kernel over the attached, active grids
  * (`reps` launches per candidate tile height from 16 to 256 rows, HIP events
- * on `stream`), keep the fastest and commit it.  The timed launches write only
+ * on `stream`), keep the fastest and commit it; where the block tiles are
+ * faster still, the batch takes those, and rows_out is the best marching
+ * height.  The timed launches write only
  * each grid's next-step buffer and mass partials, which the next real step
  * overwrites, so the states and results are unchanged.  Blocks until done.
  * Errors: EINVAL, EDEVICE. */
@@ -355,7 +359,8 @@ int dugks_batch_tune(dugks_batch *batch, int32_t reps, int32_t *rows_out,
  * travel as kernel arguments; no hipMalloc, hipFree, pinned staging or graph.
  *  - plans, states, steps: host arrays of n entries.  Every plan of one
  *    precision, reconstruction, DUGKS_FLAG_MASS_FIX setting and time scheme;
- *    each grid is tiled at its own plan's tile height.
+ *    each grid is tiled at its own plan's tile height (block tiles, as a
+ *    batch's, where all grids together are few tiles).
  *  - Limits: 1 <= n <= 256 grids and at most 116192 tiles (strips x row
  *    segments) over all grids; beyond them DUGKS_EINVAL, before anything is
  *    launched.

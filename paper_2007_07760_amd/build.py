@@ -14,7 +14,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # every HIP source of the library (csrc/*.hip)
 SOURCES = sorted(f for f in os.listdir(CSRC) if f.endswith(".hip"))
 HEADERS = ["dugks_common.h", "dugks_kernels.h", "dugks_tile.h", "dugks_plan.h",
-           "dugks_batch_impl.h", "dugks_tile_impl.h"]
+           "dugks_batch_impl.h", "dugks_tile_impl.h", "dugks_tile_batch_impl.h"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

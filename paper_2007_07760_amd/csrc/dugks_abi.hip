@@ -339,7 +339,7 @@ int launch_stage(const dugks_plan* P, void* state, int64_t n, hipStream_t s, boo
   const Layout& L = P->L;
   const StageBufs<T> q = stage_bufs<T>(P, state, n, STAGE);
   if (P->tile)
-    launch_tile<T>(P, STAGE, q, n, s);
+    launch_tile<T, STAGE>(P, q, n, s);
   else
     launch_march<T, MFIX, STAGE>(P, q, n, s);
   if (MFIX && fix)

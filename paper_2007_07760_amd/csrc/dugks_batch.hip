@@ -19,9 +19,9 @@ namespace {
 
 constexpr int NSTAGE = 3;   // pinned staging buffers in flight
 
-// Tile heights the autotuner tries (whole mass groups).
-constexpr int TUNE_ROWS[] = {16, 24, 32, 48, 64, 96, 128, 192, 256};
-constexpr int DEFAULT_ROWS = 64;
+// Tile heights the autotuner tries (whole mass groups; 0: the block tiles).
+constexpr int TUNE_ROWS[] = {0, 16, 24, 32, 48, 64, 96, 128, 192, 256};
+constexpr int DEFAULT_ROWS = 64;   // reported until the first commit chooses
 
 struct Slot {
   const dugks_plan* plan = nullptr;
@@ -37,7 +37,9 @@ namespace dugks {
 template <typename T, int R, bool MFIX>
 static int launch_batch_step(const BatchDev& D, int scheme, hipStream_t s, bool finish) {
   const GridDesc<T>* desc = static_cast<const GridDesc<T>*>(D.desc);
-  if (scheme == DUGKS_T3S3) {   // the two stages over every tile, in turn
+  if (D.tile) {
+    launch_batch_tile<T>(D, R, MFIX, scheme, s);
+  } else if (scheme == DUGKS_T3S3) {   // the two stages over every tile, in turn
     hipLaunchKernelGGL((batch_step_kernel<T, R, MFIX, STAGE_A>), dim3(D.grid_blocks),
                        dim3(LANES), 0, s, desc, D.steps, D.ctl, D.head);
     hipLaunchKernelGGL((batch_step_kernel<T, R, MFIX, STAGE_B>), dim3(D.grid_blocks),
@@ -130,18 +132,24 @@ struct dugks_batch {
   std::vector<int32_t> qstart;        // queue q: items [qstart[q], qstart[q + 1])
   int nq = 1;
   bool desc_dirty = true;
-  int rows = DEFAULT_ROWS;            // tile height (rows per item)
+  int rows = DEFAULT_ROWS;            // height of the marching tiles
+  int tile = 0;                       // rows of the list's block tiles; 0: marching tiles
+  bool given = false;                 // height and kind are the caller's (or the
+  int given_tile = 0;                 // autotuner's) choice; else each commit chooses
   int grid_blocks = 0;                // resident wavefronts of the persistent kernel
+  int tile_blocks = 0;                // resident blocks of the tile kernel
   // pinned staging ring: [ctl][desc table][steps][items]
   void* stage[NSTAGE] = {};
   size_t stage_bytes[NSTAGE] = {};
   hipEvent_t stage_ev[NSTAGE] = {};
   int stage_next = 0;
-  // graph of K steps
+  // graphs of K steps: over marching tiles, over block tiles
   hipStream_t cap_stream = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  int graph_k = 0;
+  struct Graph {
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    int k = 0;
+  } graphs[2];
 };
 
 namespace {
@@ -149,6 +157,27 @@ namespace {
 template <typename T>
 GridDesc<T> make_desc(const Slot& s, int rows) {
   return make_grid_desc<T>(s.plan, s.state, rows);
+}
+
+// Work list of block tiles: every grid's tiles, segment by segment, cut into
+// NQUEUE equal bands, one per queue (starting at another queue for each slot).
+// The blocks take fixed shares of their queue, so the queues have to stay equal
+// also when some grids have reached their targets.
+void build_tile_items(dugks_batch* B, int rows) {
+  std::vector<BatchItem> queue[NQUEUE];
+  for (int k = 0; k < B->cap; k++) {
+    const Slot& s = B->slots[k];
+    if (!s.plan) continue;
+    const int64_t n = (int64_t)s.plan->nstrips * ((s.plan->p.ny + rows - 1) / rows);
+    for (int64_t i = 0; i < n; i++)
+      queue[(i * NQUEUE / n + k) % NQUEUE].push_back({k, (int32_t)i});
+  }
+  B->qstart.assign(NQUEUE + 1, 0);
+  for (int q = 0; q < NQUEUE; q++) {
+    B->items.insert(B->items.end(), queue[q].begin(), queue[q].end());
+    B->qstart[q + 1] = (int32_t)B->items.size();
+  }
+  B->nq = B->items.empty() ? 1 : NQUEUE;
 }
 
 // Work list for tile height `rows`, cut into NQUEUE queues of about equal
@@ -159,6 +188,10 @@ GridDesc<T> make_desc(const Slot& s, int rows) {
 // queue the taller tiles come first, so that the short ones fill the tail.
 void build_items(dugks_batch* B, int rows) {
   B->items.clear();
+  if (B->tile) {
+    build_tile_items(B, rows);
+    return;
+  }
   struct Keyed {
     int h;
     BatchItem it;
@@ -255,7 +288,8 @@ int upload(dugks_batch* B, hipStream_t s) {
     return hip_status(e);
   if (B->desc_dirty) {
     GridDesc<T>* dt = reinterpret_cast<GridDesc<T>*>(h + off_desc);
-    for (int k = 0; k < B->cap; k++) dt[k] = make_desc<T>(B->slots[k], B->rows);
+    for (int k = 0; k < B->cap; k++)
+      dt[k] = make_desc<T>(B->slots[k], B->tile ? B->tile : B->rows);
     if ((e = hipMemcpyAsync(B->d_desc, dt, B->cap * sizeof(GridDesc<T>), hipMemcpyHostToDevice,
                             s)))
       return hip_status(e);
@@ -290,18 +324,49 @@ int upload(dugks_batch* B, hipStream_t s) {
 // state is unchanged, since the finish kernel never runs)
 int batch_launch(dugks_batch* B, hipStream_t s, bool finish) {
   const BatchDev D{B->d_desc, B->d_steps, B->d_status, B->d_ctl, B->d_head, B->cap,
-                   B->grid_blocks};
+                   B->grid_blocks, B->tile, B->tile_blocks};
   return launch_batch(D, B->precision, B->recon, B->mfix, B->scheme, s, finish);
 }
 
+// The kind and height of the tiles, where the caller has given none: as for
+// one grid (see default_tile_rows and tile_kernel_rows in dugks_abi.hip), by
+// the number of 16-row marching tiles of all grids together.  A batch too small
+// to fill the chip is bound by one tile's latency: us per step with 64-row
+// marching tiles / now, FP32 corrected: one 64^2 grid 164 / 12.5, eight 128^2
+// 176 / 16.6, 16 grids of sides 32-512 178 / 39; 64 of them 175 / 76, 256 239 /
+// 211.
+void choose_tiles(dugks_batch* B) {
+  auto count = [B](int rows) {
+    int64_t n = 0;
+    for (const Slot& s : B->slots)
+      if (s.plan) n += (int64_t)s.plan->nstrips * ((s.plan->p.ny + rows - 1) / rows);
+    return n;
+  };
+  const int rows0 = B->rows, tile0 = B->tile;
+  if (B->given) {
+    B->tile = B->given_tile;
+  } else {
+    const int64_t n16 = count(16);
+    B->tile = n16 <= batch_tile_limit(B->precision, B->recon, B->scheme)
+                  ? batch_tile_height(B->mfix) : 0;
+    B->rows = 16;
+    if (n16 > B->grid_blocks && n16 < 2 * (int64_t)B->grid_blocks)
+      while (B->rows < 256 && count(B->rows) > B->grid_blocks) B->rows += MASS_GROUP;
+  }
+  if (B->rows != rows0 || B->tile != tile0) B->desc_dirty = true;
+}
+
 int commit(dugks_batch* B, hipStream_t s) {
-  build_items(B, B->rows);
+  choose_tiles(B);
+  build_items(B, B->tile ? B->tile : B->rows);
   return B->precision == DUGKS_F64 ? upload<double>(B, s) : upload<float>(B, s);
 }
 
 void release(dugks_batch* B) {
-  if (B->exec) (void)hipGraphExecDestroy(B->exec);
-  if (B->graph) (void)hipGraphDestroy(B->graph);
+  for (dugks_batch::Graph& g : B->graphs) {
+    if (g.exec) (void)hipGraphExecDestroy(g.exec);
+    if (g.graph) (void)hipGraphDestroy(g.graph);
+  }
   if (B->cap_stream) (void)hipStreamDestroy(B->cap_stream);
   for (int j = 0; j < NSTAGE; j++) {
     if (B->stage_ev[j]) {
@@ -318,12 +383,15 @@ void release(dugks_batch* B) {
   if (B->d_head) (void)hipFree(B->d_head);
 }
 
-int capture_graph(dugks_batch* B, int k) {
-  if (B->exec && B->graph_k == k) return DUGKS_OK;
-  if (B->exec) (void)hipGraphExecDestroy(B->exec);
-  if (B->graph) (void)hipGraphDestroy(B->graph);
-  B->exec = nullptr;
-  B->graph = nullptr;
+// the graph of k steps over the kind of tiles the list holds
+int capture_graph(dugks_batch* B, int k, hipGraphExec_t* exec) {
+  dugks_batch::Graph& G = B->graphs[B->tile ? 1 : 0];
+  *exec = G.exec;
+  if (G.exec && G.k == k) return DUGKS_OK;
+  if (G.exec) (void)hipGraphExecDestroy(G.exec);
+  if (G.graph) (void)hipGraphDestroy(G.graph);
+  G.exec = nullptr;
+  G.graph = nullptr;
   if (hipStreamBeginCapture(B->cap_stream, hipStreamCaptureModeRelaxed) != hipSuccess)
     return DUGKS_EDEVICE;
   int rc = DUGKS_OK;
@@ -334,12 +402,13 @@ int capture_graph(dugks_batch* B, int k) {
     if (g) (void)hipGraphDestroy(g);
     return DUGKS_EDEVICE;
   }
-  B->graph = g;
-  if (hipGraphInstantiate(&B->exec, g, nullptr, nullptr, 0) != hipSuccess) {
-    B->exec = nullptr;
+  G.graph = g;
+  if (hipGraphInstantiate(&G.exec, g, nullptr, nullptr, 0) != hipSuccess) {
+    G.exec = nullptr;
     return DUGKS_EDEVICE;
   }
-  B->graph_k = k;
+  G.k = k;
+  *exec = G.exec;
   return DUGKS_OK;
 }
 
@@ -366,13 +435,15 @@ int dugks_batch_create(int32_t capacity, int32_t precision, int32_t recon, uint3
   B->slots.resize(capacity);
   B->desc_bytes = precision == DUGKS_F64 ? sizeof(GridDesc<double>) : sizeof(GridDesc<float>);
   int rc = DUGKS_OK;
-  int per_cu = 0, ncu = 0;
+  int per_cu = 0, tile_per_cu = 0, ncu = 0;
   if (hipGetDevice(&B->device) != hipSuccess ||
       hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, B->device) !=
           hipSuccess ||
       (rc = batch_occupancy(B->precision, B->recon, B->mfix, B->scheme, &per_cu)) !=
           DUGKS_OK ||
-      per_cu < 1 || ncu < 1 ||
+      (rc = batch_tile_occupancy(B->precision, B->recon, B->mfix, B->scheme, &tile_per_cu)) !=
+          DUGKS_OK ||
+      per_cu < 1 || tile_per_cu < 1 || ncu < 1 ||
       hipMalloc(&B->d_desc, capacity * B->desc_bytes) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&B->d_steps), capacity * sizeof(SlotStep)) !=
           hipSuccess ||
@@ -402,6 +473,7 @@ int dugks_batch_create(int32_t capacity, int32_t precision, int32_t recon, uint3
     return DUGKS_EDEVICE;
   }
   B->grid_blocks = per_cu * ncu;
+  B->tile_blocks = tile_per_cu * ncu;
   *out = B;
   return DUGKS_OK;
 }
@@ -452,10 +524,11 @@ int dugks_batch_step(dugks_batch* batch, int64_t nsteps, int32_t graph_steps, vo
   hipStream_t s = static_cast<hipStream_t>(stream);
   int64_t left = nsteps;
   if (graph_steps > 1 && nsteps >= graph_steps) {
-    int rc = capture_graph(batch, graph_steps);
+    hipGraphExec_t exec = nullptr;
+    int rc = capture_graph(batch, graph_steps, &exec);
     if (rc) return rc;
     for (; left >= graph_steps; left -= graph_steps)
-      if (hipGraphLaunch(batch->exec, s) != hipSuccess) return DUGKS_EDEVICE;
+      if (hipGraphLaunch(exec, s) != hipSuccess) return DUGKS_EDEVICE;
   }
   for (; left > 0; left--) {
     int rc = batch_launch(batch, s, true);
@@ -481,6 +554,8 @@ int dugks_batch_tile_rows(const dugks_batch* batch) { return batch ? batch->rows
 int dugks_batch_set_tile_rows(dugks_batch* batch, int32_t rows) {
   if (!batch || rows < MASS_GROUP || rows > 65536 || rows % MASS_GROUP) return DUGKS_EINVAL;
   batch->rows = rows;
+  batch->given = true;
+  batch->given_tile = rows <= TILE_MAX_ROWS ? batch_tile_height(batch->mfix) : 0;
   batch->desc_dirty = true;
   return DUGKS_OK;
 }
@@ -496,9 +571,13 @@ int dugks_batch_tune(dugks_batch* batch, int32_t reps, int32_t* rows_out, void* 
   }
   int rc = DUGKS_OK;
   float best_ms = -1.0f;
-  int best = batch->rows;
+  int best = batch->rows, best_tile = 0;
+  float best_tile_ms = -1.0f;
+  batch->given = true;
+  // the block tiles (rows 0), then the heights of the march
   for (int rows : TUNE_ROWS) {
-    batch->rows = rows;
+    batch->given_tile = rows ? 0 : batch_tile_height(batch->mfix);
+    if (rows) batch->rows = rows;
     batch->desc_dirty = true;
     if ((rc = commit(batch, s))) break;
     // one untimed pass, then the timed passes
@@ -521,14 +600,18 @@ int dugks_batch_tune(dugks_batch* batch, int32_t reps, int32_t* rows_out, void* 
     }
     float ms = 0.0f;
     (void)hipEventElapsedTime(&ms, e0, e1);
-    if (best_ms < 0.0f || ms < best_ms) {
+    if (!rows) {
+      best_tile_ms = ms;
+    } else if (best_ms < 0.0f || ms < best_ms) {
       best_ms = ms;
       best = rows;
     }
   }
+  if (best_ms >= 0.0f && best_tile_ms < best_ms) best_tile = batch_tile_height(batch->mfix);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   batch->rows = best;
+  batch->given_tile = best_tile;
   batch->desc_dirty = true;
   int rc2 = commit(batch, s);
   if (!rc) rc = rc2;

@@ -24,8 +24,6 @@
 // never cover stores.
 #pragma once
 
-#include <type_traits>
-
 #include "dugks_common.h"
 
 namespace dugks {
@@ -121,6 +119,14 @@ __device__ __forceinline__ T from_right(T v) { return dpp_shift<0x130>(v); }
 template <typename T>
 __device__ __forceinline__ T from_left(T v) { return dpp_shift<0x138>(v); }
 
+// the value of one lane, to every lane
+__device__ __forceinline__ double read_lane(double v, int l) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, l);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __longlong_as_double((long long)(unsigned)lo | ((long long)hi << 32));
+}
+
 // Stores (and stage B's loads of Q) through a buffer resource: a lane whose
 // byte offset lies past the resource's size writes nothing / reads 0 (the
 // hardware range check), so a row's stores are issued by every lane on every
@@ -144,15 +150,6 @@ __device__ __forceinline__ double bload(rsrc_t r, unsigned off, double) {
 }
 __device__ __forceinline__ void bstore(double v, rsrc_t r, unsigned off) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, 2);
-}
-
-// f(0), f(1), .. f(N - 1) with compile-time arguments
-template <int N, typename F>
-__device__ __forceinline__ void unroll(F&& f) {
-  if constexpr (N > 0) {
-    unroll<N - 1>(f);
-    f(std::integral_constant<int, N - 1>{});
-  }
 }
 
 // Ordering point for LDS traffic inside the (single-wavefront) workgroup: a
@@ -318,11 +315,12 @@ struct Marcher {
     const double tb = tn + a.toff;
     double gn = 1.0, gp = 1.0, gh = 1.0;
     if (a.period > 0.0) {
-      const double t = lane == 0 ? tb : (lane == 1 ? tn + a.troff : tb + a.hd);
+      const double tr = tn + a.troff, tf = tb + a.hd;
+      const double t = lane == 0 ? tb : (lane == 1 ? tr : tf);
       const double g = cos(M_PI * t / a.period);
-      gn = __shfl(g, 0);
-      gp = __shfl(g, 1);
-      gh = __shfl(g, 2);
+      gn = read_lane(g, 0);
+      gp = read_lane(g, 1);
+      gh = read_lane(g, 2);
     }
     gN = T(gn);
     gP = T(gp);
@@ -463,21 +461,25 @@ struct Marcher {
     return v;
   }
 
-  // the columns (lo <= dx <= hi) of ring row k + dy that the face values of
-  // velocity I read; lo > hi: none
-  struct Span {
-    int lo, hi;
+  // the columns (lo <= dx <= hi) of the ring rows k + dy, dy = -REACH .. REACH,
+  // that the face values of a velocity read; lo > hi: none
+  static constexpr int REACH = 3;
+  struct Spans {
+    int lo[2 * REACH + 1], hi[2 * REACH + 1];
   };
-  template <int I, bool EAST>
-  static constexpr Span tap_span(int dy) {
-    Span s{1, -1};
-    for (int o = EAST ? 0 : 1; o < 2; o++)
+  static constexpr Spans tap_spans(int i, bool east) {
+    Spans s{};
+    for (int y = 0; y <= 2 * REACH; y++) {
+      s.lo[y] = 1;
+      s.hi[y] = -1;
+    }
+    for (int o = east ? 0 : 1; o < 2; o++)
       for (int t = 0; t < ntap(R); t++)
-        if (tap_used(R, o, I, t) && tap_dy(R, o, t) == dy) {
-          const int dx = tap_dx(R, o, t);
-          if (s.lo > s.hi) s = Span{0, 0};
-          s.lo = dx < s.lo ? dx : s.lo;
-          s.hi = dx > s.hi ? dx : s.hi;
+        if (tap_used(R, o, i, t)) {
+          const int y = tap_dy(R, o, t) + REACH, dx = tap_dx(R, o, t);
+          if (s.lo[y] > s.hi[y]) s.lo[y] = s.hi[y] = 0;
+          s.lo[y] = dx < s.lo[y] ? dx : s.lo[y];
+          s.hi[y] = dx > s.hi[y] ? dx : s.hi[y];
         }
     return s;
   }
@@ -487,33 +489,31 @@ struct Marcher {
   // shifts of it (0 beyond the edge lanes, where nothing owned comes from)
   template <int I, bool EAST>
   __device__ __forceinline__ void recon_pair(int k, T& pn, T& pe) const {
-    constexpr int D = 3;                 // offsets -D .. D
-    T f[2 * D + 1][2 * D + 1];           // [dy + D][dx + D]; only the used ones are formed
-    unroll<2 * D + 1>([&](auto Y) {
-      constexpr int y = decltype(Y)::value;
-      constexpr Span sp = tap_span<I, EAST>(y - D);
-      if constexpr (sp.lo <= sp.hi) {
-        f[y][D] = bfp[slotB(k + y - D)][I][LP + lane];
-        unroll<D>([&](auto X) {
-          constexpr int dx = decltype(X)::value + 1;
-          if constexpr (dx <= sp.hi) f[y][D + dx] = from_right(f[y][D + dx - 1]);
-          if constexpr (-dx >= sp.lo) f[y][D - dx] = from_left(f[y][D - dx + 1]);
-        });
+    constexpr Spans sp = tap_spans(I, EAST);
+    constexpr int Q = REACH;
+    T f[2 * Q + 1][2 * Q + 1];           // [dy + Q][dx + Q]; only the used ones are formed
+#pragma unroll
+    for (int y = 0; y <= 2 * Q; y++)
+      if (sp.lo[y] <= sp.hi[y]) {
+        f[y][Q] = bfp[slotB(k + y - Q)][I][LP + lane];
+#pragma unroll
+        for (int dx = 1; dx <= Q; dx++) {
+          if (dx <= sp.hi[y]) f[y][Q + dx] = from_right(f[y][Q + dx - 1]);
+          if (-dx >= sp.lo[y]) f[y][Q - dx] = from_left(f[y][Q - dx + 1]);
+        }
       }
-    });
     pn = pe = T(0);
-    unroll<ntap(R)>([&](auto U) {
-      constexpr int t = decltype(U)::value;
-      if constexpr (tap_used(R, 1, I, t))
-        pn = fma(cf[compact_index(R, 1, I, t)], f[tap_dy(R, 1, t) + D][tap_dx(R, 1, t) + D], pn);
-    });
-    if constexpr (EAST)
-      unroll<ntap(R)>([&](auto U) {
-        constexpr int t = decltype(U)::value;
-        if constexpr (tap_used(R, 0, I, t))
-          pe = fma(cf[compact_index(R, 0, I, t)], f[tap_dy(R, 0, t) + D][tap_dx(R, 0, t) + D],
+#pragma unroll
+    for (int t = 0; t < ntap(R); t++)
+      if (tap_used(R, 1, I, t))
+        pn = fma(cf[compact_index(R, 1, I, t)], f[tap_dy(R, 1, t) + Q][tap_dx(R, 1, t) + Q], pn);
+    if constexpr (EAST) {
+#pragma unroll
+      for (int t = 0; t < ntap(R); t++)
+        if (tap_used(R, 0, I, t))
+          pe = fma(cf[compact_index(R, 0, I, t)], f[tap_dy(R, 0, t) + Q][tap_dx(R, 0, t) + Q],
                    pe);
-      });
+    }
   }
 
   // Faces of row k and the update of its cells.  With phi_b = sum_i fbar_i,
@@ -1064,15 +1064,27 @@ __global__ __launch_bounds__(LANES, step_waves(sizeof(T), R, MFIX)) void batch_s
   const int nq = c->nq;
   const int home = nq > 0 ? (int)(blockIdx.x % (unsigned)nq) : 0;
   unsigned* heads = head + (STAGE == STAGE_B ? 1 : 0);
-  for (int qi = 0; qi < nq; qi++) {
-    const int q = home + qi < nq ? home + qi : home + qi - nq;
+  // The home queue, then one other: another of the seven for each wavefront of
+  // the XCD, so that a queue whose grids run on while others' have stopped is
+  // drained by all XCDs.  A wavefront's first item goes by its index, so a
+  // queue's head counts from the number of its home wavefronts.  (Trying all
+  // eight queues cost ~1.5 us of failed atomics apiece at the end of every
+  // wavefront: 16-row tiles, 4 grids of 256^2 75 us a step, now 45; 256 grids
+  // 217, now 211.  Looking at the heads with plain loads first made the kernel
+  // 10-15 % slower.)
+  for (int probe = 0; probe < 2 && nq > 0; probe++) {
+    const int q = probe == 0 ? home : (home + 1 + (int)((blockIdx.x / nq) % max(nq - 1, 1))) % nq;
     const unsigned lo = (unsigned)c->qstart[q];
     const unsigned cnt = (unsigned)c->qstart[q + 1] - lo;
     unsigned* qh = heads + q * HEAD_STRIDE;
+    bool first = probe == 0;
     for (;;) {
-      unsigned it = 0;
-      if (threadIdx.x == 0) it = atomicAdd(qh, 1u);
-      it = __builtin_amdgcn_readfirstlane(it);
+      unsigned it = blockIdx.x / (unsigned)nq;
+      if (!first) {
+        if (threadIdx.x == 0) it = (gridDim.x - q + nq - 1) / (unsigned)nq + atomicAdd(qh, 1u);
+        it = __builtin_amdgcn_readfirstlane(it);
+      }
+      first = false;
       if (it >= cnt) break;
       const BatchItem w = load_const(items + lo + it);
       const int64_t n = st[w.slot].n;

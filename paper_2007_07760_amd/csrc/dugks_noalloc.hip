@@ -123,8 +123,8 @@ int scratch_of_current_device(unsigned char** out) {
 
 template <typename T>
 int noalloc_setup(const dugks_plan* const* plans, void* const* states, const int64_t* steps,
-                  int n, int64_t nsteps, const ItemStarts& starts, unsigned char* base,
-                  hipStream_t s) {
+                  int n, int64_t nsteps, int tile, const ItemStarts& starts,
+                  unsigned char* base, hipStream_t s) {
   DescChunk<T> c;
   for (int first = 0; first < n; first += DESC_CHUNK) {
     memset(&c, 0, sizeof(c));
@@ -132,7 +132,7 @@ int noalloc_setup(const dugks_plan* const* plans, void* const* states, const int
     c.count = std::min(DESC_CHUNK, n - first);
     for (int k = 0; k < c.count; k++) {
       const dugks_plan* P = plans[first + k];
-      c.d[k] = make_grid_desc<T>(P, states[first + k], P->many_rows);
+      c.d[k] = make_grid_desc<T>(P, states[first + k], tile ? tile : P->many_rows);
       c.st[k].n = steps[first + k];
       c.st[k].target = steps[first + k] + nsteps;
     }
@@ -174,10 +174,19 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
       return DUGKS_EUNSUPPORTED;
     order[j] = j;
   }
+  // block tiles where the grids together are too few to fill the chip with
+  // marching wavefronts (as a batch chooses them), else each plan's own height
+  int64_t n16 = 0;
+  for (int j = 0; j < n; j++)
+    n16 += (int64_t)plans[j]->nstrips * ((plans[j]->p.ny + 15) / 16);
+  const int tile = n16 <= batch_tile_limit(precision, recon, scheme) ? batch_tile_height(mfix) : 0;
+  auto segs = [tile](const dugks_plan* P) {
+    return tile ? (P->p.ny + tile - 1) / tile : P->many_segs;
+  };
   // rows a grid's tiles march in all
-  auto work = [plans](int j) {
+  auto work = [plans, &segs](int j) {
     const dugks_plan* P = plans[j];
-    return (int64_t)P->nstrips * ((int64_t)P->p.ny + 5 * (int64_t)P->many_segs);
+    return (int64_t)P->nstrips * ((int64_t)P->p.ny + 5 * (int64_t)segs(P));
   };
   std::stable_sort(order, order + n, [&](int a, int b) { return work(a) > work(b); });
   int queue_of[NOALLOC_GRIDS];
@@ -201,7 +210,7 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
     while (q <= queue_of[order[k]]) starts.qstart[q++] = (int32_t)total;
     starts.start[k] = (int32_t)total;
     starts.grid[k] = order[k];
-    total += (int64_t)P->nstrips * P->many_segs;
+    total += (int64_t)P->nstrips * segs(P);
     if (total > NOALLOC_ITEMS) return DUGKS_EINVAL;   // beyond the array's work list
   }
   while (q <= NQUEUE) starts.qstart[q++] = (int32_t)total;
@@ -210,16 +219,18 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
   unsigned char* base = nullptr;
   int rc = scratch_of_current_device(&base);
   if (rc) return rc;
-  int dev = 0, ncu = 0, per_cu = 0;
+  int dev = 0, ncu = 0, per_cu = 0, tile_per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return DUGKS_EDEVICE;
   if ((rc = batch_occupancy(precision, recon, mfix, scheme, &per_cu)) != DUGKS_OK) return rc;
-  if (per_cu < 1 || ncu < 1) return DUGKS_EDEVICE;
+  if ((rc = batch_tile_occupancy(precision, recon, mfix, scheme, &tile_per_cu)) != DUGKS_OK)
+    return rc;
+  if (per_cu < 1 || tile_per_cu < 1 || ncu < 1) return DUGKS_EDEVICE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   rc = precision == DUGKS_F64
-           ? noalloc_setup<double>(plans, states, steps, n, nsteps, starts, base, s)
-           : noalloc_setup<float>(plans, states, steps, n, nsteps, starts, base, s);
+           ? noalloc_setup<double>(plans, states, steps, n, nsteps, tile, starts, base, s)
+           : noalloc_setup<float>(plans, states, steps, n, nsteps, tile, starts, base, s);
   if (rc) return rc;
   const BatchDev D{base + NA_DESC,
                    reinterpret_cast<SlotStep*>(base + NA_STEPS),
@@ -227,7 +238,9 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
                    reinterpret_cast<BatchCtl*>(base + NA_CTL),
                    reinterpret_cast<unsigned*>(base + NA_HEAD),
                    n,
-                   per_cu * ncu};
+                   per_cu * ncu,
+                   tile,
+                   tile_per_cu * ncu};
   for (int64_t k = 0; k < nsteps; k++)
     if ((rc = launch_batch(D, precision, recon, mfix, scheme, s, true))) return rc;
   return DUGKS_OK;

@@ -97,9 +97,8 @@ inline StageBufs<T> stage_bufs(const dugks_plan* P, void* state, int64_t n, int 
 }
 
 // One launch of the tile kernel (plans with P->tile != 0).
-template <typename T>
-void launch_tile(const dugks_plan* P, int stage, const StageBufs<T>& q, int64_t n,
-                 hipStream_t s);
+template <typename T, int STAGE>
+void launch_tile(const dugks_plan* P, const StageBufs<T>& q, int64_t n, hipStream_t s);
 
 template <typename T>
 inline StepArgs<T> step_args(const dugks_plan* P, int stage = STAGE_T2) {

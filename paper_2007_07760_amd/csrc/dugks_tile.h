@@ -35,36 +35,29 @@ __host__ __device__ constexpr int tile_cell_rows(int recon, int TR) {
   return TR + 2 * (wide(recon) ? 3 : 2);
 }
 
-// the face values of row k, velocity by velocity: pn of the north faces, de of
-// the east less the west ones, and their sums over the velocities
-template <bool EAST, typename M, typename T>
+// the face values of row k, velocity by velocity from I on: pn of the north
+// faces, de of the east less the west ones, and their sums over the velocities
+template <bool EAST, int I = 0, typename M, typename T>
 __device__ __forceinline__ void faces(const M& m, int k, T (&pn)[9], T (&de)[9], T& phN, T& phE) {
-  unroll<9>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    T pe;
-    m.template recon_pair<i, EAST>(k, pn[i], pe);
-    phN += pn[i];
-    if constexpr (EAST) {
-      phE += pe;
-      if constexpr (ex(i) != 0) de[i] = pe - from_left(pe);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  });
+  T pe;
+  m.template recon_pair<I, EAST>(k, pn[I], pe);
+  phN += pn[I];
+  if constexpr (EAST) {
+    phE += pe;
+    if constexpr (ex(I) != 0) de[I] = pe - from_left(pe);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (I < 8) faces<EAST, I + 1>(m, k, pn, de, phN, phE);
 }
 
-template <typename T, int R, bool MFIX, int STAGE, bool VARR, int TR>
-__global__ __launch_bounds__(LANES* tile_cell_rows(R, TR), tile_waves(sizeof(T), R, TR)) void
-tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__ dst,
-            T* __restrict__ dst2, const T* __restrict__ aux, const T* __restrict__ cf,
-            const T* __restrict__ tabx, const T* __restrict__ taby, const T* __restrict__ uv,
-            double* __restrict__ part, const StateHeader* __restrict__ hdr) {
-  constexpr int CR = tile_cell_rows(R, TR);
-  using M = Marcher<T, R, MFIX, STAGE, VARR, CR>;
-  constexpr int LAG = M::LAG;
+template <typename T, int R, bool MFIX, int TR>
+struct TileShared {
+  static constexpr int CR = tile_cell_rows(R, TR);
   static_assert(!MFIX || TR == MASS_GROUP, "a tile of a corrected plan is one mass group");
+  T bfp[CR][9][LANES];          // fbar+ of the cell rows; then the north faces
   // one buffer, in turn: the row differences phi(x+1) - phi(x-1) and
   // phi(x-1) + 4 phi + phi(x+1); s of the cell rows; the mass sums of the rows
-  union Shared {
+  union {
     T da[CR + 2][2][LANES];
     T s[CR][2][LANES];
     struct {
@@ -72,21 +65,26 @@ tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__
       int fit[MFIX ? TR : 1][LANES];
     } mass;
   };
-  __shared__ T s_bfp[CR][9][LANES];
-  __shared__ Shared u;
+};
 
+// One tile by the whole block: rows [seg * TR, seg * TR + TR) of `strip`, step
+// n; the arguments are march_tile's.
+template <typename T, int R, bool MFIX, int STAGE, bool VARR, int TR>
+__device__ __forceinline__ void tile_step(const StepArgs<T>& a, int64_t n,
+                                          const T* __restrict__ src, T* __restrict__ dst,
+                                          T* __restrict__ dst2, const T* __restrict__ aux,
+                                          const T* __restrict__ cf, const T* __restrict__ tabx,
+                                          const T* __restrict__ taby, const T* __restrict__ uv,
+                                          double* __restrict__ part, double pend, double fitmax,
+                                          int strip, int seg, TileShared<T, R, MFIX, TR>& u) {
+  constexpr int CR = tile_cell_rows(R, TR);
+  using M = Marcher<T, R, MFIX, STAGE, VARR, CR>;
+  constexpr int LAG = M::LAG;
   const int lane = threadIdx.x & (LANES - 1);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
-  // bands of tiles per XCD, as in step_kernel
-  const int per = (a.nlogical + 7) >> 3;
-  const int logical = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= per || logical >= a.nlogical) return;
-  const int strip = logical % a.nstrips;
-  const int seg = logical / a.nstrips;
 
-  M m{a, src, as_const(cf), tabx, as_const(taby), uv, s_bfp};
-  m.place(lane, strip, seg * TR, TR, dst, dst2, aux, part, MFIX ? hdr->pending : 0.0,
-          MFIX ? hdr->fit_max : 0.0);
+  M m{a, src, as_const(cf), tabx, as_const(taby), uv, u.bfp};
+  m.place(lane, strip, seg * TR, TR, dst, dst2, aux, part, pend, fitmax);
   m.base = m.y0 - LAG;
   // the cell row of this wavefront; the last tile may hold fewer rows, the
   // wavefronts beyond what it needs load its top row and write nothing
@@ -147,13 +145,13 @@ tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__
     m.north_moments(kk, phN, m.sxp[LAG], m.syp[LAG], u.s[w + 1][0][lane], u.s[w + 1][1][lane],
                     PN, QNx, QNy);
 #pragma unroll
-    for (int i = 0; i < 9; i++) bp[i] = s_bfp[w][i][lane];
+    for (int i = 0; i < 9; i++) bp[i] = u.bfp[w][i][lane];
 #pragma unroll
     for (int i = 0; i < 9; i++)
-      if (ey(i) != 0) s_bfp[w][i][lane] = pn[i];
-    s_bfp[w][0][lane] = PN;
-    s_bfp[w][1][lane] = QNx;
-    s_bfp[w][5][lane] = QNy;
+      if (ey(i) != 0) u.bfp[w][i][lane] = pn[i];
+    u.bfp[w][0][lane] = PN;
+    u.bfp[w][1][lane] = QNx;
+    u.bfp[w][5][lane] = QNy;
     if (upd) m.east_moments(kk, phE, m.sxp[LAG], m.syp[LAG], eP, eQx, eQy);
   }
   __syncthreads();
@@ -163,14 +161,14 @@ tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__
     for (int i = 0; i < 9; i++) {
       out[i] = T(0);
       if (ey(i) != 0) {
-        const T dn = pn[i] - s_bfp[w - 1][i][lane];
+        const T dn = pn[i] - u.bfp[w - 1][i][lane];
         out[i] = ey(i) > 0 ? -dn : dn;
       }
       if (ex(i) != 0) out[i] = ex(i) > 0 ? out[i] - de[i] : out[i] + de[i];
     }
     double cs = 0.0, cf0 = 0.0;
-    m.update_cells(kk, bp, out, PN - s_bfp[w - 1][0][lane], QNx - s_bfp[w - 1][1][lane],
-                   QNy - s_bfp[w - 1][5][lane], eP, eQx, eQy, m.cp[LAG], m.cx[LAG], m.cy[LAG],
+    m.update_cells(kk, bp, out, PN - u.bfp[w - 1][0][lane], QNx - u.bfp[w - 1][1][lane],
+                   QNy - u.bfp[w - 1][5][lane], eP, eQx, eQy, m.cp[LAG], m.cx[LAG], m.cy[LAG],
                    p, qv, cs, cf0);
     if (M::FIX_SUM) {
       u.mass.sum[MFIX ? k - m.y0 : 0][lane] = m.owned ? cs : 0.0;
@@ -193,6 +191,57 @@ tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__
         m.part_row[2 * seg + 1] = c;
       }
     }
+  }
+}
+
+template <typename T, int R, bool MFIX, int STAGE, bool VARR, int TR>
+__global__ __launch_bounds__(LANES* tile_cell_rows(R, TR), tile_waves(sizeof(T), R, TR)) void
+tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__ dst,
+            T* __restrict__ dst2, const T* __restrict__ aux, const T* __restrict__ cf,
+            const T* __restrict__ tabx, const T* __restrict__ taby, const T* __restrict__ uv,
+            double* __restrict__ part, const StateHeader* __restrict__ hdr) {
+  __shared__ TileShared<T, R, MFIX, TR> u;
+  // bands of tiles per XCD, as in step_kernel
+  const int per = (a.nlogical + 7) >> 3;
+  const int logical = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (logical >= a.nlogical) return;
+  tile_step<T, R, MFIX, STAGE, VARR, TR>(a, n, src, dst, dst2, aux, cf, tabx, taby, uv, part,
+                                         MFIX ? hdr->pending : 0.0, MFIX ? hdr->fit_max : 0.0,
+                                         logical % a.nstrips, logical / a.nstrips, u);
+}
+
+// One batch step (or one stage of a T3S3 batch step) over a work list of
+// TR-row tiles.  The tiles cost the same, so each block takes every so-manieth
+// item of its XCD's queue: no queue heads, and no wait for one before the first
+// tile (an atomic across the XCDs takes longer than a tile's face stage).
+template <typename T, int R, bool MFIX, int STAGE, int TR>
+__global__ __launch_bounds__(LANES* tile_cell_rows(R, TR), tile_waves(sizeof(T), R, TR)) void
+batch_tile_kernel(const GridDesc<T>* __restrict__ desc, const SlotStep* __restrict__ steps,
+                  const BatchCtl* __restrict__ ctl) {
+  __shared__ TileShared<T, R, MFIX, TR> u;
+  const cptr<BatchCtl> c = as_const(ctl);
+  const cptr<BatchItem> items = as_const(c->items);
+  const cptr<SlotStep> st = as_const(steps);
+  const int nq = c->nq;
+  if (nq <= 0) return;
+  const int q = (int)(blockIdx.x % (unsigned)nq);
+  const int end = c->qstart[q + 1];
+  const int stride = ((int)gridDim.x - q + nq - 1) / nq;   // blocks of this queue
+  for (int it = c->qstart[q] + (int)(blockIdx.x / (unsigned)nq); it < end; it += stride) {
+    const BatchItem w = load_const(items + it);
+    const int64_t n = st[w.slot].n;
+    if (n >= st[w.slot].target) continue;
+    const cptr<GridDesc<T>> d = as_const(desc) + w.slot;
+    const StepArgs<T> a = load_const(as_const(STAGE == STAGE_B ? &d->b : &d->a));
+    const int b = (int)(n & 1);
+    // T2 f~^n -> f~^{n+1}; stage A f^^n -> f~(t'), Q; stage B f~(t'), Q -> f^^{n+1}
+    tile_step<T, R, MFIX, STAGE, false, TR>(
+        a, n, STAGE == STAGE_B ? d->mid : d->buf[b], STAGE == STAGE_A ? d->mid : d->buf[b ^ 1],
+        STAGE == STAGE_A ? d->q : nullptr, STAGE == STAGE_B ? d->q : nullptr,
+        STAGE == STAGE_B ? d->cf2 : d->cf, d->tabx, d->taby, nullptr, d->part,
+        MFIX ? d->hdr->pending : 0.0, MFIX ? d->hdr->fit_max : 0.0, w.tile % a.nstrips,
+        w.tile / a.nstrips, u);
+    __syncthreads();   // the next tile writes what this one's wavefronts may still read
   }
 }
 

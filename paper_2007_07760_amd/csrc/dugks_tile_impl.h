@@ -1,5 +1,5 @@
-// dugks_tile_impl.h -- launches of the tile kernel (one instantiation file per
-// precision; private to the library).
+// dugks_tile_impl.h -- launches of the tile kernel on one grid (instantiated per
+// precision and stage in dugks_tile_*.hip; private to the library).
 #pragma once
 
 #include "dugks_plan.h"
@@ -54,19 +54,13 @@ static void tile_recon_go(const dugks_plan* P, const StepArgs<T>& a, const Stage
   }
 }
 
-template <typename T>
-void launch_tile(const dugks_plan* P, int stage, const StageBufs<T>& q, int64_t n,
-                 hipStream_t s) {
-  StepArgs<T> a = step_args<T>(P, stage);
+template <typename T, int STAGE>
+void launch_tile(const dugks_plan* P, const StageBufs<T>& q, int64_t n, hipStream_t s) {
+  StepArgs<T> a = step_args<T>(P, STAGE);
   a.seg_rows = P->tile;
   a.nsegs = (P->p.ny + P->tile - 1) / P->tile;
   a.nlogical = a.nstrips * a.nsegs;
-  if (stage == STAGE_T2)
-    tile_recon_go<T, STAGE_T2>(P, a, q, n, s);
-  else if (stage == STAGE_A)
-    tile_recon_go<T, STAGE_A>(P, a, q, n, s);
-  else
-    tile_recon_go<T, STAGE_B>(P, a, q, n, s);
+  tile_recon_go<T, STAGE>(P, a, q, n, s);
 }
 
 }  // namespace dugks
