@@ -119,14 +119,6 @@ __device__ __forceinline__ T from_right(T v) { return dpp_shift<0x130>(v); }
 template <typename T>
 __device__ __forceinline__ T from_left(T v) { return dpp_shift<0x138>(v); }
 
-// the value of one lane, to every lane
-__device__ __forceinline__ double read_lane(double v, int l) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double((long long)(unsigned)lo | ((long long)hi << 32));
-}
-
 // Stores (and stage B's loads of Q) through a buffer resource: a lane whose
 // byte offset lies past the resource's size writes nothing / reads 0 (the
 // hardware range check), so a row's stores are issued by every lane on every
@@ -318,9 +310,9 @@ struct Marcher {
       const double tr = tn + a.troff, tf = tb + a.hd;
       const double t = lane == 0 ? tb : (lane == 1 ? tr : tf);
       const double g = cos(M_PI * t / a.period);
-      gn = read_lane(g, 0);
-      gp = read_lane(g, 1);
-      gh = read_lane(g, 2);
+      gn = __shfl(g, 0);
+      gp = __shfl(g, 1);
+      gh = __shfl(g, 2);
     }
     gN = T(gn);
     gP = T(gp);
