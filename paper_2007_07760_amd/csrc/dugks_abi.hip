@@ -278,30 +278,27 @@ int default_tile_rows(const dugks_params& p, int nstrips) {
 // TILE_MAX_ROWS ask for it, and by default grids too small to fill the chip
 // with marching wavefronts take it.  A marching wavefront needs ~35 us (FP64
 // upwind-3; 57 us central-4, 78 us upwind-5) for a 16-row tile however few
-// there are, the tile kernel 6.6 us (7.5, 9.4) for a grid of up to 256 tiles,
-// but it forms the cell terms of 8 rows for every 4.  The line lies at the
-// number of 16-row marching tiles where the two meet, measured on square
-// grids (us per step, tile / march): FP64 upwind-3 768^2 38.0 / 41.9, 896^2
-// 48.7 / 43.6; central-4 1024^2 71 / 77, 1280^2 108 / 110; velocity arrays
-// 1024^2 65 / 63; T3S3 640^2 80 / 87, 768^2 105 / 95; upwind-5 (8-row tiles)
-// 1024^2 105 / 124, 1280^2 170 / 160; FP32 corrected 1024^2 43.4 / 46.8,
-// 1280^2 63 / 52.
+// there are, the tile kernel 6.4 us (7.0, 9.4) for a grid of up to 256 tiles,
+// but it forms the cell terms of 12 rows for every 8 (8 for every 4).  The line
+// lies at the number of 16-row marching tiles where the two meet, measured on
+// square grids (us per step, tile / march): FP64 upwind-3 1024^2 53 / 54.5,
+// 1280^2 ~90 / 74; central-4 1024^2 67 / 77, 1280^2 108 / 110; velocity arrays
+// 1024^2 55 / 63; T3S3 768^2 89 / 95, 1024^2 147 / 137; upwind-5 1024^2 102 /
+// 124, 1280^2 170 / 160; FP32 corrected 1024^2 43.4 / 46.8, 1280^2 63 / 52.
 int tile_kernel_rows(const dugks_params& p, int nstrips) {
   if (p.tile_rows > TILE_MAX_ROWS) return 0;
   if (p.tile_rows == 0) {
     const bool slow_march = p.recon == DUGKS_CENTRAL4 || p.recon == DUGKS_UPWIND5;
     const long limit = p.precision == DUGKS_F32 ? (p.recon == DUGKS_UPWIND5 ? 1000 : 1250)
                        : slow_march             ? 1650
-                       : p.vel_kind == DUGKS_VEL_ARRAYS ? 1100
-                       : p.scheme == DUGKS_T3S3         ? 600
-                                                        : 760;
+                       : p.scheme == DUGKS_T3S3 ? 800
+                       : p.vel_kind == DUGKS_VEL_ARRAYS ? 1450
+                                                        : 1150;
     if ((long)nstrips * ((p.ny + 15) / 16) > limit) return 0;
   }
-  // a tile of a corrected plan is one mass group; upwind-5 forms 10 cell rows
-  // for 4 of its own, so it takes 8-row tiles (256^2: 12.2 us against 16.7)
-  // unless the 4-row ones leave compute units idle (64^2: 9.4 against 11.8)
-  if (p.flags & DUGKS_FLAG_MASS_FIX) return MASS_GROUP;
-  return p.recon == DUGKS_UPWIND5 && (long)nstrips * ((p.ny + 3) / 4) > 256 ? 8 : 4;
+  return block_tile_rows(p.precision == DUGKS_F64 ? 8 : 4, p.recon, p.scheme,
+                         (p.flags & DUGKS_FLAG_MASS_FIX) != 0,
+                         (int64_t)nstrips * ((p.ny + 3) / 4));
 }
 
 // ------------------------------------------------------------ launches

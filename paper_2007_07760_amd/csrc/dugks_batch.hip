@@ -135,21 +135,22 @@ struct dugks_batch {
   int rows = DEFAULT_ROWS;            // height of the marching tiles
   int tile = 0;                       // rows of the list's block tiles; 0: marching tiles
   bool given = false;                 // height and kind are the caller's (or the
-  int given_tile = 0;                 // autotuner's) choice; else each commit chooses
+  bool given_tile = false;            // autotuner's) choice; else each commit chooses
   int grid_blocks = 0;                // resident wavefronts of the persistent kernel
-  int tile_blocks = 0;                // resident blocks of the tile kernel
+  int tile_blocks = 0;                // NQUEUE x the longest queue of block tiles
   // pinned staging ring: [ctl][desc table][steps][items]
   void* stage[NSTAGE] = {};
   size_t stage_bytes[NSTAGE] = {};
   hipEvent_t stage_ev[NSTAGE] = {};
   int stage_next = 0;
-  // graphs of K steps: over marching tiles, over block tiles
+  // graphs of K steps, one per kind of tiles
   hipStream_t cap_stream = nullptr;
   struct Graph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     int k = 0;
-  } graphs[2];
+    int blocks = 0;                   // of its tile kernels: no fewer than the list needs
+  } graphs[3];                        // marching tiles, block tiles of 4 and 8 rows
 };
 
 namespace {
@@ -161,8 +162,8 @@ GridDesc<T> make_desc(const Slot& s, int rows) {
 
 // Work list of block tiles: every grid's tiles, segment by segment, cut into
 // NQUEUE equal bands, one per queue (starting at another queue for each slot).
-// The blocks take fixed shares of their queue, so the queues have to stay equal
-// also when some grids have reached their targets.
+// A block takes one item of its XCD's queue, so the queues have to stay equal also
+// when some grids have reached their targets.
 void build_tile_items(dugks_batch* B, int rows) {
   std::vector<BatchItem> queue[NQUEUE];
   for (int k = 0; k < B->cap; k++) {
@@ -178,6 +179,9 @@ void build_tile_items(dugks_batch* B, int rows) {
     B->qstart[q + 1] = (int32_t)B->items.size();
   }
   B->nq = B->items.empty() ? 1 : NQUEUE;
+  size_t most = 1;
+  for (const auto& v : queue) most = std::max(most, v.size());
+  B->tile_blocks = NQUEUE * (int)most;
 }
 
 // Work list for tile height `rows`, cut into NQUEUE queues of about equal
@@ -188,6 +192,7 @@ void build_tile_items(dugks_batch* B, int rows) {
 // queue the taller tiles come first, so that the short ones fill the tail.
 void build_items(dugks_batch* B, int rows) {
   B->items.clear();
+  B->tile_blocks = 0;
   if (B->tile) {
     build_tile_items(B, rows);
     return;
@@ -322,9 +327,9 @@ int upload(dugks_batch* B, hipStream_t s) {
 // finish = false: the step kernel alone, which writes only the next-step
 // buffers and mass partials of each active slot (used to time tilings; the
 // state is unchanged, since the finish kernel never runs)
-int batch_launch(dugks_batch* B, hipStream_t s, bool finish) {
+int batch_launch(dugks_batch* B, hipStream_t s, bool finish, int blocks) {
   const BatchDev D{B->d_desc, B->d_steps, B->d_status, B->d_ctl, B->d_head, B->cap,
-                   B->grid_blocks, B->tile, B->tile_blocks};
+                   B->grid_blocks, B->tile, blocks};
   return launch_batch(D, B->precision, B->recon, B->mfix, B->scheme, s, finish);
 }
 
@@ -343,12 +348,13 @@ void choose_tiles(dugks_batch* B) {
     return n;
   };
   const int rows0 = B->rows, tile0 = B->tile;
-  if (B->given) {
-    B->tile = B->given_tile;
-  } else {
-    const int64_t n16 = count(16);
-    B->tile = n16 <= batch_tile_limit(B->precision, B->recon, B->scheme)
-                  ? batch_tile_height(B->mfix) : 0;
+  const int64_t n16 = count(16);
+  const bool block = B->given ? B->given_tile
+                              : n16 <= batch_tile_limit(B->precision, B->recon, B->scheme);
+  B->tile = block ? block_tile_rows(B->precision == DUGKS_F64 ? 8 : 4, B->recon, B->scheme,
+                                    B->mfix, count(4))
+                  : 0;
+  if (!B->given) {
     B->rows = 16;
     if (n16 > B->grid_blocks && n16 < 2 * (int64_t)B->grid_blocks)
       while (B->rows < 256 && count(B->rows) > B->grid_blocks) B->rows += MASS_GROUP;
@@ -383,11 +389,13 @@ void release(dugks_batch* B) {
   if (B->d_head) (void)hipFree(B->d_head);
 }
 
-// the graph of k steps over the kind of tiles the list holds
+// The graph of k steps over the kind of tiles the list holds.  A graph's tile
+// kernels have a power of two of blocks per queue, so that it is captured again
+// only when the list has outgrown it.
 int capture_graph(dugks_batch* B, int k, hipGraphExec_t* exec) {
-  dugks_batch::Graph& G = B->graphs[B->tile ? 1 : 0];
+  dugks_batch::Graph& G = B->graphs[B->tile / 4];
   *exec = G.exec;
-  if (G.exec && G.k == k) return DUGKS_OK;
+  if (G.exec && G.k == k && G.blocks >= B->tile_blocks) return DUGKS_OK;
   if (G.exec) (void)hipGraphExecDestroy(G.exec);
   if (G.graph) (void)hipGraphDestroy(G.graph);
   G.exec = nullptr;
@@ -395,7 +403,10 @@ int capture_graph(dugks_batch* B, int k, hipGraphExec_t* exec) {
   if (hipStreamBeginCapture(B->cap_stream, hipStreamCaptureModeRelaxed) != hipSuccess)
     return DUGKS_EDEVICE;
   int rc = DUGKS_OK;
-  for (int j = 0; j < k && rc == DUGKS_OK; j++) rc = batch_launch(B, B->cap_stream, true);
+  G.blocks = NQUEUE;
+  while (G.blocks < B->tile_blocks) G.blocks *= 2;
+  for (int j = 0; j < k && rc == DUGKS_OK; j++)
+    rc = batch_launch(B, B->cap_stream, true, G.blocks);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(B->cap_stream, &g);
   if (rc || e != hipSuccess || !g) {
@@ -435,15 +446,13 @@ int dugks_batch_create(int32_t capacity, int32_t precision, int32_t recon, uint3
   B->slots.resize(capacity);
   B->desc_bytes = precision == DUGKS_F64 ? sizeof(GridDesc<double>) : sizeof(GridDesc<float>);
   int rc = DUGKS_OK;
-  int per_cu = 0, tile_per_cu = 0, ncu = 0;
+  int per_cu = 0, ncu = 0;
   if (hipGetDevice(&B->device) != hipSuccess ||
       hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, B->device) !=
           hipSuccess ||
       (rc = batch_occupancy(B->precision, B->recon, B->mfix, B->scheme, &per_cu)) !=
           DUGKS_OK ||
-      (rc = batch_tile_occupancy(B->precision, B->recon, B->mfix, B->scheme, &tile_per_cu)) !=
-          DUGKS_OK ||
-      per_cu < 1 || tile_per_cu < 1 || ncu < 1 ||
+      per_cu < 1 || ncu < 1 ||
       hipMalloc(&B->d_desc, capacity * B->desc_bytes) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&B->d_steps), capacity * sizeof(SlotStep)) !=
           hipSuccess ||
@@ -473,7 +482,6 @@ int dugks_batch_create(int32_t capacity, int32_t precision, int32_t recon, uint3
     return DUGKS_EDEVICE;
   }
   B->grid_blocks = per_cu * ncu;
-  B->tile_blocks = tile_per_cu * ncu;
   *out = B;
   return DUGKS_OK;
 }
@@ -531,7 +539,7 @@ int dugks_batch_step(dugks_batch* batch, int64_t nsteps, int32_t graph_steps, vo
       if (hipGraphLaunch(exec, s) != hipSuccess) return DUGKS_EDEVICE;
   }
   for (; left > 0; left--) {
-    int rc = batch_launch(batch, s, true);
+    int rc = batch_launch(batch, s, true, batch->tile_blocks);
     if (rc) return rc;
   }
   return DUGKS_OK;
@@ -555,7 +563,7 @@ int dugks_batch_set_tile_rows(dugks_batch* batch, int32_t rows) {
   if (!batch || rows < MASS_GROUP || rows > 65536 || rows % MASS_GROUP) return DUGKS_EINVAL;
   batch->rows = rows;
   batch->given = true;
-  batch->given_tile = rows <= TILE_MAX_ROWS ? batch_tile_height(batch->mfix) : 0;
+  batch->given_tile = rows <= TILE_MAX_ROWS;
   batch->desc_dirty = true;
   return DUGKS_OK;
 }
@@ -571,17 +579,17 @@ int dugks_batch_tune(dugks_batch* batch, int32_t reps, int32_t* rows_out, void* 
   }
   int rc = DUGKS_OK;
   float best_ms = -1.0f;
-  int best = batch->rows, best_tile = 0;
+  int best = batch->rows;
   float best_tile_ms = -1.0f;
   batch->given = true;
   // the block tiles (rows 0), then the heights of the march
   for (int rows : TUNE_ROWS) {
-    batch->given_tile = rows ? 0 : batch_tile_height(batch->mfix);
+    batch->given_tile = rows == 0;
     if (rows) batch->rows = rows;
     batch->desc_dirty = true;
     if ((rc = commit(batch, s))) break;
     // one untimed pass, then the timed passes
-    if ((rc = batch_launch(batch, s, false))) break;
+    if ((rc = batch_launch(batch, s, false, batch->tile_blocks))) break;
     // the step kernels alone leave the queue heads at their ends: rewind them
     if (hipMemsetAsync(batch->d_head, 0, HEAD_BYTES, s) != hipSuccess) {
       rc = DUGKS_EDEVICE;
@@ -589,7 +597,7 @@ int dugks_batch_tune(dugks_batch* batch, int32_t reps, int32_t* rows_out, void* 
     }
     (void)hipEventRecord(e0, s);
     for (int r = 0; r < reps && rc == DUGKS_OK; r++) {
-      rc = batch_launch(batch, s, false);
+      rc = batch_launch(batch, s, false, batch->tile_blocks);
       if (!rc && hipMemsetAsync(batch->d_head, 0, HEAD_BYTES, s) != hipSuccess)
         rc = DUGKS_EDEVICE;
     }
@@ -607,11 +615,10 @@ int dugks_batch_tune(dugks_batch* batch, int32_t reps, int32_t* rows_out, void* 
       best = rows;
     }
   }
-  if (best_ms >= 0.0f && best_tile_ms < best_ms) best_tile = batch_tile_height(batch->mfix);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   batch->rows = best;
-  batch->given_tile = best_tile;
+  batch->given_tile = best_ms >= 0.0f && best_tile_ms < best_ms;
   batch->desc_dirty = true;
   int rc2 = commit(batch, s);
   if (!rc) rc = rc2;

@@ -23,12 +23,8 @@ struct BatchDev {
   int nslots;        // finish-kernel blocks (one per slot)
   int grid_blocks;   // resident wavefronts of the persistent kernel
   int tile;          // rows of the block tiles the list holds; 0: marching tiles
-  int tile_blocks;   // resident blocks of the tile kernel
+  int tile_blocks;   // blocks of the tile kernel: NQUEUE x the longest queue, or more
 };
-
-// Rows of a batch's block tiles: one mass group where the plans carry the
-// fused correction, else 4 (see tile_kernel_rows in dugks_abi.hip).
-inline int batch_tile_height(bool mfix) { return mfix ? MASS_GROUP : 4; }
 
 // One batch step (finish = true) or the step kernels alone, on `s`, for grids
 // of one precision / reconstruction / mass-fix flag / time scheme.
@@ -38,25 +34,17 @@ int launch_batch(const BatchDev& D, int precision, int recon, bool mfix, int sch
 // The most 16-row marching tiles (of all grids together) for which the block
 // tiles are taken: where the two meet, measured on the first grids of a mix of
 // sides 32-512 (us per step, block / 16-row marching tiles): FP32 corrected
-// upwind-3 1305 tiles 55 / 56, central-4 1800 76 / 75, T3S3 1305 108 / 112;
-// FP64 upwind-3 841 55 / 52, central-4 1305 85 / 85, T3S3 463 76 / 102, 841
-// 127 / 111.
+// upwind-3 1305 tiles 52 / 56, 1538 60 / 57, central-4 1800 73 / 76, T3S3 1305
+// 105 / 112; FP64 upwind-3 1305 64 / 66, 1538 75 / 70, central-4 1305 83 / 87,
+// T3S3 841 111 / 111.
 inline int64_t batch_tile_limit(int precision, int recon, int scheme) {
-  if (precision == DUGKS_F32) return recon == DUGKS_CENTRAL4 ? 1700 : 1300;
-  return recon == DUGKS_CENTRAL4 ? 1300 : (scheme == DUGKS_T3S3 ? 600 : 780);
+  if (precision == DUGKS_F32) return recon == DUGKS_CENTRAL4 ? 1800 : 1400;
+  return recon == DUGKS_CENTRAL4 ? 1400 : (scheme == DUGKS_T3S3 ? 850 : 1350);
 }
 
 // The step kernels of launch_batch for a list of block tiles.
 template <typename T>
 void launch_batch_tile(const BatchDev& D, int recon, bool mfix, int scheme, hipStream_t s);
-
-// Resident blocks per CU of the batch tile kernel of that kind.
-template <typename T>
-int batch_tile_occupancy(int recon, bool mfix, int scheme, int* per_cu);
-inline int batch_tile_occupancy(int precision, int recon, bool mfix, int scheme, int* per_cu) {
-  return precision == DUGKS_F64 ? batch_tile_occupancy<double>(recon, mfix, scheme, per_cu)
-                                : batch_tile_occupancy<float>(recon, mfix, scheme, per_cu);
-}
 
 // Resident wavefronts per CU of the batch step kernel of that kind.
 int batch_occupancy(int precision, int recon, bool mfix, int scheme, int* per_cu);

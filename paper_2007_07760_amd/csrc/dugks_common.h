@@ -141,10 +141,27 @@ __host__ __device__ constexpr int step_waves(int esize, int recon, bool mfix) {
 // The tile kernel (dugks_tile.h) takes tiles of up to this many rows; the
 // register budgets of its variants, in wavefronts per SIMD.
 constexpr int TILE_MAX_ROWS = 8;
-__host__ __device__ constexpr int tile_waves(int esize, int recon, int TR) {
-  return wide(recon) ? (esize == 8 ? 4 : 6)
-                     : (esize == 8 ? (recon == DUGKS_CENTRAL4 ? 4 : (TR == 4 ? 5 : 6))
-                                   : (TR == 4 ? 8 : 6));
+// (stage_b: T3S3's second stage, which holds a row of Q as well.)
+__host__ __device__ constexpr int tile_waves(int esize, int recon, int TR, bool stage_b) {
+  if (esize == 8) return wide(recon) || recon == DUGKS_CENTRAL4 || stage_b ? 4 : 6;
+  return wide(recon) || TR > 4 ? 6 : 8;
+}
+
+// Rows of the block tiles of grids that make `tiles4` tiles of 4 rows.  A tile of
+// a corrected plan is one mass group.  Eight rows form 12 cell rows (upwind-5:
+// 14) where twice four form 16 (20), so they take less arithmetic, but a block
+// takes longer and there are half as many: 4 while that leaves compute units
+// idle (FP64 upwind-3 64^2 6.4 us against 8.0; upwind-5 9.4 / 11.8), then 8
+// (768^2 33.0 / 38.0, arrays 33.6 / 37.1; upwind-5 256^2 12.2 / 16.7).  The
+// forms whose 8-row blocks do not fit a compute unit twice keep 4 (FP64
+// central-4 512^2 20.9 / 25.8, T3S3 45.0 / 51.4), and so does FP32, which gains
+// nothing (upwind-3 512^2 10.7 / 12.1).
+__host__ __device__ constexpr bool tall_tiles(int esize, int recon, int scheme) {
+  return wide(recon) || (esize == 8 && scheme == DUGKS_T2 && recon != DUGKS_CENTRAL4);
+}
+inline int block_tile_rows(int esize, int recon, int scheme, bool mfix, int64_t tiles4) {
+  if (mfix) return 8;
+  return tall_tiles(esize, recon, scheme) && tiles4 > 256 ? 8 : 4;
 }
 
 // ------------------------------------------------------------- state layout

@@ -182,9 +182,10 @@ __device__ __forceinline__ T over_norm(T theta, T gx, T gy) {
 // VARR: the velocity comes from caller-supplied cell arrays (steady; a face
 // takes the mean of its two cells) instead of the separable tables.
 // RING_ROWS > 0: the fbar+ rows of a whole tile are in LDS, without pads (the
-// neighbour columns come from lane shifts, see recon_pair).
+// neighbour columns come from lane shifts, see recon_pair).  Args: how it holds
+// the grid's scalars (a reference, in whatever address space they are).
 template <typename T, int R, bool MFIX, int STAGE = STAGE_T2, bool VARR = false,
-          int RING_ROWS = 0>
+          int RING_ROWS = 0, typename Args = const StepArgs<T>&>
 struct Marcher {
   // the wide (upwind-5) patch reaches 2 rows below and 3 above the face row
   // and 3 columns beyond a lane: a 6-row ring, faces 3 rows behind the cell
@@ -206,7 +207,7 @@ struct Marcher {
   static constexpr bool FIX_LOAD = MFIX && STAGE != STAGE_B;
   static constexpr bool FIX_SUM = MFIX && STAGE != STAGE_A;
 
-  const StepArgs<T>& a;
+  Args a;
   const T* __restrict__ src;
   cptr<T> cf;
   const T* __restrict__ tabx;
@@ -291,14 +292,19 @@ struct Marcher {
     }
   }
 
-  // the velocity at the lane's columns and the time factors of step n
+  // the velocity at the lane's east faces (x + 1, unwrapped)
+  __device__ __forceinline__ void flow_east() {
+    if (!VARR) {
+      UXe = tabx[2 * (col + 1)];
+      VXe = tabx[(2 * a.nx + 2) + 2 * (col + 1)];
+    }
+  }
+
+  // the velocity at the lane's cells and the time factors of step n
   __device__ __forceinline__ void flow(int64_t n) {
     if (!VARR) {
-      const int ce = col + 1;  // east face of the column (x + 1), unwrapped
       UXc = tabx[2 * col + 1];
       VXc = tabx[(2 * a.nx + 2) + 2 * col + 1];
-      UXe = tabx[2 * ce];
-      VXe = tabx[(2 * a.nx + 2) + 2 * ce];
     }
     // time factors of the velocity at the stage's base time and at the time of
     // the earlier phi (cells), and at base + its half step (faces); lanes 0, 1
@@ -815,6 +821,7 @@ __device__ __forceinline__ void march_tile(const StepArgs<T>& a, int64_t n,
   m.place((int)threadIdx.x, strip, seg * a.seg_rows, a.seg_rows, dst, dst2, aux, part, pend,
           fitmax);
   m.flow(n);
+  m.flow_east();
   m.run();
 }
 

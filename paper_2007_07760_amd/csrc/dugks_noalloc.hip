@@ -176,10 +176,14 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
   }
   // block tiles where the grids together are too few to fill the chip with
   // marching wavefronts (as a batch chooses them), else each plan's own height
-  int64_t n16 = 0;
-  for (int j = 0; j < n; j++)
+  int64_t n16 = 0, n4 = 0;
+  for (int j = 0; j < n; j++) {
     n16 += (int64_t)plans[j]->nstrips * ((plans[j]->p.ny + 15) / 16);
-  const int tile = n16 <= batch_tile_limit(precision, recon, scheme) ? batch_tile_height(mfix) : 0;
+    n4 += (int64_t)plans[j]->nstrips * ((plans[j]->p.ny + 3) / 4);
+  }
+  const int tile = n16 <= batch_tile_limit(precision, recon, scheme)
+                       ? block_tile_rows(precision == DUGKS_F64 ? 8 : 4, recon, scheme, mfix, n4)
+                       : 0;
   auto segs = [tile](const dugks_plan* P) {
     return tile ? (P->p.ny + tile - 1) / tile : P->many_segs;
   };
@@ -219,14 +223,15 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
   unsigned char* base = nullptr;
   int rc = scratch_of_current_device(&base);
   if (rc) return rc;
-  int dev = 0, ncu = 0, per_cu = 0, tile_per_cu = 0;
+  int dev = 0, ncu = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return DUGKS_EDEVICE;
   if ((rc = batch_occupancy(precision, recon, mfix, scheme, &per_cu)) != DUGKS_OK) return rc;
-  if ((rc = batch_tile_occupancy(precision, recon, mfix, scheme, &tile_per_cu)) != DUGKS_OK)
-    return rc;
-  if (per_cu < 1 || tile_per_cu < 1 || ncu < 1) return DUGKS_EDEVICE;
+  if (per_cu < 1 || ncu < 1) return DUGKS_EDEVICE;
+  int longest = 1;
+  for (int k = 0; k < NQUEUE; k++)
+    longest = std::max(longest, starts.qstart[k + 1] - starts.qstart[k]);
   hipStream_t s = static_cast<hipStream_t>(stream);
   rc = precision == DUGKS_F64
            ? noalloc_setup<double>(plans, states, steps, n, nsteps, tile, starts, base, s)
@@ -240,7 +245,7 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
                    n,
                    per_cu * ncu,
                    tile,
-                   tile_per_cu * ncu};
+                   NQUEUE * longest};
   for (int64_t k = 0; k < nsteps; k++)
     if ((rc = launch_batch(D, precision, recon, mfix, scheme, s, true))) return rc;
   return DUGKS_OK;

@@ -8,20 +8,21 @@
 // y0 - LAG + w, then the faces of that row and its update, with four block
 // barriers between (differences of phi; fbar+ rows; faces; the faces' values
 // below each row).  What bounds it is that chain of latencies: 5.8-6.6 us per
-// step for grids of up to 256 tiles (64^2 FP64: 36 us with the march, 6.7 now;
-// 256^2 8.7; FP32 corrected 256^2 with its reduction 37.7, 12.3; upwind-5 64^2
-// 79, 9.4).  On larger grids it is bound by VALU and LDS: TR rows take the
-// cell terms of TR + 4 (6), so 4-row tiles do twice the march's cell work, and
-// the march wins from ~800^2 (FP64) or ~1100^2 (FP32) on (plan creation holds
-// the rule).  4 rows against 8: a tile's faces wait for fewer rows, and its
-// blocks spread over more compute units (FP64 upwind-3 64^2 6.7 against 8.2
-// us, 1024^2 59.9 against 64.0).
+// step for grids of up to 256 tiles (64^2 FP64: 36 us with the march, 6.4 now;
+// 256^2 8.5; FP32 corrected 256^2 with its reduction 37.7, 12.4; upwind-5 64^2
+// 79, 8.8).  On larger grids it is bound by VALU (a third of it lane shifts):
+// TR rows take the cell terms of TR + 4 (6), so the march wins from ~1050^2 on
+// (see tile_kernel_rows; 4 rows against 8: block_tile_rows).
 //
 // The arithmetic is the march's, expression by expression, so the results are
 // bitwise the same.  The face values take their neighbour columns from lane
-// shifts of one LDS read per row, which needs 80-100 registers in FP64 where
-// reading every tap from LDS needed 224 (spilled at the 5 wavefronts per SIMD
-// it is built for).
+// shifts of one LDS read per row: reading every tap from LDS needed 224
+// registers in FP64, this 80, which leaves room for 24 wavefronts per compute
+// unit (three blocks of 4-row tiles or two of 8).  For that, values that are
+// needed again only after the faces are re-read then (s from LDS, the face
+// velocities from their table), and the north faces' values go to rows of fbar+
+// that no update needs (768^2 FP64 38.9 -> 33.0 us with 8-row tiles; T3S3
+// 104 -> 89).
 #pragma once
 
 #include "dugks_common.h"
@@ -69,8 +70,8 @@ struct TileShared {
 
 // One tile by the whole block: rows [seg * TR, seg * TR + TR) of `strip`, step
 // n; the arguments are march_tile's.
-template <typename T, int R, bool MFIX, int STAGE, bool VARR, int TR>
-__device__ __forceinline__ void tile_step(const StepArgs<T>& a, int64_t n,
+template <typename T, int R, bool MFIX, int STAGE, bool VARR, int TR, typename Args>
+__device__ __forceinline__ void tile_step(Args& a, int64_t n,
                                           const T* __restrict__ src, T* __restrict__ dst,
                                           T* __restrict__ dst2, const T* __restrict__ aux,
                                           const T* __restrict__ cf, const T* __restrict__ tabx,
@@ -78,7 +79,7 @@ __device__ __forceinline__ void tile_step(const StepArgs<T>& a, int64_t n,
                                           double* __restrict__ part, double pend, double fitmax,
                                           int strip, int seg, TileShared<T, R, MFIX, TR>& u) {
   constexpr int CR = tile_cell_rows(R, TR);
-  using M = Marcher<T, R, MFIX, STAGE, VARR, CR>;
+  using M = Marcher<T, R, MFIX, STAGE, VARR, CR, Args&>;
   constexpr int LAG = M::LAG;
   const int lane = threadIdx.x & (LANES - 1);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
@@ -100,6 +101,8 @@ __device__ __forceinline__ void tile_step(const StepArgs<T>& a, int64_t n,
   T qv[10];
   if (STAGE == STAGE_B && upd) m.load_q(k, qv);
   m.flow(n);
+  constexpr bool LEAN = sizeof(T) == 8;
+  if (!LEAN) m.flow_east();
 
   T p, D, A;
   m.phi_row(d, p, D, A);
@@ -134,41 +137,59 @@ __device__ __forceinline__ void tile_step(const StepArgs<T>& a, int64_t n,
     faces<true>(m, k, pn, de, phN, phE);
   else if (north)
     faces<false>(m, k, pn, de, phN, phE);
-  // no wavefront reads another's fbar+ row from here on: each keeps its own in
-  // registers and leaves its north faces (dt*alpha*fbar of the six crossing
-  // velocities, P, Q) in its place for the row above
+  // no wavefront reads another's fbar+ row from here on: each leaves its north
+  // faces (dt*alpha*fbar of the six crossing velocities, P, Q) in a row for the
+  // row above -- of 4-row tiles one that no update needs, else its own, kept
+  // in registers
   __syncthreads();
   const int kk = wrapi(k, a.ny);
+  constexpr bool SPARE = 2 * LAG >= TR;
+  auto face_row = [](int v) {   // of the wavefront v, LAG - 1 <= v < LAG - 1 + TR
+    return !SPARE ? v : (v - (LAG - 1) < LAG ? v - (LAG - 1) : v - (LAG - 1) + TR);
+  };
   T eP, eQx, eQy, PN, QNx, QNy;
   T bp[9];
   if (north) {
-    m.north_moments(kk, phN, m.sxp[LAG], m.syp[LAG], u.s[w + 1][0][lane], u.s[w + 1][1][lane],
+    // FP64: read again here, not held across the faces (6 wavefronts per SIMD)
+    const T sx = LEAN ? u.s[w][0][lane] : m.sxp[LAG], sy = LEAN ? u.s[w][1][lane] : m.syp[LAG];
+    if (LEAN) m.flow_east();
+    m.north_moments(kk, phN, sx, sy, u.s[w + 1][0][lane], u.s[w + 1][1][lane],
                     PN, QNx, QNy);
+    if (!SPARE) {
 #pragma unroll
-    for (int i = 0; i < 9; i++) bp[i] = u.bfp[w][i][lane];
+      for (int i = 0; i < 9; i++) bp[i] = u.bfp[w][i][lane];
+    }
+    if (!SPARE || w < LAG - 1 + TR) {
+      const int v = face_row(w);
 #pragma unroll
-    for (int i = 0; i < 9; i++)
-      if (ey(i) != 0) u.bfp[w][i][lane] = pn[i];
-    u.bfp[w][0][lane] = PN;
-    u.bfp[w][1][lane] = QNx;
-    u.bfp[w][5][lane] = QNy;
-    if (upd) m.east_moments(kk, phE, m.sxp[LAG], m.syp[LAG], eP, eQx, eQy);
+      for (int i = 0; i < 9; i++)
+        if (ey(i) != 0) u.bfp[v][i][lane] = pn[i];
+      u.bfp[v][0][lane] = PN;
+      u.bfp[v][1][lane] = QNx;
+      u.bfp[v][5][lane] = QNy;
+    }
+    if (upd) m.east_moments(kk, phE, sx, sy, eP, eQx, eQy);
   }
   __syncthreads();
   if (upd) {
     T out[9];
+    const int v = face_row(w - 1);
 #pragma unroll
     for (int i = 0; i < 9; i++) {
       out[i] = T(0);
       if (ey(i) != 0) {
-        const T dn = pn[i] - u.bfp[w - 1][i][lane];
+        const T dn = pn[i] - u.bfp[v][i][lane];
         out[i] = ey(i) > 0 ? -dn : dn;
       }
       if (ex(i) != 0) out[i] = ex(i) > 0 ? out[i] - de[i] : out[i] + de[i];
     }
+    if (SPARE) {
+#pragma unroll
+      for (int i = 0; i < 9; i++) bp[i] = u.bfp[w][i][lane];
+    }
     double cs = 0.0, cf0 = 0.0;
-    m.update_cells(kk, bp, out, PN - u.bfp[w - 1][0][lane], QNx - u.bfp[w - 1][1][lane],
-                   QNy - u.bfp[w - 1][5][lane], eP, eQx, eQy, m.cp[LAG], m.cx[LAG], m.cy[LAG],
+    m.update_cells(kk, bp, out, PN - u.bfp[v][0][lane], QNx - u.bfp[v][1][lane],
+                   QNy - u.bfp[v][5][lane], eP, eQx, eQy, m.cp[LAG], m.cx[LAG], m.cy[LAG],
                    p, qv, cs, cf0);
     if (M::FIX_SUM) {
       u.mass.sum[MFIX ? k - m.y0 : 0][lane] = m.owned ? cs : 0.0;
@@ -195,7 +216,7 @@ __device__ __forceinline__ void tile_step(const StepArgs<T>& a, int64_t n,
 }
 
 template <typename T, int R, bool MFIX, int STAGE, bool VARR, int TR>
-__global__ __launch_bounds__(LANES* tile_cell_rows(R, TR), tile_waves(sizeof(T), R, TR)) void
+__global__ __launch_bounds__(LANES* tile_cell_rows(R, TR), tile_waves(sizeof(T), R, TR, STAGE == STAGE_B)) void
 tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__ dst,
             T* __restrict__ dst2, const T* __restrict__ aux, const T* __restrict__ cf,
             const T* __restrict__ tabx, const T* __restrict__ taby, const T* __restrict__ uv,
@@ -205,44 +226,42 @@ tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__
   const int per = (a.nlogical + 7) >> 3;
   const int logical = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if (logical >= a.nlogical) return;
-  tile_step<T, R, MFIX, STAGE, VARR, TR>(a, n, src, dst, dst2, aux, cf, tabx, taby, uv, part,
+  const StepArgs<T>& args = a;
+  tile_step<T, R, MFIX, STAGE, VARR, TR>(args, n, src, dst, dst2, aux, cf, tabx, taby, uv, part,
                                          MFIX ? hdr->pending : 0.0, MFIX ? hdr->fit_max : 0.0,
                                          logical % a.nstrips, logical / a.nstrips, u);
 }
 
 // One batch step (or one stage of a T3S3 batch step) over a work list of
-// TR-row tiles.  The tiles cost the same, so each block takes every so-manieth
-// item of its XCD's queue: no queue heads, and no wait for one before the first
-// tile (an atomic across the XCDs takes longer than a tile's face stage).
+// TR-row tiles, a block per item: the launch holds 8 blocks for every item of
+// the longest queue (or more), block b taking item b / 8 of queue b % 8, its
+// XCD's.  (A loop over items, for a fixed number of resident blocks, kept
+// constants of the arithmetic in registers: 27 spilled in FP64.)
 template <typename T, int R, bool MFIX, int STAGE, int TR>
-__global__ __launch_bounds__(LANES* tile_cell_rows(R, TR), tile_waves(sizeof(T), R, TR)) void
+__global__ __launch_bounds__(LANES* tile_cell_rows(R, TR),
+                             tile_waves(sizeof(T), R, TR, STAGE == STAGE_B)) void
 batch_tile_kernel(const GridDesc<T>* __restrict__ desc, const SlotStep* __restrict__ steps,
                   const BatchCtl* __restrict__ ctl) {
   __shared__ TileShared<T, R, MFIX, TR> u;
   const cptr<BatchCtl> c = as_const(ctl);
-  const cptr<BatchItem> items = as_const(c->items);
   const cptr<SlotStep> st = as_const(steps);
-  const int nq = c->nq;
-  if (nq <= 0) return;
-  const int q = (int)(blockIdx.x % (unsigned)nq);
-  const int end = c->qstart[q + 1];
-  const int stride = ((int)gridDim.x - q + nq - 1) / nq;   // blocks of this queue
-  for (int it = c->qstart[q] + (int)(blockIdx.x / (unsigned)nq); it < end; it += stride) {
-    const BatchItem w = load_const(items + it);
-    const int64_t n = st[w.slot].n;
-    if (n >= st[w.slot].target) continue;
-    const cptr<GridDesc<T>> d = as_const(desc) + w.slot;
-    const StepArgs<T> a = load_const(as_const(STAGE == STAGE_B ? &d->b : &d->a));
-    const int b = (int)(n & 1);
-    // T2 f~^n -> f~^{n+1}; stage A f^^n -> f~(t'), Q; stage B f~(t'), Q -> f^^{n+1}
-    tile_step<T, R, MFIX, STAGE, false, TR>(
-        a, n, STAGE == STAGE_B ? d->mid : d->buf[b], STAGE == STAGE_A ? d->mid : d->buf[b ^ 1],
-        STAGE == STAGE_A ? d->q : nullptr, STAGE == STAGE_B ? d->q : nullptr,
-        STAGE == STAGE_B ? d->cf2 : d->cf, d->tabx, d->taby, nullptr, d->part,
-        MFIX ? d->hdr->pending : 0.0, MFIX ? d->hdr->fit_max : 0.0, w.tile % a.nstrips,
-        w.tile / a.nstrips, u);
-    __syncthreads();   // the next tile writes what this one's wavefronts may still read
-  }
+  const int q = (int)(blockIdx.x % NQUEUE);
+  if (q >= c->nq) return;
+  const int it = c->qstart[q] + (int)(blockIdx.x / NQUEUE);
+  if (it >= c->qstart[q + 1]) return;
+  const BatchItem w = load_const(as_const(c->items) + it);
+  const int64_t n = st[w.slot].n;
+  if (n >= st[w.slot].target) return;
+  const cptr<GridDesc<T>> d = as_const(desc) + w.slot;
+  const auto& a = STAGE == STAGE_B ? d->b : d->a;
+  const int b = (int)(n & 1);
+  // T2 f~^n -> f~^{n+1}; stage A f^^n -> f~(t'), Q; stage B f~(t'), Q -> f^^{n+1}
+  tile_step<T, R, MFIX, STAGE, false, TR>(
+      a, n, STAGE == STAGE_B ? d->mid : d->buf[b], STAGE == STAGE_A ? d->mid : d->buf[b ^ 1],
+      STAGE == STAGE_A ? d->q : nullptr, STAGE == STAGE_B ? d->q : nullptr,
+      STAGE == STAGE_B ? d->cf2 : d->cf, d->tabx, d->taby, nullptr, d->part,
+      MFIX ? d->hdr->pending : 0.0, MFIX ? d->hdr->fit_max : 0.0, w.tile % a.nstrips,
+      w.tile / a.nstrips, u);
 }
 
 }  // namespace dugks

@@ -2,4 +2,3 @@
 #include "dugks_tile_batch_impl.h"
 
 template void dugks::launch_batch_tile<double>(const dugks::BatchDev&, int, bool, int, hipStream_t);
-template int dugks::batch_tile_occupancy<double>(int, bool, int, int*);
