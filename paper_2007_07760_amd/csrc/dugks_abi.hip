@@ -329,17 +329,18 @@ void launch_march(const dugks_plan* P, const StageBufs<T>& q, int64_t n, hipStre
 #undef DUGKS_LAUNCH
 }
 
-// fix = false leaves out the fused mass correction's reduction (tile timing:
-// the header then keeps the correction the next real step applies)
 template <typename T, bool MFIX, int STAGE>
-int launch_stage(const dugks_plan* P, void* state, int64_t n, hipStream_t s, bool fix = true) {
+int launch_stage(const dugks_plan* P, void* state, int64_t n, hipStream_t s, FixUse fix) {
   const Layout& L = P->L;
-  const StageBufs<T> q = stage_bufs<T>(P, state, n, STAGE);
+  StageBufs<T> q = stage_bufs<T>(P, state, n, STAGE);
+  if (fix.prev && STAGE != STAGE_B)
+    q.prev = at<double>(state, fix.prev_spare ? L.off_scratch : L.off_groups);
+  if (fix.spare) q.part = at<double>(state, L.off_scratch);
   if (P->tile)
     launch_tile<T, STAGE>(P, q, n, s);
   else
     launch_march<T, MFIX, STAGE>(P, q, n, s);
-  if (MFIX && fix)
+  if (MFIX && fix.reduce && STAGE != STAGE_A)
     hipLaunchKernelGGL(mass_fix_strips_kernel, dim3(L.tl.nstrips), dim3(LANES), 0, s,
                        q.part, L.ngroups, L.tl.nstrips, at<double>(state, L.off_strips), q.hdr,
                        (double)P->p.nx * (double)P->p.ny);
@@ -347,20 +348,20 @@ int launch_stage(const dugks_plan* P, void* state, int64_t n, hipStream_t s, boo
 }
 
 template <typename T>
-int launch_step(const dugks_plan* P, void* state, int64_t n, hipStream_t s, bool fix = true) {
+int launch_step(const dugks_plan* P, void* state, int64_t n, hipStream_t s, FixUse fix) {
   if (P->p.scheme == DUGKS_T3S3) {
     // with the fused correction, stage A applies the pending one as it reads
     // f^^n and stage B gives the partials of f^^{n+1}: one reduction per step
     if (P->p.flags & DUGKS_FLAG_MASS_FIX) {
-      int rc = launch_stage<T, true, STAGE_A>(P, state, n, s, false);
+      int rc = launch_stage<T, true, STAGE_A>(P, state, n, s, fix);
       return rc ? rc : launch_stage<T, true, STAGE_B>(P, state, n, s, fix);
     }
-    int rc = launch_stage<T, false, STAGE_A>(P, state, n, s);
-    return rc ? rc : launch_stage<T, false, STAGE_B>(P, state, n, s);
+    int rc = launch_stage<T, false, STAGE_A>(P, state, n, s, fix);
+    return rc ? rc : launch_stage<T, false, STAGE_B>(P, state, n, s, fix);
   }
   return (P->p.flags & DUGKS_FLAG_MASS_FIX)
              ? launch_stage<T, true, STAGE_T2>(P, state, n, s, fix)
-             : launch_stage<T, false, STAGE_T2>(P, state, n, s);
+             : launch_stage<T, false, STAGE_T2>(P, state, n, s, fix);
 }
 
 template <typename T>
@@ -604,9 +605,17 @@ int dugks_step(const dugks_plan* plan, void* state, int64_t step, int64_t nsteps
                void* stream) {
   if (!plan || !state || !aligned(state) || step < 0 || nsteps < 0) return DUGKS_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const bool inl = fix_inline(plan);
+  const bool two = plan->p.scheme == DUGKS_T2;   // alternate sets of partials
   for (int64_t k = 0; k < nsteps; k++) {
-    int rc = plan->p.precision == DUGKS_F64 ? launch_step<double>(plan, state, step + k, s)
-                                            : launch_step<float>(plan, state, step + k, s);
+    // the last step's partials are the regular ones, reduced into the header
+    FixUse fix;
+    fix.reduce = !inl || k == nsteps - 1;
+    fix.prev = inl && k > 0;
+    fix.spare = inl && two && ((nsteps - 1 - k) & 1);
+    fix.prev_spare = two && ((nsteps - k) & 1);
+    int rc = plan->p.precision == DUGKS_F64 ? launch_step<double>(plan, state, step + k, s, fix)
+                                            : launch_step<float>(plan, state, step + k, s, fix);
     if (rc) return rc;
   }
   return DUGKS_OK;
@@ -636,9 +645,13 @@ int dugks_tune(const dugks_params* params, void* state, int64_t step, int32_t re
     else
       plans.push_back(P);
   }
+  // without the correction's reduction: the header keeps the correction the next
+  // real step applies
+  FixUse keep;
+  keep.reduce = false;
   auto launch = [&](const dugks_plan* P) {
-    return P->p.precision == DUGKS_F64 ? launch_step<double>(P, state, step, s, false)
-                                       : launch_step<float>(P, state, step, s, false);
+    return P->p.precision == DUGKS_F64 ? launch_step<double>(P, state, step, s, keep)
+                                       : launch_step<float>(P, state, step, s, keep);
   };
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (!rc && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess))

@@ -283,10 +283,7 @@ struct Marcher {
     y1 = min(first + rows, a.ny);
     base = y0 - LAG - 1;   // at or below every ring row the march touches
     if (MFIX) {
-      cw0 = T(wq(0) * pend);
-      cw1 = T(wq(1) * pend);
-      cw2 = T(wq(2) * pend);
-      fitmax = T(fitmax_);
+      set_fix(pend, fitmax_);
       part_row = part + 2 * (int64_t)strip * a.ngroups;
       rpart = make_rsrc(part_row, (unsigned)(16 * a.ngroups));
     }
@@ -340,31 +337,48 @@ struct Marcher {
     return src + (int64_t)rr * a.CH + loff;
   }
 
-  __device__ __forceinline__ void load_row(RowRegs<T>& d, int row) {
+  // a row of the source as stored
+  __device__ __forceinline__ void load_raw(RowRegs<T>& d, int row) {
     const int rw = wrapi(row, a.ny);
     const T* p = row_src(rw);
 #pragma unroll
     for (int i = 0; i < 9; i++) d.f[i] = p[i * OWN];
-    if (FIX_LOAD) {
-      // the pending w_i delta of the cell's weight class, or 0 (one select
-      // per class instead of one per plane)
-      const bool fit = d.f[0] < fitmax;
-      const T c0 = fit ? cw0 : T(0), c1 = fit ? cw1 : T(0), c2 = fit ? cw2 : T(0);
-#pragma unroll
-      for (int i = 0; i < 9; i++) d.f[i] += i == 0 ? c0 : ((i & 1) ? c1 : c2);
-    }
     d.hp = p[9 * OWN];
     if (WIDE && (lane == 0 || lane == LANES - 1)) {
       const T* q = src + (int64_t)rw * a.CH + loffx;
 #pragma unroll
       for (int i = 0; i < 9; i++) d.g[i] = q[i * OWN];
-      if (FIX_LOAD) {
-        const bool fit = d.g[0] < fitmax;
-        const T c0 = fit ? cw0 : T(0), c1 = fit ? cw1 : T(0), c2 = fit ? cw2 : T(0);
-#pragma unroll
-        for (int i = 0; i < 9; i++) d.g[i] += i == 0 ? c0 : ((i & 1) ? c1 : c2);
-      }
     }
+  }
+
+  // the mass correction still to apply (FIX_LOAD), to a loaded row
+  __device__ __forceinline__ void set_fix(double pend, double fit_max) {
+    cw0 = T(wq(0) * pend);
+    cw1 = T(wq(1) * pend);
+    cw2 = T(wq(2) * pend);
+    fitmax = T(fit_max);
+  }
+  __device__ __forceinline__ void fix_row(RowRegs<T>& d) const {
+    if (!FIX_LOAD) return;
+    // the pending w_i delta of the cell's weight class, or 0 (one select
+    // per class instead of one per plane)
+    {
+      const bool fit = d.f[0] < fitmax;
+      const T c0 = fit ? cw0 : T(0), c1 = fit ? cw1 : T(0), c2 = fit ? cw2 : T(0);
+#pragma unroll
+      for (int i = 0; i < 9; i++) d.f[i] += i == 0 ? c0 : ((i & 1) ? c1 : c2);
+    }
+    if (WIDE && (lane == 0 || lane == LANES - 1)) {
+      const bool fit = d.g[0] < fitmax;
+      const T c0 = fit ? cw0 : T(0), c1 = fit ? cw1 : T(0), c2 = fit ? cw2 : T(0);
+#pragma unroll
+      for (int i = 0; i < 9; i++) d.g[i] += i == 0 ? c0 : ((i & 1) ? c1 : c2);
+    }
+  }
+
+  __device__ __forceinline__ void load_row(RowRegs<T>& d, int row) {
+    load_raw(d, row);
+    fix_row(d);
   }
 
   // phi = sum_i f~_i (Eq. 30, pairwise) of a new row and its horizontal
@@ -890,55 +904,59 @@ __device__ __forceinline__ void neu_add(double& s, double& c, double v) {
 // still loses is in the next step's total and corrected then.
 // A non-finite total marks the state as blown up (sticky status ENUMERIC) and
 // sets no correction.
-__device__ __forceinline__ void mass_fix_set(StateHeader* __restrict__ hdr, double m_new,
-                                             double nfit, double ncells) {
+__device__ __forceinline__ void mass_fix_values(double mass0, double m_new, double nfit,
+                                                double ncells, double& pending,
+                                                double& fit_max) {
   const bool to_fit = nfit >= 0.01 * ncells && nfit >= 1.0;
-  hdr->fit_max = to_fit ? MASS_FIT_MAX : INFINITY;
-  hdr->mass_now = m_new;
-  if (isfinite(m_new)) {
-    hdr->pending = (hdr->mass0 - m_new) / (to_fit ? nfit : ncells);
-  } else {
-    hdr->pending = 0.0;
-    hdr->status = DUGKS_ENUMERIC;
-  }
+  fit_max = to_fit ? MASS_FIT_MAX : INFINITY;
+  pending = isfinite(m_new) ? (mass0 - m_new) / (to_fit ? nfit : ncells) : 0.0;
 }
 
-// Fixed-order (Neumaier) sum of n pairs (v[2j], v[2j+1]) by one wavefront:
-// lane l takes the pairs l, l + 64, ... (U loads in flight), then the lanes
-// are folded in halves.  Lane 0 receives the two totals.  The order depends
-// on n only, so any wavefront of any kernel computes the same bits.
-__device__ __forceinline__ void wave_pair_sum(const double* __restrict__ v, int n, double& t0,
-                                              double& t1) {
+__device__ __forceinline__ void mass_fix_set(StateHeader* __restrict__ hdr, double m_new,
+                                             double nfit, double ncells) {
+  mass_fix_values(hdr->mass0, m_new, nfit, ncells, hdr->pending, hdr->fit_max);
+  hdr->mass_now = m_new;
+  if (!isfinite(m_new)) hdr->status = DUGKS_ENUMERIC;
+}
+
+// Fixed-order sum of n pairs (v[2j], v[2j+1]) by one wavefront, Neumaier for the
+// first of the pair (masses), plain for the second (counts, whose sums are
+// exact): lane l takes the pairs l, l + 64, ... (U loads in flight), then the
+// lanes are folded in halves.  Lane 0 receives the two totals.  The order
+// depends on n only, so any wavefront of any kernel computes the same bits;
+// pairs and folds that would only add zeros are left out.
+__device__ __forceinline__ void wave_pair_sum(const double* v, int n, double& t0, double& t1) {
   constexpr int U = 8;
   const int lane = threadIdx.x & (LANES - 1);
-  double s0 = 0.0, c0 = 0.0, s1 = 0.0, c1 = 0.0;
-  for (int j0 = lane; j0 < n; j0 += U * LANES) {
+  double s0 = 0.0, c0 = 0.0, s1 = 0.0;
+  for (int j0 = 0; j0 < n; j0 += U * LANES) {
     double w[U][2];
 #pragma unroll
     for (int u = 0; u < U; u++) {
-      const int j = j0 + u * LANES;
+      const int j = j0 + u * LANES + lane;
       w[u][0] = j < n ? v[2 * j] : 0.0;
       w[u][1] = j < n ? v[2 * j + 1] : 0.0;
     }
 #pragma unroll
     for (int u = 0; u < U; u++) {
+      if (j0 + u * LANES >= n) break;
       neu_add(s0, c0, w[u][0]);
-      neu_add(s1, c1, w[u][1]);
+      s1 += w[u][1];
     }
   }
 #pragma unroll
   for (int off = LANES / 2; off > 0; off >>= 1) {
+    if (off >= n) continue;
     const double os0 = __shfl_down(s0, off), oc0 = __shfl_down(c0, off);
-    const double os1 = __shfl_down(s1, off), oc1 = __shfl_down(c1, off);
+    const double os1 = __shfl_down(s1, off);
     if (lane < off) {
       c0 += oc0;
       neu_add(s0, c0, os0);
-      c1 += oc1;
-      neu_add(s1, c1, os1);
+      s1 += os1;
     }
   }
   t0 = s0 + c0;
-  t1 = s1 + c1;
+  t1 = s1;
 }
 
 // One-grid reduction in one launch: wavefront b sums the groups of strip b

@@ -41,6 +41,25 @@ struct dugks_plan {
 
 namespace dugks {
 
+// How a launch of the step deals with the fused mass correction: `reduce` runs
+// the reduction kernel after it, which leaves the correction in the header;
+// `prev` forms the correction from the last step's partials in the step kernel
+// itself; `spare`, `prev_spare`: the partials written, read are in the state's
+// mass scratch.
+struct FixUse {
+  bool reduce = true, prev = false, spare = false, prev_spare = false;
+};
+
+// Plans whose steps may form the correction themselves: the tile kernel sums the
+// partials again in every block, so few of them (one strip per wavefront, one
+// group per lane), and a second set of them has to fit the mass scratch (T3S3
+// writes them a launch after it has read them).
+inline bool fix_inline(const dugks_plan* P) {
+  if (!(P->p.flags & DUGKS_FLAG_MASS_FIX) || !P->tile) return false;
+  if (P->nstrips > MASS_GROUP + 4 || P->L.ngroups > LANES) return false;
+  return P->p.scheme == DUGKS_T3S3 || P->nstrips * P->L.ngroups <= MASS_BLOCKS;
+}
+
 inline int hip_status(hipError_t e) { return e == hipSuccess ? DUGKS_OK : DUGKS_EDEVICE; }
 
 template <typename T>
@@ -66,7 +85,8 @@ struct StageBufs {
   const T* tabx;
   const T* taby;
   const T* uv;
-  double* part;
+  double* part;              // mass partials this launch writes
+  const double* prev;        // those its correction is to be formed from, or nullptr
   StateHeader* hdr;
 };
 
@@ -92,6 +112,7 @@ inline StageBufs<T> stage_bufs(const dugks_plan* P, void* state, int64_t n, int 
   q.taby = at<T>(state, L.off_taby);
   q.uv = P->p.vel_kind == DUGKS_VEL_ARRAYS ? at<T>(state, L.off_vel) : nullptr;
   q.part = at<double>(state, L.off_groups);
+  q.prev = nullptr;
   q.hdr = at<StateHeader>(state, 0);
   return q;
 }

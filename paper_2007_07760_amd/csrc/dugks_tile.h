@@ -9,7 +9,7 @@
 // barriers between (differences of phi; fbar+ rows; faces; the faces' values
 // below each row).  What bounds it is that chain of latencies: 5.8-6.6 us per
 // step for grids of up to 256 tiles (64^2 FP64: 36 us with the march, 6.4 now;
-// 256^2 8.5; FP32 corrected 256^2 with its reduction 37.7, 12.4; upwind-5 64^2
+// 256^2 8.5; FP32 corrected 256^2 with its reduction 37.7, 9.2; upwind-5 64^2
 // 79, 8.8).  On larger grids it is bound by VALU (a third of it lane shifts):
 // TR rows take the cell terms of TR + 4 (6), so the march wins from ~1050^2 on
 // (see tile_kernel_rows; 4 rows against 8: block_tile_rows).
@@ -66,10 +66,47 @@ struct TileShared {
       int fit[MFIX ? TR : 1][LANES];
     } mass;
   };
+  double red[MFIX ? 2 * CR + 2 : 1];   // sums of the strips, the correction (see fix_inline)
 };
 
+// The mass correction from the partials of the last step, by every block: strip
+// w by wavefront w, then the strips by the first, in the order of
+// mass_fix_strips_kernel (the same bits).  Its loads are in flight with those of
+// the rows, so a step pays the sums (~1 us) and not another launch (5.2 us):
+// FP32 corrected 256^2 12.4 -> 9.2 us, 64^2 11.9 -> 8.0.  For up to CR strips and 64 groups each
+// (fix_inline): the sums are done by every block again.
+template <int CR>
+__device__ __forceinline__ void block_fix(const double* __restrict__ prev, int nstrips,
+                                          int ngroups, double ncells, bool first,
+                                          StateHeader* __restrict__ hdr, double* red,
+                                          double& pend, double& fitmax) {
+  const int lane = threadIdx.x & (LANES - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
+  const double mass0 = hdr->mass0;
+  double m, c;
+  if (w < nstrips) {
+    wave_pair_sum(prev + 2 * (int64_t)w * ngroups, ngroups, m, c);
+    if (lane == 0) {
+      red[2 * w] = m;
+      red[2 * w + 1] = c;
+    }
+  }
+  __syncthreads();
+  if (w == 0) {
+    wave_pair_sum(red, nstrips, m, c);
+    if (lane == 0) {
+      mass_fix_values(mass0, m, c, ncells, red[2 * CR], red[2 * CR + 1]);
+      if (first && !isfinite(m)) hdr->status = DUGKS_ENUMERIC;
+    }
+  }
+  __syncthreads();
+  pend = red[2 * CR];
+  fitmax = red[2 * CR + 1];
+}
+
 // One tile by the whole block: rows [seg * TR, seg * TR + TR) of `strip`, step
-// n; the arguments are march_tile's.
+// n; the arguments are march_tile's, and prev: the partials of the last step, if
+// the correction is still to be formed from them (see block_fix).
 template <typename T, int R, bool MFIX, int STAGE, bool VARR, int TR, typename Args>
 __device__ __forceinline__ void tile_step(Args& a, int64_t n,
                                           const T* __restrict__ src, T* __restrict__ dst,
@@ -77,7 +114,9 @@ __device__ __forceinline__ void tile_step(Args& a, int64_t n,
                                           const T* __restrict__ cf, const T* __restrict__ tabx,
                                           const T* __restrict__ taby, const T* __restrict__ uv,
                                           double* __restrict__ part, double pend, double fitmax,
-                                          int strip, int seg, TileShared<T, R, MFIX, TR>& u) {
+                                          int strip, int seg, const double* __restrict__ prev,
+                                          StateHeader* __restrict__ hdr,
+                                          TileShared<T, R, MFIX, TR>& u) {
   constexpr int CR = tile_cell_rows(R, TR);
   using M = Marcher<T, R, MFIX, STAGE, VARR, CR, Args&>;
   constexpr int LAG = M::LAG;
@@ -95,14 +134,23 @@ __device__ __forceinline__ void tile_step(Args& a, int64_t n,
   const int k = r;                                  // its face row
   const bool upd = k >= m.y0 && k < m.y1;
   RowRegs<T> d, o;
-  m.load_row(d, min(r, top + 1));
+  m.load_raw(d, min(r, top + 1));
   const bool outer = w == 0 || w == CR - 1;
-  if (outer) m.load_row(o, w == 0 ? m.y0 - LAG - 1 : min(r + 1, top + 1));
+  if (outer) m.load_raw(o, w == 0 ? m.y0 - LAG - 1 : min(r + 1, top + 1));
   T qv[10];
   if (STAGE == STAGE_B && upd) m.load_q(k, qv);
   m.flow(n);
   constexpr bool LEAN = sizeof(T) == 8;
   if (!LEAN) m.flow_east();
+  if (M::FIX_LOAD) {
+    if (prev) {
+      block_fix<CR>(prev, a.nstrips, a.ngroups, (double)a.nx * (double)a.ny,
+                    strip == 0 && seg == 0, hdr, u.red, pend, fitmax);
+      m.set_fix(pend, fitmax);
+    }
+    m.fix_row(d);
+    if (outer) m.fix_row(o);
+  }
 
   T p, D, A;
   m.phi_row(d, p, D, A);
@@ -220,7 +268,8 @@ __global__ __launch_bounds__(LANES* tile_cell_rows(R, TR), tile_waves(sizeof(T),
 tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__ dst,
             T* __restrict__ dst2, const T* __restrict__ aux, const T* __restrict__ cf,
             const T* __restrict__ tabx, const T* __restrict__ taby, const T* __restrict__ uv,
-            double* __restrict__ part, const StateHeader* __restrict__ hdr) {
+            double* __restrict__ part, const double* __restrict__ prev,
+            StateHeader* __restrict__ hdr) {
   __shared__ TileShared<T, R, MFIX, TR> u;
   // bands of tiles per XCD, as in step_kernel
   const int per = (a.nlogical + 7) >> 3;
@@ -229,7 +278,7 @@ tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__
   const StepArgs<T>& args = a;
   tile_step<T, R, MFIX, STAGE, VARR, TR>(args, n, src, dst, dst2, aux, cf, tabx, taby, uv, part,
                                          MFIX ? hdr->pending : 0.0, MFIX ? hdr->fit_max : 0.0,
-                                         logical % a.nstrips, logical / a.nstrips, u);
+                                         logical % a.nstrips, logical / a.nstrips, prev, hdr, u);
 }
 
 // One batch step (or one stage of a T3S3 batch step) over a work list of
@@ -261,7 +310,7 @@ batch_tile_kernel(const GridDesc<T>* __restrict__ desc, const SlotStep* __restri
       STAGE == STAGE_A ? d->q : nullptr, STAGE == STAGE_B ? d->q : nullptr,
       STAGE == STAGE_B ? d->cf2 : d->cf, d->tabx, d->taby, nullptr, d->part,
       MFIX ? d->hdr->pending : 0.0, MFIX ? d->hdr->fit_max : 0.0, w.tile % a.nstrips,
-      w.tile / a.nstrips, u);
+      w.tile / a.nstrips, nullptr, d->hdr, u);
 }
 
 }  // namespace dugks

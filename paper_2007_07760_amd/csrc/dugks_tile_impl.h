@@ -12,7 +12,7 @@ static void tile_go(const StepArgs<T>& a, const StageBufs<T>& q, int64_t n, hipS
   const int per = (a.nlogical + 7) / 8;   // tiles per XCD (see the kernel's order)
   hipLaunchKernelGGL((tile_kernel<T, R, MFIX, STAGE, VARR, TR>), dim3(per * 8),
                      dim3(LANES * tile_cell_rows(R, TR)), 0, s, a, n, q.src, q.dst, q.dst2, q.aux,
-                     q.cf, q.tabx, q.taby, q.uv, q.part, q.hdr);
+                     q.cf, q.tabx, q.taby, q.uv, q.part, q.prev, q.hdr);
 }
 
 template <typename T, int R, int STAGE, bool VARR>

@@ -43,3 +43,41 @@ def test_tile_equals_march_bitwise(precision, recon, flags, scheme, vel):
             assert torch.equal(s.distributions(), march.distributions()), (nx, ny, rows)
             assert torch.equal(s.history(), march.history()), (nx, ny, rows)
             assert s.mass() == march.mass() and s.status() == march.status()
+
+
+# sides at the edges of the rule for forming the correction in the step kernel:
+# 12 strips, 64 groups of 8 rows and (T2) 256 groups in all do, one more does not
+@pytest.mark.parametrize("nx,ny,scheme", [(640, 168, 0), (696, 170, 0), (697, 40, 0),
+                                          (58, 512, 0), (20, 513, 0), (696, 512, 1)])
+def test_correction_formed_in_the_step(nx, ny, scheme):
+    """Corrected plans: six steps in one call (the correction formed from the
+    last step's partials by the step kernel) against six calls (each with the
+    reduction kernel) and the march; bitwise, with the mass and the status.
+    The blow-up of one cell is reported by all."""
+    import torch
+    from paper_2007_07760_amd.solver import Solver
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    print(f"case {nx}x{ny} scheme={scheme}", flush=True)
+    r = min(nx, ny)
+    phi0 = I.random_circles(nx, ny, 3, 0.1 * r, 0.3 * r, 4.0, seed=nx)
+    for bad in (False, True):
+        if bad:
+            phi0 = phi0.copy()
+            phi0[ny // 2, nx // 3] = 1e38   # its square overflows in FP32
+
+        def start(rows):
+            return Solver(nx, ny, 0.02, 4.0, 0.5, precision=1, vel_kind=1,
+                          vel_param=(0.0005, nx / 2, ny / 2), flags=2, tile_rows=rows,
+                          scheme=scheme).init(phi0)
+
+        one, many, march = start(8).step(6), start(8), start(16).step(6)
+        for _ in range(6):
+            many.step(1)
+        for s in (many, march):
+            assert s.status() == one.status()
+            if not bad:
+                assert torch.equal(s.distributions(), one.distributions())
+                assert torch.equal(s.history(), one.history())
+                assert s.mass() == one.mass()
+        assert (one.status() != 0) == bad
