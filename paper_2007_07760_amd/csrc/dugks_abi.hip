@@ -435,29 +435,26 @@ int do_init(const dugks_plan* P, void* state, const double* phi0, const double* 
 template <typename T>
 int do_phi(const dugks_plan* P, const void* state, int64_t n, void* out, hipStream_t s) {
   const Layout& L = P->L;
-  const int nx = P->p.nx, ny = P->p.ny;
-  dim3 grid((nx + 255) / 256, ny), block(256);
-  hipLaunchKernelGGL((phi_kernel<T>), grid, block, 0, s, at<T>(state, L.off_buf[n & 1]), L.tl,
-                     at<StateHeader>(state, 0), static_cast<T*>(out));
+  hipLaunchKernelGGL((phi_kernel<T>), read_grid<T>(P->p.nx, P->p.ny), dim3(READ_THREADS), 0, s,
+                     at<T>(state, L.off_buf[n & 1]), L.tl, at<StateHeader>(state, 0),
+                     static_cast<T*>(out));
   return hip_status(hipGetLastError());
 }
 
 template <typename T>
 int do_export(const dugks_plan* P, const void* state, int64_t n, void* out, hipStream_t s) {
   const Layout& L = P->L;
-  const int nx = P->p.nx, ny = P->p.ny;
-  dim3 grid((nx + 255) / 256, ny, 9), block(256);
-  hipLaunchKernelGGL((export_kernel<T>), grid, block, 0, s, at<T>(state, L.off_buf[n & 1]), L.tl,
-                     at<StateHeader>(state, 0), static_cast<T*>(out));
+  hipLaunchKernelGGL((export_kernel<T>), read_grid<T>(P->p.nx, P->p.ny), dim3(READ_THREADS), 0, s,
+                     at<T>(state, L.off_buf[n & 1]), L.tl, at<StateHeader>(state, 0),
+                     static_cast<T*>(out));
   return hip_status(hipGetLastError());
 }
 
 template <typename T>
 int do_history(const dugks_plan* P, const void* state, int64_t n, void* out, hipStream_t s) {
   const Layout& L = P->L;
-  dim3 grid((P->p.nx + 255) / 256, P->p.ny), block(256);
-  hipLaunchKernelGGL((history_kernel<T>), grid, block, 0, s, at<T>(state, L.off_buf[n & 1]),
-                     L.tl, static_cast<T*>(out));
+  hipLaunchKernelGGL((history_kernel<T>), read_grid<T>(P->p.nx, P->p.ny), dim3(READ_THREADS), 0, s,
+                     at<T>(state, L.off_buf[n & 1]), L.tl, static_cast<T*>(out));
   return hip_status(hipGetLastError());
 }
 

@@ -1228,41 +1228,95 @@ __device__ __forceinline__ T stored_f(T v, int i, T f0, const StateHeader* hdr) 
   return (pend != 0.0 && f0 < T(hdr->fit_max)) ? v + T(wq(i) * pend) : v;
 }
 
+// Reading the state back: a thread takes two neighbouring columns in FP32 (strips
+// and chunks have even lengths, so a pair never straddles two strips and loads
+// as one word; a 4-byte column per lane reached 3-3.5 TB/s), one in FP64 (two
+// were 7 % slower), and all planes of its cells, where a thread per plane read
+// plane 0 nine times over for the correction.  4096^2: FP32 phi 189 -> 129 us,
+// distributions 385 -> 253 (5.7 and 4.8 TB/s); FP64 250, 498 -> 460.  Bound: HBM.
+constexpr int READ_THREADS = 256;                // along a row
 template <typename T>
-__global__ __launch_bounds__(256) void phi_kernel(const T* __restrict__ buf, Tiling tl,
-                                                  const StateHeader* __restrict__ hdr,
-                                                  T* __restrict__ out) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y;
-  if (x >= tl.nx || y >= tl.ny) return;
-  const int64_t o = tl.idx(0, y, x);
-  const T f0 = buf[o];
-  T s = stored_f(f0, 0, f0, hdr);
+constexpr int READ_C = sizeof(T) == 4 ? 2 : 1;   // columns of a thread
+template <typename T>
+dim3 read_grid(int nx, int ny) {
+  constexpr int cols = READ_C<T> * READ_THREADS;
+  return dim3((nx + cols - 1) / cols, ny);
+}
+
+template <typename T>
+struct alignas(READ_C<T> * sizeof(T)) Cells {
+  T v[READ_C<T>];
+};
+
+// the thread's cells (x, y), ..; false: outside the grid
+template <typename T>
+__device__ __forceinline__ bool read_cells(const Tiling& tl, int& x, int& y) {
+  x = READ_C<T> * (blockIdx.x * READ_THREADS + threadIdx.x);
+  y = blockIdx.y;
+  return x < tl.nx;
+}
+
+template <typename T>
+__device__ __forceinline__ Cells<T> load_cells(const T* __restrict__ p) {
+  return *reinterpret_cast<const Cells<T>*>(p);
+}
+
+// dense rows: their starts are aligned to single elements only
+template <typename T>
+__device__ __forceinline__ void store_cells(T* __restrict__ out, const Cells<T>& q, bool whole) {
+  if (whole)
+    __builtin_memcpy(out, q.v, sizeof(q.v));
+  else
+    out[0] = q.v[0];
+}
+
+template <typename T>
+__global__ __launch_bounds__(READ_THREADS) void phi_kernel(const T* __restrict__ buf, Tiling tl,
+                                                           const StateHeader* __restrict__ hdr,
+                                                           T* __restrict__ out) {
+  int x, y;
+  if (!read_cells<T>(tl, x, y)) return;
+  const T* __restrict__ p = buf + tl.idx(0, y, x);
+  Cells<T> f[9];
 #pragma unroll
-  for (int i = 1; i < 9; i++) s += stored_f(buf[o + i * OWN], i, f0, hdr);
-  out[(int64_t)y * tl.nx + x] = s;
+  for (int i = 0; i < 9; i++) f[i] = load_cells(p + i * OWN);
+  Cells<T> s;
+#pragma unroll
+  for (int c = 0; c < READ_C<T>; c++) {
+    s.v[c] = stored_f(f[0].v[c], 0, f[0].v[c], hdr);
+#pragma unroll
+    for (int i = 1; i < 9; i++) s.v[c] += stored_f(f[i].v[c], i, f[0].v[c], hdr);
+  }
+  store_cells(out + (int64_t)y * tl.nx + x, s, x + READ_C<T> <= tl.nx);
 }
 
 // the phi history plane (phi^{n-1} of a state at step n), as stored
 template <typename T>
-__global__ __launch_bounds__(256) void history_kernel(const T* __restrict__ buf, Tiling tl,
-                                                      T* __restrict__ out) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y;
-  if (x >= tl.nx || y >= tl.ny) return;
-  out[(int64_t)y * tl.nx + x] = buf[tl.idx(9, y, x)];
+__global__ __launch_bounds__(READ_THREADS) void history_kernel(const T* __restrict__ buf, Tiling tl,
+                                                               T* __restrict__ out) {
+  int x, y;
+  if (!read_cells<T>(tl, x, y)) return;
+  store_cells(out + (int64_t)y * tl.nx + x, load_cells(buf + tl.idx(9, y, x)),
+              x + READ_C<T> <= tl.nx);
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void export_kernel(const T* __restrict__ buf, Tiling tl,
-                                                     const StateHeader* __restrict__ hdr,
-                                                     T* __restrict__ out) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y;
-  const int i = blockIdx.z;
-  if (x >= tl.nx || y >= tl.ny) return;
-  out[((int64_t)i * tl.ny + y) * tl.nx + x] =
-      stored_f(buf[tl.idx(i, y, x)], i, buf[tl.idx(0, y, x)], hdr);
+__global__ __launch_bounds__(READ_THREADS) void export_kernel(
+    const T* __restrict__ buf, Tiling tl, const StateHeader* __restrict__ hdr,
+    T* __restrict__ out) {
+  int x, y;
+  if (!read_cells<T>(tl, x, y)) return;
+  const T* __restrict__ p = buf + tl.idx(0, y, x);
+  Cells<T> f[9];
+#pragma unroll
+  for (int i = 0; i < 9; i++) f[i] = load_cells(p + i * OWN);
+  const Cells<T> f0 = f[0];
+#pragma unroll
+  for (int i = 0; i < 9; i++) {
+#pragma unroll
+    for (int c = 0; c < READ_C<T>; c++) f[i].v[c] = stored_f(f[i].v[c], i, f0.v[c], hdr);
+    store_cells(out + ((int64_t)i * tl.ny + y) * tl.nx + x, f[i], x + READ_C<T> <= tl.nx);
+  }
 }
 
 // ------------------------------------------------------------------ mass
