@@ -9,7 +9,7 @@ import numpy as np
 import torch
 
 from . import _lib as C
-from .solver import Solver
+from .solver import Solver, current_stream
 
 
 class Batch:
@@ -32,9 +32,7 @@ class Batch:
             C.dugks_batch_destroy(h)
             self.handle = None
 
-    @staticmethod
-    def stream() -> int:
-        return torch.cuda.current_stream().cuda_stream
+    stream = staticmethod(current_stream)
 
     def set(self, slot: int, solver: Solver, target: int) -> None:
         """Attach `solver` (at its current step) to `slot` until `target`."""

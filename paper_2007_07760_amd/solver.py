@@ -10,6 +10,17 @@ import torch
 
 from . import _lib as C
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def current_stream() -> int:
+    """The hipStream_t of the current device's current stream.  Building the
+    Stream object torch.cuda.current_stream() returns takes 2.8 us, of a call
+    that launches one kernel in 4; torch's own accessor of the handle 0.3."""
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
 
 class Solver:
     """A D2Q9 DUGKS solve of the conservative Allen-Cahn equation on one
@@ -42,9 +53,7 @@ class Solver:
             C.dugks_plan_destroy(plan)
             self.plan = None
 
-    @staticmethod
-    def stream() -> int:
-        return torch.cuda.current_stream().cuda_stream
+    stream = staticmethod(current_stream)
 
     @staticmethod
     def _device_f64(a, device) -> torch.Tensor:

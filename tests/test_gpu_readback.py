@@ -32,3 +32,15 @@ def test_readback(precision, flags, nx, ny):
     # the cells are where they were put: phi moves by far less than it varies
     s.init(phi0)
     assert float((s.phi() - first).abs().max()) < 1e-5
+
+
+def test_stream_is_the_current_one():
+    import torch
+    from paper_2007_07760_amd.batch import Batch
+    from paper_2007_07760_amd.solver import Solver
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    side = torch.cuda.Stream()
+    for ctx in (torch.cuda.stream(torch.cuda.default_stream()), torch.cuda.stream(side)):
+        with ctx:
+            assert Solver.stream() == Batch.stream() == torch.cuda.current_stream().cuda_stream
