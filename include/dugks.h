@@ -153,7 +153,8 @@ typedef struct {
   double vel_param[6];     /* p0.. of the velocity kind; finite                  */
   int32_t tile_rows;       /* rows of a tile; 0 = library default.  Up to 8: a block
                               of wavefronts takes the tile's rows side by side (the
-                              default for small grids); more: one wavefront marches
+                              default for small grids; at 8, for grids whose default
+                              is to march 8 rows, that); more: one wavefront marches
                               them.  Results do not depend on it. */
   int32_t scheme;          /* dugks_scheme                                       */
 } dugks_params;

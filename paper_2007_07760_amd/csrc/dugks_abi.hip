@@ -253,22 +253,34 @@ int whole_round_rows(const dugks_params& p, int nstrips) {
   return best;
 }
 
-// Default rows per marching wavefront.  16, the shortest: although its halo
-// rows cost a fifth of the arithmetic, the wavefronts of neighbouring strips
-// stay in step, so the lines they share are still cached, and the last round
-// is short.  us per step at 16 / 72-128 rows (the whole-round heights): 4096^2
-// FP64 upwind-3 602 / 692, FP32 corrected 367 / 469, velocity arrays 715 / 821,
-// T3S3 1779 / 2006; 2900^2 FP64 309 / 325, FP32 corrected 194 / 244.  Only
-// where 16-row tiles make a second round that is not full, the shortest height
-// that makes one round: 1536^2 FP64 97 at 24 rows against 105 at 16, central-4
-// 1280^2 110 at 24 against 136, FP32 corrected T3S3 2048^2 277 at 32 against
-// 288.  Upwind-5, one wavefront per SIMD in FP64, keeps whole rounds (2048^2
-// 377 against 432 at 16).
+// Default rows per marching wavefront.
+// Grids of two rounds of 16-row tiles and more: 16.  Although its halo rows cost
+// a fifth of the arithmetic, the wavefronts of neighbouring strips stay in step,
+// so the lines they share are still cached, and the last round is short.  us
+// per step at 16 / 72-128 rows (whole rounds): 4096^2 FP64 upwind-3 602 / 692,
+// FP32 corrected 367 / 469, velocity arrays 715 / 821, T3S3 1779 / 2006; 2900^2
+// FP64 309 / 325, FP32 corrected 194 / 244.
+// Smaller ones: the shortest height of one round (at least 8 rows), since a
+// step then takes one tile's time.  us per step at it / at 16: FP64 upwind-3
+// 1024^2 51.7 (10 rows) / 54.9, 1536^2 97 (24) / 105; central-4 1280^2 110 (24)
+// / 136; T3S3 896^2 96.6 (8) / 105.9; FP32 corrected 1024^2 38.0 (8) / 45.8, T3S3
+// 2048^2 277 (32) / 288.  FP32 without the correction runs 4 wavefronts per SIMD
+// and is bound by VALU long before they are all there: a round of half of them
+// (1280^2 50.2 at 8 rows, 45.6 at 16).
+// Upwind-5, one wavefront per SIMD in FP64, keeps whole rounds (2048^2 377
+// against 432 at 16).
 int default_tile_rows(const dugks_params& p, int nstrips) {
   if (p.recon == DUGKS_UPWIND5) return whole_round_rows(p, nstrips);
+  const bool fix = (p.flags & DUGKS_FLAG_MASS_FIX) != 0;
   const long resident = resident_wavefronts(p);
   auto tiles = [&](int seg) { return (long)nstrips * ((p.ny + seg - 1) / seg); };
-  if (tiles(16) <= resident || tiles(16) >= 2 * resident) return 16;
+  if (tiles(16) >= 2 * resident) return 16;
+  if (tiles(16) <= resident) {
+    const long round = p.precision == DUGKS_F32 && !fix ? resident / 2 : resident;
+    for (int seg = 8; seg < 16; seg += fix ? MASS_GROUP : 1)
+      if (tiles(seg) <= round) return seg;
+    return 16;
+  }
   int seg = 24;
   while (tiles(seg) > resident) seg += MASS_GROUP;
   return seg;
@@ -276,26 +288,28 @@ int default_tile_rows(const dugks_params& p, int nstrips) {
 
 // Rows of the tile kernel's tiles, or 0 where the march runs: heights up to
 // TILE_MAX_ROWS ask for it, and by default grids too small to fill the chip
-// with marching wavefronts take it.  A marching wavefront needs ~35 us (FP64
-// upwind-3; 57 us central-4, 78 us upwind-5) for a 16-row tile however few
-// there are, the tile kernel 6.4 us (7.0, 9.4) for a grid of up to 256 tiles,
-// but it forms the cell terms of 12 rows for every 8 (8 for every 4).  The line
-// lies at the number of 16-row marching tiles where the two meet, measured on
-// square grids (us per step, tile / march): FP64 upwind-3 1024^2 53 / 54.5,
-// 1280^2 ~90 / 74; central-4 1024^2 67 / 77, 1280^2 108 / 110; velocity arrays
-// 1024^2 55 / 63; T3S3 768^2 89 / 95, 1024^2 147 / 137; upwind-5 1024^2 102 /
-// 124, 1280^2 170 / 160; FP32 corrected 1024^2 43.4 / 46.8, 1280^2 63 / 52.
+// with marching wavefronts take it.  A marching wavefront needs ~25 us (FP64
+// upwind-3) for an 8-row tile however few there are, the tile kernel 6.4 us for
+// a grid of up to 256 tiles, but it forms the cell terms of 12 rows for every 8
+// (8 for every 4).  The line lies at the number of 16-row marching tiles where
+// the two meet, measured on square grids (us per step, tile / march): FP64
+// upwind-3 768^2 33.0 / 35.2, 896^2 43.0 / 40.2; central-4 768^2 43.3 / 45.8,
+// 896^2 56.0 / 54.5; velocity arrays 768^2 34.5 / 38.4, 896^2 45.2 / 43.7; T3S3
+// 640^2 66.3 / 60.9; upwind-5 1024^2 102 / 124, 1280^2 170 / 160;
+// FP32 corrected 768^2 29.0 / 30.8, 896^2 34.9 / 32.3, central-4 896^2 37.6 / 37.6.
+// Where the march's default is 8 rows too, asking for 8 gives the default.
 int tile_kernel_rows(const dugks_params& p, int nstrips) {
   if (p.tile_rows > TILE_MAX_ROWS) return 0;
-  if (p.tile_rows == 0) {
-    const bool slow_march = p.recon == DUGKS_CENTRAL4 || p.recon == DUGKS_UPWIND5;
-    const long limit = p.precision == DUGKS_F32 ? (p.recon == DUGKS_UPWIND5 ? 1000 : 1250)
-                       : slow_march             ? 1650
-                       : p.scheme == DUGKS_T3S3 ? 800
-                       : p.vel_kind == DUGKS_VEL_ARRAYS ? 1450
-                                                        : 1150;
-    if ((long)nstrips * ((p.ny + 15) / 16) > limit) return 0;
-  }
+  const long n16 = (long)nstrips * ((p.ny + 15) / 16);
+  const long limit = p.recon == DUGKS_UPWIND5    ? (p.precision == DUGKS_F32 ? 1000 : 1650)
+                     : p.recon == DUGKS_CENTRAL4 ? (p.precision == DUGKS_F32 ? 900 : 840)
+                     : p.precision == DUGKS_F32  ? 760
+                     : p.scheme == DUGKS_T3S3    ? 400
+                     : p.vel_kind == DUGKS_VEL_ARRAYS ? 840
+                                                      : 760;
+  const bool small = n16 <= limit;
+  if (p.tile_rows == 0 && !small) return 0;
+  if (p.tile_rows == 8 && !small && default_tile_rows(p, nstrips) == 8) return 0;
   return block_tile_rows(p.precision == DUGKS_F64 ? 8 : 4, p.recon, p.scheme,
                          (p.flags & DUGKS_FLAG_MASS_FIX) != 0,
                          (int64_t)nstrips * ((p.ny + 3) / 4));

@@ -335,7 +335,9 @@ int batch_launch(dugks_batch* B, hipStream_t s, bool finish, int blocks) {
 
 // The kind and height of the tiles, where the caller has given none: as for
 // one grid (see default_tile_rows and tile_kernel_rows in dugks_abi.hip), by
-// the number of 16-row marching tiles of all grids together.  A batch too small
+// the number of 16-row marching tiles of all grids together; 8 rows where those
+// still make one round (24 of a mix of FP32 grids: 45.5 us a step against 52.3
+// at 16).  A batch too small
 // to fill the chip is bound by one tile's latency: us per step with 64-row
 // marching tiles / now, FP32 corrected: one 64^2 grid 164 / 12.5, eight 128^2
 // 176 / 16.6, 16 grids of sides 32-512 178 / 39; 64 of them 175 / 76, 256 239 /
@@ -355,7 +357,7 @@ void choose_tiles(dugks_batch* B) {
                                     B->mfix, count(4))
                   : 0;
   if (!B->given) {
-    B->rows = 16;
+    B->rows = count(8) <= B->grid_blocks ? 8 : 16;
     if (n16 > B->grid_blocks && n16 < 2 * (int64_t)B->grid_blocks)
       while (B->rows < 256 && count(B->rows) > B->grid_blocks) B->rows += MASS_GROUP;
   }

@@ -32,14 +32,16 @@ int launch_batch(const BatchDev& D, int precision, int recon, bool mfix, int sch
                  hipStream_t s, bool finish);
 
 // The most 16-row marching tiles (of all grids together) for which the block
-// tiles are taken: where the two meet, measured on the first grids of a mix of
-// sides 32-512 (us per step, block / 16-row marching tiles): FP32 corrected
-// upwind-3 1305 tiles 52 / 56, 1538 60 / 57, central-4 1800 73 / 76, T3S3 1305
-// 105 / 112; FP64 upwind-3 1305 64 / 66, 1538 75 / 70, central-4 1305 83 / 87,
-// T3S3 841 111 / 111.
+// tiles are taken: where they meet the marching tiles of the batch's choice (8
+// or 16 rows), measured on the first grids of a mix of sides 32-512 (us per
+// step, block / marching tiles): FP32 corrected upwind-3 841 tiles 37.9 / 38.4,
+// 1143 45.6 / 44.4, T3S3 841 73.8 / 73.9, central-4 1305 53.7 / 54.9, 1538 61.0 /
+// 58.5; FP64 upwind-3 1305 63.0 / 65.6, 1538 74.2 / 70.1, central-4 1305 82.2 /
+// 86.3, 1538 93.7 / 87.8, T3S3 463 68.2 / 71.7, 841 111 / 101.
 inline int64_t batch_tile_limit(int precision, int recon, int scheme) {
-  if (precision == DUGKS_F32) return recon == DUGKS_CENTRAL4 ? 1800 : 1400;
-  return recon == DUGKS_CENTRAL4 ? 1400 : (scheme == DUGKS_T3S3 ? 850 : 1350);
+  if (recon == DUGKS_CENTRAL4) return precision == DUGKS_F32 ? 1350 : 1400;
+  if (precision == DUGKS_F32) return 900;
+  return scheme == DUGKS_T3S3 ? 600 : 1350;
 }
 
 // The step kernels of launch_batch for a list of block tiles.
