@@ -253,37 +253,42 @@ int whole_round_rows(const dugks_params& p, int nstrips) {
   return best;
 }
 
-// Default rows per marching wavefront.
-// Grids of two rounds of 16-row tiles and more: 16.  Although its halo rows cost
-// a fifth of the arithmetic, the wavefronts of neighbouring strips stay in step,
-// so the lines they share are still cached, and the last round is short.  us
-// per step at 16 / 72-128 rows (whole rounds): 4096^2 FP64 upwind-3 602 / 692,
-// FP32 corrected 367 / 469, velocity arrays 715 / 821, T3S3 1779 / 2006; 2900^2
-// FP64 309 / 325, FP32 corrected 194 / 244.
-// Smaller ones: the shortest height of one round (at least 8 rows), since a
-// step then takes one tile's time.  us per step at it / at 16: FP64 upwind-3
-// 1024^2 51.7 (10 rows) / 54.9, 1536^2 97 (24) / 105; central-4 1280^2 110 (24)
-// / 136; T3S3 896^2 96.6 (8) / 105.9; FP32 corrected 1024^2 38.0 (8) / 45.8, T3S3
-// 2048^2 277 (32) / 288.  FP32 without the correction runs 4 wavefronts per SIMD
-// and is bound by VALU long before they are all there: a round of half of them
-// (1280^2 50.2 at 8 rows, 45.6 at 16).
+// Default rows per marching wavefront: the height with the least estimated time.
+// An XCD takes a band of whole segments (or of tiles, see step_args), so with t
+// tiles in the largest band and c wavefronts resident on an XCD it works
+// n = t / c rounds.  A full round takes seg + 5 rows' time, a part f of one
+// 0.5 + 0.5 f of that (few wavefronts run faster, to half the time), and a row
+// costs 0.6 % more for every row of height beyond 16 (the wavefronts of
+// neighbouring strips fall out of step, and lines they share leave the caches).
+// FP32 without the correction has 4 wavefronts per SIMD but is bound by VALU from
+// 2 on.  The estimate orders the heights as measured within 3-5 %; us per step at
+// its choice / at the lowest multiple of 8 that makes whole rounds of the chip:
+// FP64 upwind-3 1024^2 51.7 (10 rows) / 54.9, 1400^2 83 (18) / 92, 1900^2 139
+// (16) / 187 (32 rows: 8 segments in some bands, and a second round there),
+// 4096^2 602 (16) / 692 (72); central-4 1900^2 203 (14) / 216; FP32 corrected
+// 2000^2 105 (32) / 125 (24), 4096^2 358 (32) / 469 (96); T3S3 1900^2 400 / 509.
 // Upwind-5, one wavefront per SIMD in FP64, keeps whole rounds (2048^2 377
 // against 432 at 16).
 int default_tile_rows(const dugks_params& p, int nstrips) {
   if (p.recon == DUGKS_UPWIND5) return whole_round_rows(p, nstrips);
   const bool fix = (p.flags & DUGKS_FLAG_MASS_FIX) != 0;
-  const long resident = resident_wavefronts(p);
-  auto tiles = [&](int seg) { return (long)nstrips * ((p.ny + seg - 1) / seg); };
-  if (tiles(16) >= 2 * resident) return 16;
-  if (tiles(16) <= resident) {
-    const long round = p.precision == DUGKS_F32 && !fix ? resident / 2 : resident;
-    for (int seg = 8; seg < 16; seg += fix ? MASS_GROUP : 1)
-      if (tiles(seg) <= round) return seg;
-    return 16;
-  }
-  int seg = 24;
-  while (tiles(seg) > resident) seg += MASS_GROUP;
-  return seg;
+  long resident = resident_wavefronts(p);
+  if (p.precision == DUGKS_F32 && !fix) resident = std::min(resident, 2048L);
+  const double c = resident / 8.0;
+  auto cost = [&](int seg) {
+    const int nsegs = (p.ny + seg - 1) / seg;
+    const double t = segment_bands(nsegs, p.recon) ? (double)((nsegs + 7) / 8) * nstrips
+                                                   : (double)(((long)nstrips * nsegs + 7) / 8);
+    const double n = t / c, whole = floor(n), f = n - whole;
+    return (whole + (f > 0.0 ? 0.5 + 0.5 * f : 0.0)) * (seg + 5) * (1.0 + 0.006 * (seg - 16));
+  };
+  // every height where there are few rounds, else the multiples of 8 from 16 on
+  const long tiles16 = (long)nstrips * ((p.ny + 15) / 16);
+  const bool few = tiles16 < 4 * resident;
+  int best = 16;
+  for (int seg = few ? 8 : 16; seg <= 40; seg += few && !fix ? 1 : MASS_GROUP)
+    if (cost(seg) < cost(best)) best = seg;
+  return best;
 }
 
 // Rows of the tile kernel's tiles, or 0 where the march runs: heights up to

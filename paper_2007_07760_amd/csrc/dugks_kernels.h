@@ -562,12 +562,13 @@ struct Marcher {
       // LDS latency
       __builtin_amdgcn_sched_barrier(0);
     }
-    T PN, QNx, QNy, eP, eQx, eQy;
-    north_moments(kk, phN, sxp[0], syp[0], sxp[1], syp[1], PN, QNx, QNy);
+    T PN, QNx, QNy, eP, eQx, eQy, uk, vk;
+    uv_row(kk, uk, vk);
+    north_moments(kk, uk, vk, phN, sxp[0], syp[0], sxp[1], syp[1], PN, QNx, QNy);
     const T dP = PN - PS, dQx = QNx - QSx, dQy = QNy - QSy;
     PS = PN; QSx = QNx; QSy = QNy;
     if (!upd) return;
-    east_moments(kk, phE, sxp[0], syp[0], eP, eQx, eQy);
+    east_moments(kk, uk, vk, phE, sxp[0], syp[0], eP, eQx, eQy);
     double cs = 0.0, cf0 = 0.0;
     T bp[9];
 #pragma unroll
@@ -616,9 +617,15 @@ struct Marcher {
     qv[9] = bload(rin, oq + 9 * (unsigned)(OWN * sizeof(T)), T(0));
   }
 
-  // collision part of the north faces of (wrapped) row kk: phN = dt*alpha*phi_b
-  // there, (sx0, sy0) and (sx1, sy1) s of the rows kk and kk + 1
-  __device__ __forceinline__ void north_moments(int kk, T phN, T sx0, T sy0, T sx1, T sy1, T& PN,
+  // VARR: the velocity at the cells of (wrapped) row kk
+  __device__ __forceinline__ void uv_row(int kk, T& uk, T& vk) const {
+    uk = VARR ? uv_at(0, kk) : T(0);
+    vk = VARR ? uv_at(1, kk) : T(0);
+  }
+
+  // collision part of the north faces of (wrapped) row kk: (uk, vk) from uv_row,
+  // phN = dt*alpha*phi_b there, (sx0, sy0) and (sx1, sy1) s of rows kk and kk + 1
+  __device__ __forceinline__ void north_moments(int kk, T uk, T vk, T phN, T sx0, T sy0, T sx1, T sy1, T& PN,
                                                 T& QNx, T& QNy) const {
     const cptr<T> UY = taby;
     const cptr<T> VY = taby + (2 * a.ny + 2);
@@ -627,8 +634,8 @@ struct Marcher {
     T ubN, vbN;
     if (VARR) {
       const int k1 = wrapi(kk + 1, a.ny);
-      ubN = T(0.5) * (uv_at(0, kk) + uv_at(0, k1));
-      vbN = T(0.5) * (uv_at(1, kk) + uv_at(1, k1));
+      ubN = T(0.5) * (uk + uv_at(0, k1));
+      vbN = T(0.5) * (vk + uv_at(1, k1));
     } else {
       ubN = gH * (UXc * UY[2 * kk + 2]);
       vbN = gH * (VXc * VY[2 * kk + 2]);
@@ -642,15 +649,10 @@ struct Marcher {
 
   // collision part of the east faces of (wrapped) row kk, less that of the
   // west faces: phE = dt*alpha*phi_b of the east faces, (sx0, sy0) s of the row
-  __device__ __forceinline__ void east_moments(int kk, T phE, T sx0, T sy0, T& eP, T& eQx,
+  __device__ __forceinline__ void east_moments(int kk, T uk, T vk, T phE, T sx0, T sy0, T& eP, T& eQx,
                                                T& eQy) const {
     const cptr<T> UY = taby;
     const cptr<T> VY = taby + (2 * a.ny + 2);
-    T uk = T(0), vk = T(0);
-    if (VARR) {
-      uk = uv_at(0, kk);
-      vk = uv_at(1, kk);
-    }
     // east face (x + 1, y + 1/2): S_b = mean of own and east cell
     const T ubE = VARR ? T(0.5) * (uk + from_right(uk)) : gH * (UXe * UY[2 * kk + 1]);
     const T vbE = VARR ? T(0.5) * (vk + from_right(vk)) : gH * (VXe * VY[2 * kk + 1]);

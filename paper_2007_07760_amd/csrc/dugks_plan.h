@@ -121,6 +121,11 @@ inline StageBufs<T> stage_bufs(const dugks_plan* P, void* state, int64_t n, int 
 template <typename T, int STAGE>
 void launch_tile(const dugks_plan* P, const StageBufs<T>& q, int64_t n, hipStream_t s);
 
+// Whether an XCD's band of the march is whole segments, its two halves in turn:
+// once it holds 4 segments or more (not for the wide patch: one wavefront per
+// SIMD, and it measured slower).
+inline bool segment_bands(int nsegs, int recon) { return nsegs >= 32 && !wide(recon); }
+
 template <typename T>
 inline StepArgs<T> step_args(const dugks_plan* P, int stage = STAGE_T2) {
   const Layout& L = P->L;
@@ -132,9 +137,7 @@ inline StepArgs<T> step_args(const dugks_plan* P, int stage = STAGE_T2) {
   a.nstrips = P->nstrips;
   a.nsegs = P->nsegs;
   a.nlogical = P->nstrips * P->nsegs;
-  // interleave two chunks of each XCD's band once it holds 4 segments or more
-  // (not for the wide patch: one wavefront per SIMD, and it measured slower)
-  a.ileave = P->nsegs >= 32 && !wide(P->p.recon) ? 2 : 1;
+  a.ileave = segment_bands(P->nsegs, P->p.recon) ? 2 : 1;
   a.clen = ((P->nsegs + 7) / 8 + a.ileave - 1) / a.ileave;
   a.ngroups = L.ngroups;
   const dugks_plan::StageCoef& c = P->st[stage];

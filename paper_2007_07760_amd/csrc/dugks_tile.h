@@ -201,7 +201,9 @@ __device__ __forceinline__ void tile_step(Args& a, int64_t n,
     // FP64: read again here, not held across the faces (6 wavefronts per SIMD)
     const T sx = LEAN ? u.s[w][0][lane] : m.sxp[LAG], sy = LEAN ? u.s[w][1][lane] : m.syp[LAG];
     if (LEAN) m.flow_east();
-    m.north_moments(kk, phN, sx, sy, u.s[w + 1][0][lane], u.s[w + 1][1][lane],
+    T uk, vk;
+    m.uv_row(kk, uk, vk);
+    m.north_moments(kk, uk, vk, phN, sx, sy, u.s[w + 1][0][lane], u.s[w + 1][1][lane],
                     PN, QNx, QNy);
     if (!SPARE) {
 #pragma unroll
@@ -216,7 +218,7 @@ __device__ __forceinline__ void tile_step(Args& a, int64_t n,
       u.bfp[v][1][lane] = QNx;
       u.bfp[v][5][lane] = QNy;
     }
-    if (upd) m.east_moments(kk, phE, sx, sy, eP, eQx, eQy);
+    if (upd) m.east_moments(kk, uk, vk, phE, sx, sy, eP, eQx, eQy);
   }
   __syncthreads();
   if (upd) {
