@@ -134,6 +134,20 @@ __device__ __forceinline__ void tile_step(Args& a, int64_t n,
   const int k = r;                                  // its face row
   const bool upd = k >= m.y0 && k < m.y1;
   RowRegs<T> d, o;
+  // touch the stencil table's scalar-cache lines (64 bytes) and the row's
+  // velocity factors now: the cache is cold at every launch, and their first
+  // misses would otherwise come one by one in the face stage
+  constexpr int LINES = (4 * cclass(R) * (int)sizeof(T) + 63) / 64;
+  T warm[LINES + 2];
+#pragma unroll
+  for (int j = 0; j < LINES; j++) warm[j] = m.cf[j * (64 / (int)sizeof(T))];
+  if (!VARR) {
+    warm[LINES] = m.taby[2 * wrapi(min(r, top), a.ny) + 1];
+    warm[LINES + 1] = m.taby[(2 * a.ny + 2) + 2 * wrapi(min(r, top), a.ny) + 1];
+  } else {
+    warm[LINES] = warm[LINES + 1] = T(0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
   m.load_raw(d, min(r, top + 1));
   const bool outer = w == 0 || w == CR - 1;
   if (outer) m.load_raw(o, w == 0 ? m.y0 - LAG - 1 : min(r + 1, top + 1));
@@ -163,6 +177,8 @@ __device__ __forceinline__ void tile_step(Args& a, int64_t n,
     u.da[w == 0 ? 0 : CR + 1][1][lane] = Ao;
   }
   __syncthreads();
+#pragma unroll
+  for (int j = 0; j < LINES + 2; j++) asm volatile("" ::"s"(warm[j]));
   if (cells) {
     m.D0 = u.da[w][0][lane];
     m.A0 = u.da[w][1][lane];
@@ -273,10 +289,11 @@ tile_kernel(StepArgs<T> a, int64_t n, const T* __restrict__ src, T* __restrict__
             double* __restrict__ part, const double* __restrict__ prev,
             StateHeader* __restrict__ hdr) {
   __shared__ TileShared<T, R, MFIX, TR> u;
-  // bands of tiles per XCD, as in step_kernel
-  const int per = (a.nlogical + 7) >> 3;
-  const int logical = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-  if (logical >= a.nlogical) return;
+  // bands of tiles per XCD, as in step_kernel, cut so that the launch has exactly
+  // a block per tile: without an exit on the way, all arguments are fetched at
+  // once (each fetch that waits for another costs a cold scalar-cache miss)
+  const int x = blockIdx.x & 7;
+  const int logical = x * (a.nlogical >> 3) + min(x, a.nlogical & 7) + (int)(blockIdx.x >> 3);
   const StepArgs<T>& args = a;
   tile_step<T, R, MFIX, STAGE, VARR, TR>(args, n, src, dst, dst2, aux, cf, tabx, taby, uv, part,
                                          MFIX ? hdr->pending : 0.0, MFIX ? hdr->fit_max : 0.0,

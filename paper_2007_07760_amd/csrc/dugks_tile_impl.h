@@ -9,8 +9,7 @@ namespace dugks {
 
 template <typename T, int R, bool MFIX, int STAGE, bool VARR, int TR>
 static void tile_go(const StepArgs<T>& a, const StageBufs<T>& q, int64_t n, hipStream_t s) {
-  const int per = (a.nlogical + 7) / 8;   // tiles per XCD (see the kernel's order)
-  hipLaunchKernelGGL((tile_kernel<T, R, MFIX, STAGE, VARR, TR>), dim3(per * 8),
+  hipLaunchKernelGGL((tile_kernel<T, R, MFIX, STAGE, VARR, TR>), dim3(a.nlogical),
                      dim3(LANES * tile_cell_rows(R, TR)), 0, s, a, n, q.src, q.dst, q.dst2, q.aux,
                      q.cf, q.tabx, q.taby, q.uv, q.part, q.prev, q.hdr);
 }
