@@ -300,13 +300,13 @@ int default_tile_rows(const dugks_params& p, int nstrips) {
 // the two meet, measured on square grids (us per step, tile / march): FP64
 // upwind-3 768^2 33.0 / 35.2, 896^2 43.0 / 40.2; central-4 768^2 43.3 / 45.8,
 // 896^2 56.0 / 54.5; velocity arrays 768^2 34.5 / 38.4, 896^2 45.2 / 43.7; T3S3
-// 640^2 66.3 / 60.9; upwind-5 1024^2 102 / 124, 1280^2 170 / 160;
+// 640^2 66.3 / 60.9; upwind-5 1024^2 100 / 124, 1280^2 149 / 160;
 // FP32 corrected 768^2 29.0 / 30.8, 896^2 34.9 / 32.3, central-4 896^2 37.6 / 37.6.
 // Where the march's default is 8 rows too, asking for 8 gives the default.
 int tile_kernel_rows(const dugks_params& p, int nstrips) {
   if (p.tile_rows > TILE_MAX_ROWS) return 0;
   const long n16 = (long)nstrips * ((p.ny + 15) / 16);
-  const long limit = p.recon == DUGKS_UPWIND5    ? (p.precision == DUGKS_F32 ? 1000 : 1650)
+  const long limit = p.recon == DUGKS_UPWIND5    ? (p.precision == DUGKS_F32 ? 1000 : 1850)
                      : p.recon == DUGKS_CENTRAL4 ? (p.precision == DUGKS_F32 ? 900 : 840)
                      : p.precision == DUGKS_F32  ? 760
                      : p.scheme == DUGKS_T3S3    ? 400
@@ -315,9 +315,19 @@ int tile_kernel_rows(const dugks_params& p, int nstrips) {
   const bool small = n16 <= limit;
   if (p.tile_rows == 0 && !small) return 0;
   if (p.tile_rows == 8 && !small && default_tile_rows(p, nstrips) == 8) return 0;
-  return block_tile_rows(p.precision == DUGKS_F64 ? 8 : 4, p.recon, p.scheme,
-                         (p.flags & DUGKS_FLAG_MASS_FIX) != 0,
-                         (int64_t)nstrips * ((p.ny + 3) / 4));
+  const bool mfix = (p.flags & DUGKS_FLAG_MASS_FIX) != 0;
+  const int rows = block_tile_rows(p.precision == DUGKS_F64 ? 8 : 4, p.recon, p.scheme, mfix,
+                                   (int64_t)nstrips * ((p.ny + 3) / 4));
+  if (!wide(p.recon) || mfix || rows != 8) return rows;
+  // An upwind-5 block of 8 rows is 14 wavefronts and has a compute unit for
+  // itself, so a step takes whole rounds of 256 blocks (~11 us each in FP64, ~7.5
+  // in FP32, also for a last round of a few).  10 rows, 16 wavefronts, take ~12.5
+  // (8.5) but may take fewer rounds: 512^2 FP64 3 rounds 32.6 us, 2 of 10 rows
+  // 26.4 (FP32 22.2, 17.0); 832^2 7 rounds 76.1, 5 64.1; 384^2 2 rounds either
+  // way, 21.7 and 23.8; 1024^2 9 and 8, 101.5 and 99.9.
+  const int r8 = (nstrips * ((p.ny + 7) / 8) + 255) / 256;
+  const int r10 = (nstrips * ((p.ny + 9) / 10) + 255) / 256;
+  return 10 * r10 < 9 * r8 ? 10 : 8;
 }
 
 // ------------------------------------------------------------ launches

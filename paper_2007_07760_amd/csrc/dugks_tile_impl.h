@@ -21,6 +21,12 @@ static void tile_rows_go(const dugks_plan* P, const StepArgs<T>& a, const StageB
     tile_go<T, R, true, STAGE, VARR, MASS_GROUP>(a, q, n, s);
     return;
   }
+  if constexpr (wide(R)) {
+    if (P->tile == 10) {
+      tile_go<T, R, false, STAGE, VARR, 10>(a, q, n, s);
+      return;
+    }
+  }
   if constexpr (tall_tiles(sizeof(T), R, STAGE == STAGE_T2 ? DUGKS_T2 : DUGKS_T3S3)) {
     if (P->tile == 8) {
       tile_go<T, R, false, STAGE, VARR, 8>(a, q, n, s);

@@ -81,3 +81,27 @@ def test_correction_formed_in_the_step(nx, ny, scheme):
                 assert torch.equal(s.history(), one.history())
                 assert s.mass() == one.mass()
         assert (one.status() != 0) == bad
+
+
+# upwind-5 grids of three rounds of 8-row blocks and two of 10-row ones: the rule
+# takes 10; heights that leave a last tile of 1, 5, 9 and 10 rows
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("nx,ny", [(9, 4101), (59, 2055), (130, 1389), (130, 1380)])
+def test_ten_row_tiles_equal_march_bitwise(precision, nx, ny):
+    import torch
+    from paper_2007_07760_amd.solver import Solver
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    print(f"case {nx}x{ny} prec={precision}", flush=True)
+    phi0 = I.random_circles(nx, ny, 3, 0.2 * nx, 0.4 * nx, 4.0, seed=ny)
+
+    def state(rows):
+        return Solver(nx, ny, 0.02, 4.0, 0.5, recon=3, precision=precision, vel_kind=2,
+                      vel_param=(0.05, 90.0), tile_rows=rows).init(phi0).step(5)
+
+    march = state(16)
+    for rows in (8, 0):
+        s = state(rows)
+        assert torch.equal(s.distributions(), march.distributions()), rows
+        assert torch.equal(s.history(), march.history()), rows
+        assert s.mass() == march.mass() and s.status() == march.status()
