@@ -294,7 +294,7 @@ int default_tile_rows(const dugks_params& p, int nstrips) {
 // Rows of the tile kernel's tiles, or 0 where the march runs: heights up to
 // TILE_MAX_ROWS ask for it, and by default grids too small to fill the chip
 // with marching wavefronts take it.  A marching wavefront needs ~25 us (FP64
-// upwind-3) for an 8-row tile however few there are, the tile kernel 6.4 us for
+// upwind-3) for an 8-row tile however few there are, the tile kernel 6.0 us for
 // a grid of up to 256 tiles, but it forms the cell terms of 12 rows for every 8
 // (8 for every 4).  The line lies at the number of 16-row marching tiles where
 // the two meet, measured on square grids (us per step, tile / march): FP64

@@ -152,10 +152,13 @@ __host__ __device__ constexpr int tile_waves(int esize, int recon, int TR, bool 
 // 14) where twice four form 16 (20), so they take less arithmetic, but a block
 // takes longer and there are half as many: 4 while that leaves compute units
 // idle (FP64 upwind-3 64^2 6.4 us against 8.0; upwind-5 9.4 / 11.8), then 8
-// (768^2 33.0 / 38.0, arrays 33.6 / 37.1; upwind-5 256^2 12.2 / 16.7).  The
+// (768^2 33.0 / 38.0, arrays 33.6 / 37.1; upwind-5 256^2 11.9 / 16.7).  The
 // forms whose 8-row blocks do not fit a compute unit twice keep 4 (FP64
 // central-4 512^2 20.9 / 25.8, T3S3 45.0 / 51.4), and so does FP32, which gains
-// nothing (upwind-3 512^2 10.7 / 12.1).
+// nothing (upwind-3 512^2 10.7 / 12.1).  Upwind-5 may take 10 (see
+// tile_kernel_rows).  Blocks of 10 or 14 wavefronts do not pack two to a compute
+// unit, so heights between lose: central-4 512^2 28.0 with 6 rows at 5
+// wavefronts per SIMD, arrays 20.7 with 10 at 7 (18.6 with 8).
 __host__ __device__ constexpr bool tall_tiles(int esize, int recon, int scheme) {
   return wide(recon) || (esize == 8 && scheme == DUGKS_T2 && recon != DUGKS_CENTRAL4);
 }

@@ -7,12 +7,18 @@
 // side: wavefront w of a block forms phi, the cell terms and fbar+ of cell row
 // y0 - LAG + w, then the faces of that row and its update, with four block
 // barriers between (differences of phi; fbar+ rows; faces; the faces' values
-// below each row).  What bounds it is that chain of latencies: 5.8-6.6 us per
-// step for grids of up to 256 tiles (64^2 FP64: 36 us with the march, 6.4 now;
-// 256^2 8.5; FP32 corrected 256^2 with its reduction 37.7, 9.2; upwind-5 64^2
-// 79, 8.8).  On larger grids it is bound by VALU (a third of it lane shifts):
-// TR rows take the cell terms of TR + 4 (6), so the march wins from ~1050^2 on
-// (see tile_kernel_rows; 4 rows against 8: block_tile_rows).
+// below each row).  What bounds it is that chain of latencies: 5.2-6.7 us per
+// step for grids of up to 256 tiles (64^2 FP64: 36 us with the march, 6.0 now;
+// 256^2 8.6; FP32 corrected 256^2 with its reduction 37.7, 9.2; upwind-5 64^2
+// 79, 8.7): a wavefront issues for a quarter of its life there and waits for
+// loads, LDS and barriers for most of the rest.  On larger grids VALU (a third
+// of it lane shifts) is busy half the time, and TR rows take the cell terms of
+// TR + 4 (6), so the march wins from ~800^2 on, upwind-5 from ~1300^2 (see
+// tile_kernel_rows; the rows of a tile: block_tile_rows).
+//
+// Two stages in one launch (two T2 steps, or both of T3S3's) were slower: per
+// step 64^2 6.2 us against 6.0, 200^2 7.8 against 6.7, T3S3 200^2 15.8 against
+// 14.0.  A step waits for its own chain, not for the launch.
 //
 // The arithmetic is the march's, expression by expression, so the results are
 // bitwise the same.  The face values take their neighbour columns from lane
