@@ -55,19 +55,21 @@ __global__ __launch_bounds__(64) void noalloc_desc_kernel(DescChunk<T> c, unsign
   status[c.first + k] = DUGKS_OK;
 }
 
-// the work list: item i belongs to the grid j with start[j] <= i < start[j+1]
-// (grids by queue, then in decreasing order of tile height), tile
-// i - start[j]; queue q holds items [qstart[q], qstart[q+1]).  One thread
-// also writes the control block and rewinds the queue heads
-struct ItemStarts {
-  int32_t start[NOALLOC_GRIDS + 1];
-  int32_t grid[NOALLOC_GRIDS];
+// the work list, in pieces: item i of piece p (start[p] <= i < start[p + 1]) is
+// tile first[p] + i - start[p] of grid[p]; queue q holds items [qstart[q],
+// qstart[q + 1]).  A grid is one piece, or one per queue it reaches into.  One
+// thread also writes the control block and rewinds the queue heads
+constexpr int NOALLOC_PIECES = NOALLOC_GRIDS + NQUEUE - 1;
+struct ItemPieces {
   int32_t qstart[NQUEUE + 1];
-  int n, nq;
+  int32_t n;
+  int32_t start[NOALLOC_PIECES + 1];
+  int32_t grid[NOALLOC_PIECES];
+  int32_t first[NOALLOC_PIECES];
 };
-static_assert(sizeof(ItemStarts) <= 4096, "kernel argument size");
+static_assert(sizeof(ItemPieces) <= 4096, "kernel argument size");
 
-static __global__ __launch_bounds__(256) void noalloc_items_kernel(ItemStarts a,
+static __global__ __launch_bounds__(256) void noalloc_items_kernel(ItemPieces a,
                                                                    unsigned char* base) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int nitems = a.start[a.n];
@@ -76,18 +78,103 @@ static __global__ __launch_bounds__(256) void noalloc_items_kernel(ItemStarts a,
     BatchCtl* ctl = reinterpret_cast<BatchCtl*>(base + NA_CTL);
     ctl->items = items;
     ctl->nitems = nitems;
-    ctl->nq = a.nq;
+    ctl->nq = NQUEUE;
     for (int q = 0; q <= NQUEUE; q++) ctl->qstart[q] = a.qstart[q];
     unsigned* head = reinterpret_cast<unsigned*>(base + NA_HEAD);
     for (int q = 0; q < NQUEUE; q++) head[q * HEAD_STRIDE] = head[q * HEAD_STRIDE + 1] = 0u;
   }
   if (i >= nitems) return;
-  int lo = 0, hi = a.n - 1;   // last j with start[j] <= i
+  int lo = 0, hi = a.n - 1;   // last p with start[p] <= i
   while (lo < hi) {
     const int mid = (lo + hi + 1) / 2;
     if (a.start[mid] <= i) lo = mid; else hi = mid - 1;
   }
-  items[i] = BatchItem{a.grid[lo], (int32_t)(i - a.start[lo])};
+  items[i] = BatchItem{a.grid[lo], (int32_t)(a.first[lo] + i - a.start[lo])};
+}
+
+struct GridTiles {
+  int j, cost;       // the grid, the cost of a tile
+  int64_t tiles;
+};
+
+// Grids (the largest first) whole to the least loaded queue each, if no queue gets
+// more blocks than an XCD has compute units: the tiles' shared rows and columns
+// stay in one L2, and every block runs at once (see make_pieces).
+bool whole_grids(const GridTiles* g, int n, int* queue_of) {
+  int64_t load[NQUEUE] = {};
+  for (int k = 0; k < n; k++) {
+    const int q = (int)(std::min_element(load, load + NQUEUE) - load);
+    queue_of[k] = q;
+    if ((load[q] += g[k].tiles) > 32) return false;
+  }
+  return true;
+}
+
+// The work list of n grids in block tiles of `tile` rows, or (0) in marching
+// tiles of each plan's many_rows.  The grids' tiles, those of the most marched
+// rows first and each grid's segment by segment, are laid end to end and cut at
+// NQUEUE equal shares (of tiles, or of marched rows), so that every XCD has the
+// same work, however few or uneven the grids: a block of the tile kernel takes
+// tiles of its XCD's queue only, and a marching wavefront tries one other.  Within
+// a queue the taller tiles come first, so that the short ones fill the tail.
+// us per step with every grid whole in one queue / now: one FP64 grid of 1000^2
+// 326 / 57, of 2048^2 410 / 181, one corrected FP32 grid of 512^2 71 / 20, 1024^2
+// with 63 of 32-512 136 / 112.  Grids whose blocks fit an XCD at once do stay
+// whole: one 33^2 grid 9.7 / 10.8 (FP64 8.3 / 9.0), four of 64^2 10.6 / 11.1.
+void make_pieces(const dugks_plan* const* plans, int n, int tile, ItemPieces* out) {
+  GridTiles g[NOALLOC_GRIDS];
+  int64_t total = 0;
+  for (int j = 0; j < n; j++) {
+    const dugks_plan* P = plans[j];
+    const int segs = tile ? (P->p.ny + tile - 1) / tile : P->many_segs;
+    g[j] = {j, tile ? 1 : P->many_rows + 5, (int64_t)P->nstrips * segs};
+    total += g[j].tiles * g[j].cost;
+  }
+  std::stable_sort(g, g + n, [](const GridTiles& a, const GridTiles& b) {
+    return a.tiles * a.cost > b.tiles * b.cost;
+  });
+  struct Piece {
+    int32_t grid, first, count, cost;
+  };
+  Piece p[NOALLOC_PIECES];
+  int np = 0, k = 0;
+  int64_t items = 0, done = 0, taken = 0;   // taken: tiles of g[k] so far
+  int queue_of[NOALLOC_GRIDS];
+  const bool whole = tile && whole_grids(g, n, queue_of);
+  for (int q = 0; q < NQUEUE; q++) {
+    const int from = np;
+    out->qstart[q] = (int32_t)items;
+    for (int j = 0; whole && j < n; j++)
+      if (queue_of[j] == q) {
+        p[np++] = {g[j].j, 0, (int32_t)g[j].tiles, g[j].cost};
+        items += g[j].tiles;
+      }
+    // up to the queue's share of the work (the last queue takes the rest)
+    const int64_t upto = total * (q + 1) / NQUEUE;
+    while (!whole && k < n) {
+      const int64_t left = g[k].tiles - taken;
+      const int64_t m = q == NQUEUE - 1 ? left : std::min(left, (upto - done) / g[k].cost);
+      if (m > 0) {
+        p[np++] = {g[k].j, (int32_t)taken, (int32_t)m, g[k].cost};
+        items += m;
+        done += m * g[k].cost;
+        taken += m;
+      }
+      if (m < left) break;
+      taken = 0;
+      k++;
+    }
+    std::stable_sort(p + from, p + np,
+                     [](const Piece& a, const Piece& b) { return a.cost > b.cost; });
+  }
+  out->qstart[NQUEUE] = (int32_t)items;
+  out->n = np;
+  out->start[0] = 0;
+  for (int i = 0; i < np; i++) {
+    out->grid[i] = p[i].grid;
+    out->first[i] = p[i].first;
+    out->start[i + 1] = out->start[i] + p[i].count;
+  }
 }
 
 }  // namespace
@@ -123,7 +210,7 @@ int scratch_of_current_device(unsigned char** out) {
 
 template <typename T>
 int noalloc_setup(const dugks_plan* const* plans, void* const* states, const int64_t* steps,
-                  int n, int64_t nsteps, int tile, const ItemStarts& starts,
+                  int n, int64_t nsteps, int tile, const ItemPieces& pieces,
                   unsigned char* base, hipStream_t s) {
   DescChunk<T> c;
   for (int first = 0; first < n; first += DESC_CHUNK) {
@@ -138,9 +225,9 @@ int noalloc_setup(const dugks_plan* const* plans, void* const* states, const int
     }
     hipLaunchKernelGGL((noalloc_desc_kernel<T>), dim3(1), dim3(64), 0, s, c, base);
   }
-  const int nitems = starts.start[n];
+  const int nitems = pieces.qstart[NQUEUE];
   hipLaunchKernelGGL(noalloc_items_kernel, dim3((unsigned)((nitems + 255) / 256)), dim3(256),
-                     0, s, starts, base);
+                     0, s, pieces, base);
   return hip_status(hipGetLastError());
 }
 
@@ -156,14 +243,6 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
   if (!p0) return DUGKS_EINVAL;
   const int precision = p0->p.precision, recon = p0->p.recon, scheme = p0->p.scheme;
   const bool mfix = (p0->p.flags & DUGKS_FLAG_MASS_FIX) != 0;
-  // tiles per grid (each grid at its plan's own segment height); each grid
-  // whole to one of the NQUEUE queues (one per XCD), the largest first to
-  // the least loaded; within a queue the grids in decreasing order of tile
-  // height, so that the short tiles fill the tail
-  ItemStarts starts;
-  memset(&starts, 0, sizeof(starts));
-  starts.n = n;
-  int order[NOALLOC_GRIDS];
   for (int j = 0; j < n; j++) {
     const dugks_plan* P = plans[j];
     if (!P || !states[j] || !aligned(states[j]) || steps[j] < 0) return DUGKS_EINVAL;
@@ -172,7 +251,6 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
       return DUGKS_EINVAL;
     if (P->p.vel_kind == DUGKS_VEL_ARRAYS || P->p.recon == DUGKS_UPWIND5)
       return DUGKS_EUNSUPPORTED;
-    order[j] = j;
   }
   // block tiles where the grids together are too few to fill the chip with
   // marching wavefronts (as a batch chooses them), else each plan's own height
@@ -184,41 +262,12 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
   const int tile = n16 <= batch_tile_limit(precision, recon, scheme)
                        ? block_tile_rows(precision == DUGKS_F64 ? 8 : 4, recon, scheme, mfix, n4)
                        : 0;
-  auto segs = [tile](const dugks_plan* P) {
-    return tile ? (P->p.ny + tile - 1) / tile : P->many_segs;
-  };
-  // rows a grid's tiles march in all
-  auto work = [plans, &segs](int j) {
-    const dugks_plan* P = plans[j];
-    return (int64_t)P->nstrips * ((int64_t)P->p.ny + 5 * (int64_t)segs(P));
-  };
-  std::stable_sort(order, order + n, [&](int a, int b) { return work(a) > work(b); });
-  int queue_of[NOALLOC_GRIDS];
-  int64_t load[NQUEUE] = {};
-  for (int k = 0; k < n; k++) {
-    int q = 0;
-    for (int r = 1; r < NQUEUE; r++)
-      if (load[r] < load[q]) q = r;
-    queue_of[order[k]] = q;
-    load[q] += work(order[k]);
-  }
-  std::stable_sort(order, order + n, [&](int a, int b) {
-    if (queue_of[a] != queue_of[b]) return queue_of[a] < queue_of[b];
-    return plans[a]->many_rows > plans[b]->many_rows;
-  });
-  starts.nq = NQUEUE;
   int64_t total = 0;
-  int q = 0;
-  for (int k = 0; k < n; k++) {
-    const dugks_plan* P = plans[order[k]];
-    while (q <= queue_of[order[k]]) starts.qstart[q++] = (int32_t)total;
-    starts.start[k] = (int32_t)total;
-    starts.grid[k] = order[k];
-    total += (int64_t)P->nstrips * segs(P);
+  for (int j = 0; j < n; j++) {
+    const dugks_plan* P = plans[j];
+    total += (int64_t)P->nstrips * (tile ? (P->p.ny + tile - 1) / tile : P->many_segs);
     if (total > NOALLOC_ITEMS) return DUGKS_EINVAL;   // beyond the array's work list
   }
-  while (q <= NQUEUE) starts.qstart[q++] = (int32_t)total;
-  starts.start[n] = (int32_t)total;
   if (nsteps == 0) return DUGKS_OK;
   unsigned char* base = nullptr;
   int rc = scratch_of_current_device(&base);
@@ -229,13 +278,16 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
     return DUGKS_EDEVICE;
   if ((rc = batch_occupancy(precision, recon, mfix, scheme, &per_cu)) != DUGKS_OK) return rc;
   if (per_cu < 1 || ncu < 1) return DUGKS_EDEVICE;
+  ItemPieces pieces;
+  memset(&pieces, 0, sizeof(pieces));
+  make_pieces(plans, n, tile, &pieces);
   int longest = 1;
   for (int k = 0; k < NQUEUE; k++)
-    longest = std::max(longest, starts.qstart[k + 1] - starts.qstart[k]);
+    longest = std::max(longest, pieces.qstart[k + 1] - pieces.qstart[k]);
   hipStream_t s = static_cast<hipStream_t>(stream);
   rc = precision == DUGKS_F64
-           ? noalloc_setup<double>(plans, states, steps, n, nsteps, tile, starts, base, s)
-           : noalloc_setup<float>(plans, states, steps, n, nsteps, tile, starts, base, s);
+           ? noalloc_setup<double>(plans, states, steps, n, nsteps, tile, pieces, base, s)
+           : noalloc_setup<float>(plans, states, steps, n, nsteps, tile, pieces, base, s);
   if (rc) return rc;
   const BatchDev D{base + NA_DESC,
                    reinterpret_cast<SlotStep*>(base + NA_STEPS),

@@ -1,0 +1,133 @@
+"""Host code that prepares and issues the launches, on the CPU: libdugks.so runs
+over a stand-in for the HIP runtime (hip_stub.c), which hands every launch with
+its arguments to the test.  The stand-in's symbols must come before the real
+ones, so each case runs in a process of its own."""
+import collections
+import ctypes
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+NQUEUE = 8
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-w", "-o", so,
+                    os.path.join(HERE, "hip_stub.c")], check=True)
+    return so
+
+
+def run(stub, case, *args):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), stub, case, *map(str, args)],
+                       cwd=os.path.dirname(HERE), capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+# ------------------------------------------------------------ in the process
+class Dim3(ctypes.Structure):
+    _fields_ = [(c, ctypes.c_uint32) for c in "xyz"]
+
+
+class ItemPieces(ctypes.Structure):   # dugks_noalloc.hip
+    _fields_ = [("qstart", ctypes.c_int32 * 9), ("n", ctypes.c_int32),
+                ("start", ctypes.c_int32 * 264), ("grid", ctypes.c_int32 * 263),
+                ("first", ctypes.c_int32 * 263)]
+
+
+Event = collections.namedtuple("Event", "what obj blocks threads args")
+HOOK = ctypes.CFUNCTYPE(None, ctypes.c_char_p, ctypes.c_void_p, Dim3, Dim3,
+                        ctypes.POINTER(ctypes.c_void_p))
+
+
+class Trace(list):
+    """The calls since the last clear(); `on` may look at each as it is made."""
+
+    def __init__(self, so):
+        super().__init__()
+        self.on = None
+
+        def hook(what, obj, grid, block, args):
+            e = Event(what.decode(), obj, grid.x * grid.y * grid.z,
+                      block.x * block.y * block.z, args)
+            self.append(e)
+            if self.on:
+                self.on(e)
+
+        self.hook = HOOK(hook)
+        ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL).stub_set_hook(self.hook)
+
+    def kernels(self, name):
+        return [e for e in self if name in e.what]
+
+
+def plan(C, nx, ny, precision=0, recon=1, flags=0, scheme=0, rows=0):
+    return C.dugks_plan_create(C.make_params(nx, ny, 0.02, 4.0, 0.5, recon, precision=precision,
+                                             flags=flags, scheme=scheme, tile_rows=rows))
+
+
+LISTS = {"one 512": [512], "one 1000": [1000], "one 2048": [2048], "uneven": [512, 32, 40, 64],
+         "large and small": [1600] + [64] * 40, "three": [1000, 999, 700], "tiny": [64, 40, 33],
+         "mix": [32 + 37 * k % 480 for k in range(256)]}
+
+
+def many_queues(C, trace, sizes, precision, flags, scheme):
+    """dugks_step_many_noalloc gives the 8 XCDs equal work, whatever the grids
+    (but whole grids where no XCD has more blocks than its 32 compute units); every
+    tile of every grid is in the list once, taller marching tiles first within a
+    queue."""
+    pieces = ItemPieces()
+
+    def on(e):
+        if "noalloc_items_kernel" in e.what:
+            ctypes.memmove(ctypes.byref(pieces), e.args[0], ctypes.sizeof(pieces))
+
+    trace.on = on
+    sizes = LISTS[sizes]
+    plans = [plan(C, n, n, precision, 1, flags, scheme, 24 if n == 700 else 0) for n in sizes]
+    C.dugks_step_many_noalloc(plans, [256] * len(plans), [0] * len(plans), 1, 0)
+    total = pieces.qstart[NQUEUE]
+    seen = collections.Counter()
+    for p in range(pieces.n):
+        for i in range(pieces.start[p], pieces.start[p + 1]):
+            seen[pieces.grid[p], pieces.first[p] + i - pieces.start[p]] += 1
+    assert len(seen) == total and set(seen.values()) == {1}
+    tiles = [1 + max(t for g, t in seen if g == j) for j in range(len(sizes))]
+    assert sum(tiles) == total
+    block = trace.kernels("batch_tile_kernel")
+    counts = [pieces.qstart[q + 1] - pieces.qstart[q] for q in range(NQUEUE)]
+    if block:
+        assert max(counts) <= 32 or max(counts) - min(counts) <= 1, counts
+        assert all(e.blocks == NQUEUE * max(counts) for e in block)
+        return
+    # marching: a tile costs its rows (whole groups of 8) and 5 more; each cut is
+    # less than a tile short of an eighth of all
+    segs = [t // -(-n // 58) for n, t in zip(sizes, tiles)]
+    cost = [min(n, 8 * -(-(-(-n // s)) // 8)) + 5 for n, s in zip(sizes, segs)]
+    share = [0] * NQUEUE
+    for p in range(pieces.n):
+        q = max(k for k in range(NQUEUE) if pieces.qstart[k] <= pieces.start[p])
+        share[q] += (pieces.start[p + 1] - pieces.start[p]) * cost[pieces.grid[p]]
+    assert max(share) - min(share) < 2 * max(cost), share
+    for p in range(pieces.n - 1):
+        if pieces.start[p + 1] not in list(pieces.qstart):
+            assert cost[pieces.grid[p]] >= cost[pieces.grid[p + 1]]
+
+
+# --------------------------------------------------------------------- tests
+@pytest.mark.parametrize("precision,flags,scheme", [(0, 0, 0), (1, 2, 0), (0, 0, 1), (1, 0, 0)])
+@pytest.mark.parametrize("sizes", sorted(LISTS))
+def test_allocation_free_step_spreads_over_the_xcds(stub, sizes, precision, flags, scheme):
+    run(stub, "many_queues", sizes, precision, flags, scheme)
+
+
+if __name__ == "__main__":
+    sys.path.insert(0, os.getcwd())
+    the_trace = Trace(sys.argv[1])
+    from paper_2007_07760_amd import _lib
+    globals()[sys.argv[2]](_lib, the_trace,
+                           *[int(a) if a.lstrip("-").isdigit() else a for a in sys.argv[3:]])
