@@ -27,6 +27,7 @@ struct Slot {
   const dugks_plan* plan = nullptr;
   void* state = nullptr;
   int64_t step = 0, target = 0;
+  int64_t until = 0;                  // the batch's step (see done) it stops at
   bool step_dirty = false;
 };
 
@@ -132,6 +133,7 @@ struct dugks_batch {
   std::vector<int32_t> qstart;        // queue q: items [qstart[q], qstart[q + 1])
   int nq = 1;
   bool desc_dirty = true;
+  int64_t done = 0;                   // steps issued
   int rows = DEFAULT_ROWS;            // height of the marching tiles
   int tile = 0;                       // rows of the list's block tiles; 0: marching tiles
   bool given = false;                 // height and kind are the caller's (or the
@@ -160,48 +162,51 @@ GridDesc<T> make_desc(const Slot& s, int rows) {
   return make_grid_desc<T>(s.plan, s.state, rows);
 }
 
-// Work list of block tiles: every grid's tiles, segment by segment, cut into
-// NQUEUE equal bands, one per queue (starting at another queue for each slot).
-// A block takes one item of its XCD's queue, so the queues have to stay equal also
+// Whether a list of marching tiles of `rows` rows is more than two rounds of the
+// resident wavefronts, of grids that stop at different steps of the batch.  (Of
+// up to two rounds, a queue left alone is one for the quarter of the wavefronts
+// that reach it.)
+bool uneven_rounds(const dugks_batch* B, int rows) {
+  int64_t first = -1, tiles = 0;
+  bool differ = false;
+  for (const Slot& s : B->slots) {
+    if (!s.plan) continue;
+    const int64_t left = std::max<int64_t>(s.until - B->done, 0);
+    differ = differ || (first >= 0 && left != first);
+    first = left;
+    tiles += (int64_t)s.plan->nstrips * ((s.plan->p.ny + rows - 1) / rows);
+  }
+  return differ && tiles > 2 * (int64_t)B->grid_blocks;
+}
+
+struct Keyed {
+  int h;         // rows of the tile
+  BatchItem it;
+};
+
+// Every grid's tiles, segment by segment, cut into NQUEUE equal bands, one per
+// queue (starting at another queue for each slot): the queues stay equal also
 // when some grids have reached their targets.
-void build_tile_items(dugks_batch* B, int rows) {
-  std::vector<BatchItem> queue[NQUEUE];
+void spread_tiles(const dugks_batch* B, int rows, std::vector<Keyed>* queue) {
   for (int k = 0; k < B->cap; k++) {
     const Slot& s = B->slots[k];
     if (!s.plan) continue;
-    const int64_t n = (int64_t)s.plan->nstrips * ((s.plan->p.ny + rows - 1) / rows);
+    const int ny = s.plan->p.ny, nstrips = s.plan->nstrips;
+    const int seg = std::min(rows, ny);
+    const int64_t n = (int64_t)nstrips * ((ny + seg - 1) / seg);
     for (int64_t i = 0; i < n; i++)
-      queue[(i * NQUEUE / n + k) % NQUEUE].push_back({k, (int32_t)i});
+      queue[(i * NQUEUE / n + k) % NQUEUE].push_back(
+          {std::min(seg, ny - (int)(i / nstrips) * seg), {k, (int32_t)i}});
   }
-  B->qstart.assign(NQUEUE + 1, 0);
-  for (int q = 0; q < NQUEUE; q++) {
-    B->items.insert(B->items.end(), queue[q].begin(), queue[q].end());
-    B->qstart[q + 1] = (int32_t)B->items.size();
-  }
-  B->nq = B->items.empty() ? 1 : NQUEUE;
-  size_t most = 1;
-  for (const auto& v : queue) most = std::max(most, v.size());
-  B->tile_blocks = NQUEUE * (int)most;
 }
 
-// Work list for tile height `rows`, cut into NQUEUE queues of about equal
-// work (one per XCD).  The slots' tiles, largest slot first and each slot's
-// tiles segment by segment, are laid end to end and cut at equal shares of
-// the marched rows, so a queue holds whole small grids or a band of segments
-// of a large one: tiles that share halos stay in one XCD's L2.  Within a
-// queue the taller tiles come first, so that the short ones fill the tail.
-void build_items(dugks_batch* B, int rows) {
-  B->items.clear();
-  B->tile_blocks = 0;
-  if (B->tile) {
-    build_tile_items(B, rows);
-    return;
-  }
-  struct Keyed {
-    int h;
-    BatchItem it;
-  };
+// The grids' tiles, the largest grid first and each grid's segment by segment,
+// laid end to end and cut at equal shares of the marched rows, so a queue holds
+// whole small grids or a band of segments of a large one: tiles that share halos
+// stay in one XCD's L2.
+void share_tiles(const dugks_batch* B, int rows, std::vector<Keyed>* queue) {
   std::vector<std::pair<int64_t, int>> order;   // (marched rows, slot)
+  int64_t total = 0;
   for (int k = 0; k < B->cap; k++) {
     const Slot& s = B->slots[k];
     if (!s.plan) continue;
@@ -209,12 +214,14 @@ void build_items(dugks_batch* B, int rows) {
     const int seg = std::min(rows, ny);
     const int64_t nsegs = (ny + seg - 1) / seg;
     order.push_back({(int64_t)s.plan->nstrips * (ny + 5 * nsegs), k});
+    total += order.back().first;
   }
   std::stable_sort(order.begin(), order.end(),
                    [](const std::pair<int64_t, int>& a, const std::pair<int64_t, int>& b) {
                      return a.first > b.first;
                    });
-  std::vector<Keyed> v;
+  int q = 0;
+  int64_t done = 0;
   for (const auto& o : order) {
     const int k = o.second;
     const Slot& s = B->slots[k];
@@ -223,27 +230,45 @@ void build_items(dugks_batch* B, int rows) {
     const int nsegs = (ny + seg - 1) / seg;
     for (int g = 0; g < nsegs; g++) {
       const int h = std::min(seg, ny - g * seg);
-      for (int st = 0; st < nstrips; st++) v.push_back({h, {k, g * nstrips + st}});
+      for (int st = 0; st < nstrips; st++) {
+        // up to the queue's share of the work (the last queue takes the rest)
+        while (q < NQUEUE - 1 && done + h + 5 > total * (q + 1) / NQUEUE) q++;
+        queue[q].push_back({h, {k, g * nstrips + st}});
+        done += h + 5;
+      }
     }
   }
-  int64_t total = 0;
-  for (const Keyed& k : v) total += k.h + 5;
-  B->nq = v.empty() ? 1 : NQUEUE;
-  B->qstart.assign(NQUEUE + 1, (int32_t)v.size());
-  B->qstart[0] = 0;
-  size_t i = 0;
-  int64_t done = 0;
-  for (int q = 0; q < B->nq; q++) {
-    const size_t first = i;
-    // up to the queue's share of the work (the last queue takes the rest)
-    const int64_t upto = total * (q + 1) / B->nq;
-    while (i < v.size() && (q == B->nq - 1 || done + v[i].h + 5 <= upto)) done += v[i++].h + 5;
-    std::stable_sort(v.begin() + first, v.begin() + i,
-                     [](const Keyed& a, const Keyed& b) { return a.h > b.h; });
-    B->qstart[q + 1] = (int32_t)i;
+}
+
+// The work list for tiles of `rows` rows, cut into NQUEUE queues of about equal
+// work (one per XCD); within a queue the taller tiles come first, so that the
+// short ones fill the tail.  A block of the tile kernel takes one item of its
+// XCD's queue, so every queue gets a band of each grid, and so it does where
+// marching wavefronts take several tiles each and the grids stop at different
+// steps: once a queue's grids have stopped, a seventh of its wavefronts goes on to
+// each of the others.  128 of 1024 corrected FP32 grids of 256^2 going on, us per
+// step with whole grids in a queue / bands: 652 / 317 (FP64 1008 / 453), 32 of 256
+// grids 187 / 78.  While all run, bands cost up to 1 % at the default heights (4 %
+// for central-4 of hardly more than two rounds) and 2-5 % at 64 rows.
+void build_items(dugks_batch* B, int rows) {
+  std::vector<Keyed> queue[NQUEUE];
+  if (B->tile || uneven_rounds(B, rows))
+    spread_tiles(B, rows, queue);
+  else
+    share_tiles(B, rows, queue);
+  B->items.clear();
+  B->qstart.assign(NQUEUE + 1, 0);
+  size_t most = 1;
+  for (int q = 0; q < NQUEUE; q++) {
+    if (!B->tile)
+      std::stable_sort(queue[q].begin(), queue[q].end(),
+                       [](const Keyed& a, const Keyed& b) { return a.h > b.h; });
+    for (const Keyed& k : queue[q]) B->items.push_back(k.it);
+    B->qstart[q + 1] = (int32_t)B->items.size();
+    most = std::max(most, queue[q].size());
   }
-  B->items.reserve(v.size());
-  for (const Keyed& k : v) B->items.push_back(k.it);
+  B->nq = B->items.empty() ? 1 : NQUEUE;
+  B->tile_blocks = B->tile ? NQUEUE * (int)most : 0;
 }
 
 int ensure_items_cap(dugks_batch* B, size_t n, hipStream_t s) {
@@ -510,6 +535,7 @@ int dugks_batch_set(dugks_batch* batch, int32_t slot, const dugks_plan* plan, vo
   s.state = state;
   s.step = step;
   s.target = target;
+  s.until = target - step > INT64_MAX - batch->done ? INT64_MAX : batch->done + (target - step);
   s.step_dirty = true;
   batch->desc_dirty = true;
   return DUGKS_OK;
@@ -537,12 +563,15 @@ int dugks_batch_step(dugks_batch* batch, int64_t nsteps, int32_t graph_steps, vo
     hipGraphExec_t exec = nullptr;
     int rc = capture_graph(batch, graph_steps, &exec);
     if (rc) return rc;
-    for (; left >= graph_steps; left -= graph_steps)
+    for (; left >= graph_steps; left -= graph_steps) {
       if (hipGraphLaunch(exec, s) != hipSuccess) return DUGKS_EDEVICE;
+      batch->done += graph_steps;
+    }
   }
   for (; left > 0; left--) {
     int rc = batch_launch(batch, s, true, batch->tile_blocks);
     if (rc) return rc;
+    batch->done++;
   }
   return DUGKS_OK;
 }

@@ -1050,7 +1050,8 @@ struct BatchItem {
 // blocks of a launch go round-robin to the 8 XCDs, so block b drains queue
 // b % nq first, and the tiles that share halo rows and columns (one grid's
 // neighbouring strips and segments, kept together in one queue) meet in one
-// L2.  A block whose own queue is drained takes items from the others.
+// L2.  A marching wavefront whose own queue is drained takes items from one
+// other, so the lists are cut into queues of equal work.
 constexpr int NQUEUE = 8;
 // Queue q keeps its heads (stage A or T2, then stage B) in a 128-byte line of
 // its own: atomics from different XCDs on one line run several times slower.
@@ -1083,10 +1084,10 @@ __global__ __launch_bounds__(LANES, step_waves(sizeof(T), R, MFIX)) void batch_s
   const int nq = c->nq;
   const int home = nq > 0 ? (int)(blockIdx.x % (unsigned)nq) : 0;
   unsigned* heads = head + (STAGE == STAGE_B ? 1 : 0);
-  // The home queue, then one other: another of the seven for each wavefront of
-  // the XCD, so that a queue whose grids run on while others' have stopped is
-  // drained by all XCDs.  A wavefront's first item goes by its index, so a
-  // queue's head counts from the number of its home wavefronts.  (Trying all
+  // The home queue, then one other, another of the seven for each wavefront of
+  // the XCD: that evens out what equal shares leave over (a queue left alone with
+  // work would have a quarter of the chip).  A wavefront's first item goes by its
+  // index, so a queue's head counts from the number of its home wavefronts.  (Trying all
   // eight queues cost ~1.5 us of failed atomics apiece at the end of every
   // wavefront: 16-row tiles, 4 grids of 256^2 75 us a step, now 45; 256 grids
   // 217, now 211.  Looking at the heads with plain loads first made the kernel

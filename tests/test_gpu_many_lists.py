@@ -48,3 +48,38 @@ def test_many_equals_alone_bitwise(name, precision, flags, scheme):
         assert torch.equal(s.distributions(), o.distributions()), g
         assert torch.equal(s.history(), o.history()), g
         assert s.mass() == o.mass() and s.status() == o.status() == C.OK, g
+
+
+@pytest.mark.parametrize("precision,flags,scheme", [(1, 2, 0), (0, 0, 0), (0, 0, 1)])
+def test_batch_of_many_rounds_with_its_own_targets(precision, flags, scheme):
+    """A batch of more than two rounds of marching tiles (3072 and 2048 wavefronts)
+    whose grids stop at different steps: bitwise the grids alone."""
+    import torch
+    from paper_2007_07760_amd import _lib as C
+    from paper_2007_07760_amd.batch import Batch
+    from paper_2007_07760_amd.solver import Solver
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    print(f"case batch prec={precision} flags={flags} scheme={scheme}", flush=True)
+    n = 40
+    sizes = [(291 + 9 * (k % 8), 410 + k) for k in range(n)]
+    targets = [1 + 5 * (k % 3) for k in range(n)]
+
+    def make():
+        return [Solver(nx, ny, 0.02, 4.0, 0.5, precision=precision, vel_kind=3,
+                       vel_param=(0.04, 70.0), flags=flags, scheme=scheme)
+                .init(I.random_circles(nx, ny, 3, 20.0, 60.0, 4.0, seed=k))
+                for k, (nx, ny) in enumerate(sizes)]
+
+    batched, alone = make(), make()
+    b = Batch(n, precision, C.UPWIND3, flags | (C.BATCH_T3S3 if scheme else 0))
+    for k, s in enumerate(batched):
+        b.set(k, s, targets[k])
+    b.commit()
+    b.step(13, graph_steps=4)
+    b.sync()
+    for k, (s, o) in enumerate(zip(batched, alone)):
+        o.step(targets[k])
+        assert s.step_index == targets[k]
+        assert torch.equal(s.distributions(), o.distributions()), k
+        assert torch.equal(s.history(), o.history()) and s.mass() == o.mass(), k

@@ -118,11 +118,48 @@ def many_queues(C, trace, sizes, precision, flags, scheme):
             assert cost[pieces.grid[p]] >= cost[pieces.grid[p + 1]]
 
 
+class BatchCtl(ctypes.Structure):     # dugks_kernels.h
+    _fields_ = [("items", ctypes.POINTER(ctypes.c_int32 * 2)), ("nitems", ctypes.c_int32),
+                ("nq", ctypes.c_int32), ("qstart", ctypes.c_int32 * 9)]
+
+
+def batch_queues(C, trace, precision, flags, scheme):
+    """A batch of which an eighth of the grids goes on after the others: each
+    XCD's queue holds an eighth of the tiles that are left."""
+    n, keep = 1024, 128
+    plans = [plan(C, 256, 256, precision, 1, flags, scheme)] * n
+    b = C.dugks_batch_create(n, precision, 1, flags | (C.BATCH_T3S3 if scheme else 0))
+    for k, p in enumerate(plans):
+        C.dugks_batch_set(b, k, p, 256, 0, 50 if k < keep else 5)
+    C.dugks_batch_commit(b, 0)
+    left = [0] * NQUEUE
+
+    def on(e):
+        if "batch_step_kernel" in e.what:
+            ctl = ctypes.cast(ctypes.cast(e.args[2], ctypes.POINTER(ctypes.c_void_p))[0],
+                              ctypes.POINTER(BatchCtl))[0]
+            assert ctl.nq == NQUEUE and len({tuple(ctl.items[i]) for i in range(ctl.nitems)}) \
+                == ctl.nitems == 5 * 16 * n
+            for q in range(NQUEUE):
+                left[q] = sum(ctl.items[i][0] < keep
+                              for i in range(ctl.qstart[q], ctl.qstart[q + 1]))
+
+    trace.on = on
+    C.dugks_batch_step(b, 1, 0, 0)
+    # a grid's bands differ by one tile
+    assert sum(left) == 5 * 16 * keep and max(left) - min(left) <= keep, left
+
+
 # --------------------------------------------------------------------- tests
 @pytest.mark.parametrize("precision,flags,scheme", [(0, 0, 0), (1, 2, 0), (0, 0, 1), (1, 0, 0)])
 @pytest.mark.parametrize("sizes", sorted(LISTS))
 def test_allocation_free_step_spreads_over_the_xcds(stub, sizes, precision, flags, scheme):
     run(stub, "many_queues", sizes, precision, flags, scheme)
+
+
+@pytest.mark.parametrize("precision,flags,scheme", [(0, 0, 0), (1, 2, 0), (0, 0, 1)])
+def test_batch_spreads_what_goes_on_over_the_xcds(stub, precision, flags, scheme):
+    run(stub, "batch_queues", precision, flags, scheme)
 
 
 if __name__ == "__main__":
