@@ -153,6 +153,13 @@ struct dugks_batch {
     int k = 0;
     int blocks = 0;                   // of its tile kernels: no fewer than the list needs
   } graphs[3];                        // marching tiles, block tiles of 4 and 8 rows
+  // replaced graphs whose replays may still be running: until `over` has passed
+  struct Retired {
+    hipGraph_t graph;
+    hipGraphExec_t exec;
+    hipEvent_t over;
+  };
+  std::vector<Retired> retired;
 };
 
 namespace {
@@ -395,7 +402,47 @@ int commit(dugks_batch* B, hipStream_t s) {
   return B->precision == DUGKS_F64 ? upload<double>(B, s) : upload<float>(B, s);
 }
 
+void drop(const dugks_batch::Retired& r) {
+  (void)hipGraphExecDestroy(r.exec);
+  (void)hipGraphDestroy(r.graph);
+  if (r.over) (void)hipEventDestroy(r.over);
+}
+
+// A graph is replaced while its last replay may be running (work list and steps
+// are only queued), and an executable graph has to outlive its replays: kept
+// until an event behind them on `s` has passed (batch calls follow one another
+// in stream order).  Under a capture of the caller's, until the batch goes.  At
+// most RETIRED_MAX wait, then the oldest is waited for.
+constexpr size_t RETIRED_MAX = 16;
+void retire(dugks_batch* B, dugks_batch::Graph* G, hipStream_t s) {
+  dugks_batch::Retired r{G->graph, G->exec, nullptr};
+  G->exec = nullptr;
+  G->graph = nullptr;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+  if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+      hipEventCreateWithFlags(&r.over, hipEventDisableTiming) == hipSuccess &&
+      hipEventRecord(r.over, s) != hipSuccess) {
+    (void)hipEventDestroy(r.over);
+    r.over = nullptr;
+  }
+  B->retired.push_back(r);
+  std::vector<dugks_batch::Retired> keep;
+  size_t waiting = 0;
+  for (const auto& o : B->retired) waiting += o.over != nullptr;
+  for (const auto& o : B->retired) {
+    if (o.over && (hipEventQuery(o.over) == hipSuccess ||
+                   (waiting > RETIRED_MAX && hipEventSynchronize(o.over) == hipSuccess))) {
+      drop(o);
+      waiting--;
+    } else {
+      keep.push_back(o);
+    }
+  }
+  B->retired.swap(keep);
+}
+
 void release(dugks_batch* B) {
+  for (const auto& r : B->retired) drop(r);
   for (dugks_batch::Graph& g : B->graphs) {
     if (g.exec) (void)hipGraphExecDestroy(g.exec);
     if (g.graph) (void)hipGraphDestroy(g.graph);
@@ -419,14 +466,11 @@ void release(dugks_batch* B) {
 // The graph of k steps over the kind of tiles the list holds.  A graph's tile
 // kernels have a power of two of blocks per queue, so that it is captured again
 // only when the list has outgrown it.
-int capture_graph(dugks_batch* B, int k, hipGraphExec_t* exec) {
+int capture_graph(dugks_batch* B, int k, hipStream_t s, hipGraphExec_t* exec) {
   dugks_batch::Graph& G = B->graphs[B->tile / 4];
   *exec = G.exec;
   if (G.exec && G.k == k && G.blocks >= B->tile_blocks) return DUGKS_OK;
-  if (G.exec) (void)hipGraphExecDestroy(G.exec);
-  if (G.graph) (void)hipGraphDestroy(G.graph);
-  G.exec = nullptr;
-  G.graph = nullptr;
+  if (G.exec) retire(B, &G, s);
   if (hipStreamBeginCapture(B->cap_stream, hipStreamCaptureModeRelaxed) != hipSuccess)
     return DUGKS_EDEVICE;
   int rc = DUGKS_OK;
@@ -442,7 +486,9 @@ int capture_graph(dugks_batch* B, int k, hipGraphExec_t* exec) {
   }
   G.graph = g;
   if (hipGraphInstantiate(&G.exec, g, nullptr, nullptr, 0) != hipSuccess) {
+    (void)hipGraphDestroy(g);
     G.exec = nullptr;
+    G.graph = nullptr;
     return DUGKS_EDEVICE;
   }
   G.k = k;
@@ -561,7 +607,7 @@ int dugks_batch_step(dugks_batch* batch, int64_t nsteps, int32_t graph_steps, vo
   int64_t left = nsteps;
   if (graph_steps > 1 && nsteps >= graph_steps) {
     hipGraphExec_t exec = nullptr;
-    int rc = capture_graph(batch, graph_steps, &exec);
+    int rc = capture_graph(batch, graph_steps, s, &exec);
     if (rc) return rc;
     for (; left >= graph_steps; left -= graph_steps) {
       if (hipGraphLaunch(exec, s) != hipSuccess) return DUGKS_EDEVICE;

@@ -50,13 +50,17 @@ class Trace(list):
     def __init__(self, so):
         super().__init__()
         self.on = None
+        self.error = None             # the first exception of `on` (ctypes drops them)
 
         def hook(what, obj, grid, block, args):
             e = Event(what.decode(), obj, grid.x * grid.y * grid.z,
                       block.x * block.y * block.z, args)
             self.append(e)
-            if self.on:
-                self.on(e)
+            try:
+                if self.on:
+                    self.on(e)
+            except Exception as x:
+                self.error = self.error or x
 
         self.hook = HOOK(hook)
         ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL).stub_set_hook(self.hook)
@@ -150,6 +154,49 @@ def batch_queues(C, trace, precision, flags, scheme):
     assert sum(left) == 5 * 16 * keep and max(left) - min(left) <= keep, left
 
 
+def graph_lifetime(C, trace):
+    """An executable graph the batch replaces (its list has outgrown it, or the
+    steps per graph changed) is not destroyed while a replay may be running: not
+    before an event recorded after its last replay has been waited for or found
+    passed (the stand-in's events never pass by themselves).  Never more than a
+    few of them are kept, and destroying the batch leaves none."""
+    sizes = [16, 64, 128, 256, 512]
+    plans = [plan(C, n, n) for n in sizes]
+    b = C.dugks_batch_create(len(sizes), 0, 1, 0)
+    live, replayed, recorded, over = set(), {}, {}, set()
+    clock = [0]
+    most = [0]
+
+    def on(e):
+        clock[0] += 1
+        if e.what == "instantiate":
+            live.add(e.obj)
+            most[0] = max(most[0], len(live))
+        elif e.what == "graph_launch":
+            assert e.obj in live
+            replayed[e.obj] = clock[0]
+        elif e.what == "event_record":
+            recorded[e.obj] = clock[0]
+        elif e.what == "event_sync":
+            over.add(recorded.get(e.obj, 0))
+        elif e.what == "device_sync":
+            over.add(clock[0])
+        elif e.what == "exec_destroy":
+            assert any(t > replayed[e.obj] for t in over), "destroyed while it may be running"
+            live.remove(e.obj)
+
+    trace.on = on
+    for k, p in enumerate(plans):      # the list grows, with a round in flight
+        C.dugks_batch_set(b, k, p, 256, 0, 1 << 20)
+        C.dugks_batch_commit(b, 0)
+        C.dugks_batch_step(b, 16, 16, 0)
+    for k in range(60):
+        C.dugks_batch_step(b, 20, 4 + k % 3, 0)
+    assert most[0] <= 24
+    C.dugks_batch_destroy(b)
+    assert not live
+
+
 # --------------------------------------------------------------------- tests
 @pytest.mark.parametrize("precision,flags,scheme", [(0, 0, 0), (1, 2, 0), (0, 0, 1), (1, 0, 0)])
 @pytest.mark.parametrize("sizes", sorted(LISTS))
@@ -162,9 +209,15 @@ def test_batch_spreads_what_goes_on_over_the_xcds(stub, precision, flags, scheme
     run(stub, "batch_queues", precision, flags, scheme)
 
 
+def test_replaced_graphs_outlive_their_replays(stub):
+    run(stub, "graph_lifetime")
+
+
 if __name__ == "__main__":
     sys.path.insert(0, os.getcwd())
     the_trace = Trace(sys.argv[1])
     from paper_2007_07760_amd import _lib
     globals()[sys.argv[2]](_lib, the_trace,
                            *[int(a) if a.lstrip("-").isdigit() else a for a in sys.argv[3:]])
+    if the_trace.error:
+        raise the_trace.error
