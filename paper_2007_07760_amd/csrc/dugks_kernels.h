@@ -766,8 +766,13 @@ struct Marcher {
   // load row y1 + LAG again, so that every row issues the same loads), faces
   // of r-LAG (none for the first rows of the tile; the north faces only for
   // row y0 - 1, the south faces of row y0)
+  // Central-4 with velocity arrays in FP64 reads the stencil table afresh on every
+  // row: kept across rows it took all scalar registers, and moves to and from
+  // vector lanes made a quarter of the kernel (1000^2, 16 rows: 122 -> 82 us).
+  static constexpr bool RELOAD = VARR && sizeof(T) == 8 && R == DUGKS_CENTRAL4 && !MFIX;
   template <int FACE>
   __device__ __forceinline__ void body(int r, RowRegs<T>& cur, RowRegs<T>& nxt) {
+    if constexpr (RELOAD) asm volatile("" : "+s"(cf));
     phi_push(nxt);
     cell_stage(cur, r);
     load_row(cur, min(r + 2, y1 + LAG));
