@@ -151,11 +151,13 @@ typedef struct {
   int32_t vel_kind;        /* dugks_vel_kind                                     */
   int32_t flags;           /* DUGKS_FLAG_*                                       */
   double vel_param[6];     /* p0.. of the velocity kind; finite                  */
-  int32_t tile_rows;       /* rows of a tile; 0 = library default.  Up to 8: a block
-                              of wavefronts takes the tile's rows side by side (the
-                              default for small grids; at 8, for grids whose default
-                              is to march 8 rows, that); more: one wavefront marches
-                              them.  Results do not depend on it. */
+  int32_t tile_rows;       /* rows of a tile; 0 = library default.  Up to 8 asks for
+                              tiles that a block of wavefronts takes, its rows
+                              side by side (4, 8 or 10 of them, by the library's
+                              rule): the default for small grids, taken on larger
+                              ones where it beats a march of that height.  Else
+                              one wavefront marches that many rows.  Results do
+                              not depend on it. */
   int32_t scheme;          /* dugks_scheme                                       */
 } dugks_params;
 

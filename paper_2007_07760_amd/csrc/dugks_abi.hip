@@ -291,30 +291,8 @@ int default_tile_rows(const dugks_params& p, int nstrips) {
   return best;
 }
 
-// Rows of the tile kernel's tiles, or 0 where the march runs: heights up to
-// TILE_MAX_ROWS ask for it, and by default grids too small to fill the chip
-// with marching wavefronts take it.  A marching wavefront needs ~25 us (FP64
-// upwind-3) for an 8-row tile however few there are, the tile kernel 6.0 us for
-// a grid of up to 256 tiles, but it forms the cell terms of 12 rows for every 8
-// (8 for every 4).  The line lies at the number of 16-row marching tiles where
-// the two meet, measured on square grids (us per step, tile / march): FP64
-// upwind-3 768^2 33.0 / 35.2, 896^2 43.0 / 40.2; central-4 768^2 43.3 / 45.8,
-// 896^2 56.0 / 54.5; velocity arrays 768^2 34.5 / 38.4, 896^2 45.2 / 43.7; T3S3
-// 640^2 66.3 / 60.9; upwind-5 1024^2 100 / 124, 1280^2 149 / 160;
-// FP32 corrected 768^2 29.0 / 30.8, 896^2 34.9 / 32.3, central-4 896^2 37.6 / 37.6.
-// Where the march's default is 8 rows too, asking for 8 gives the default.
-int tile_kernel_rows(const dugks_params& p, int nstrips) {
-  if (p.tile_rows > TILE_MAX_ROWS) return 0;
-  const long n16 = (long)nstrips * ((p.ny + 15) / 16);
-  const long limit = p.recon == DUGKS_UPWIND5    ? (p.precision == DUGKS_F32 ? 1000 : 1850)
-                     : p.recon == DUGKS_CENTRAL4 ? (p.precision == DUGKS_F32 ? 900 : 840)
-                     : p.precision == DUGKS_F32  ? 760
-                     : p.scheme == DUGKS_T3S3    ? 400
-                     : p.vel_kind == DUGKS_VEL_ARRAYS ? 840
-                                                      : 760;
-  const bool small = n16 <= limit;
-  if (p.tile_rows == 0 && !small) return 0;
-  if (p.tile_rows == 8 && !small && default_tile_rows(p, nstrips) == 8) return 0;
+// Rows of the tiles the tile kernel takes of such a grid.
+int tile_rows_of(const dugks_params& p, int nstrips) {
   const bool mfix = (p.flags & DUGKS_FLAG_MASS_FIX) != 0;
   const int rows = block_tile_rows(p.precision == DUGKS_F64 ? 8 : 4, p.recon, p.scheme, mfix,
                                    (int64_t)nstrips * ((p.ny + 3) / 4));
@@ -328,6 +306,85 @@ int tile_kernel_rows(const dugks_params& p, int nstrips) {
   const int r8 = (nstrips * ((p.ny + 7) / 8) + 255) / 256;
   const int r10 = (nstrips * ((p.ny + 9) / 10) + 255) / 256;
   return 10 * r10 < 9 * r8 ? 10 : 8;
+}
+
+// Whether a grid is too small to fill the chip with marching wavefronts, so that
+// the tile kernel is its default.  A marching wavefront needs ~25 us (FP64
+// upwind-3) for an 8-row tile however few there are, the tile kernel 6.0 us for
+// a grid of up to 256 tiles, but it forms the cell terms of 12 rows for every 8
+// (8 for every 4).  The line lies at the number of 16-row marching tiles where
+// the two meet, measured on square grids (us per step, tile / march): FP64
+// upwind-3 768^2 33.0 / 35.2, 896^2 43.0 / 40.2; central-4 768^2 43.3 / 45.8,
+// 896^2 56.0 / 54.5; central-2 900^2 38.4 / 40.9, 1000^2 45.1 / 44.3; velocity
+// arrays 768^2 34.5 / 38.4, 896^2 45.2 / 43.7; T3S3 640^2 66.3 / 60.9; FP32 corrected 768^2 29.0 / 30.8, 896^2 34.9 / 32.3, central-4
+// 896^2 37.6 / 37.6, upwind-5 768^2 66 / 69, 832^2 76 / 71.  The corrected FP64
+// kernels of the 3-point patches have room for one round of 512 blocks: upwind-3
+// 448^2 27 / 33, 512^2 38 / 34; central-2 26 / 27, 37 / 27; T3S3 46 / 62, 69 / 65;
+// with arrays upwind-3 576^2 36 / 38, 640^2 42 / 40.
+// FP64 upwind-5 runs whole rounds either way, of 256 blocks or of 1024 marching
+// wavefronts (one per SIMD): ~11.3 us a round of 8-row blocks, 12.7 of 10-row
+// ones, 4.45 a row of a marching round (corrected 13.8 and 5.35): 1040^2 105 /
+// 124, 1000 x 1300 129 / 125, 1400^2 178 / 195; corrected 832^2 97 / 106, 940^2
+// 114 / 108, 1000^2 128 / 149, 1150^2 162 / 152.
+bool tile_kernel_default(const dugks_params& p, int nstrips, int rows) {
+  const bool f64 = p.precision == DUGKS_F64, mfix = (p.flags & DUGKS_FLAG_MASS_FIX) != 0;
+  const bool arrays = p.vel_kind == DUGKS_VEL_ARRAYS;
+  if (f64 && wide(p.recon)) {
+    const int h = std::min(whole_round_rows(p, nstrips), p.ny);
+    const long blocks = (long)nstrips * ((p.ny + rows - 1) / rows);
+    const long tiles = (long)nstrips * ((p.ny + h - 1) / h);
+    const double block_us = mfix ? 13.8 : (rows == 10 ? 12.7 : 11.3);
+    return (double)((blocks + 255) / 256) * block_us <
+           (double)((tiles + 1023) / 1024) * (h + 4) * (mfix ? 5.35 : 4.45);
+  }
+  const long n16 = (long)nstrips * ((p.ny + 15) / 16);
+  const long limit = wide(p.recon)                ? (mfix ? 740 : 1000)
+                     : p.recon == DUGKS_CENTRAL4  ? (f64 ? 840 : 900)
+                     : f64 && mfix                ? (arrays ? 400 : 256)
+                     : f64 && p.scheme == DUGKS_T3S3 ? 400
+                     : f64 && p.recon == DUGKS_CENTRAL2 ? 930
+                     : f64 && arrays              ? 840
+                                                  : 760;
+  return n16 <= limit;
+}
+
+// Rows of the tile kernel's tiles, or 0 where the march runs.  Heights up to
+// TILE_MAX_ROWS ask for the kernel.  They get it wherever it is the default, and on
+// larger grids where it beats a march of that height (us per step, tile / march):
+// always in FP64 upwind-5 (8 rows: 2500^2 corrected 712 / 770) and uncorrected FP64
+// central-4 (361 / 451), and for up to 3 rows uncorrected (2500^2: FP64 upwind-3 297 /
+// 335, FP32 195 / 203); up to some way beyond the default's line in the other FP64 T2
+// forms (8 rows: upwind-3 1024^2 54 / 62, 1448^2 103 / 103, 2500^2 298 / 273;
+// corrected central-4 1200^2 120 / 129, 1448^2 167 / 149) and in uncorrected FP32 (6
+// rows: upwind-3 1200^2 47.0 / 49.3, 2500^2 199 / 165, T3S3 900^2 67 / 63; 8 rows:
+// central-4 1200^2 51.4 / 58.2, 1448^2 71.2 / 68.5).  Elsewhere they are marched (8 rows: 2500^2 FP32 upwind-3
+// 199 / 159, corrected 224 / 183, upwind-5 363 / 268; T3S3 1448^2 285 / 259), FP32
+// upwind-5 from 740^2 on (704^2 35 / 40, 768^2 43 / 40), corrected 640^2.  Where the
+// march's default is 8 rows too, asking for 8 gives the default.
+int tile_kernel_rows(const dugks_params& p, int nstrips) {
+  if (p.tile_rows > TILE_MAX_ROWS) return 0;
+  const int rows = tile_rows_of(p, nstrips);
+  bool take = tile_kernel_default(p, nstrips, rows);
+  if (p.tile_rows > 0) {
+    const bool f64 = p.precision == DUGKS_F64, mfix = (p.flags & DUGKS_FLAG_MASS_FIX) != 0;
+    const bool c4 = p.recon == DUGKS_CENTRAL4;
+    const long n16 = (long)nstrips * ((p.ny + 15) / 16);
+    if (!take && p.tile_rows == 8 && default_tile_rows(p, nstrips) == 8) return 0;
+    long line = 0;
+    if (wide(p.recon)) {
+      if (!f64 && p.tile_rows > (mfix ? 0 : 6)) take = n16 <= (mfix ? 450 : 620);
+    } else if (f64 && p.scheme == DUGKS_T2) {
+      line = !mfix ? 2280 : (c4 ? 1680 : 0);
+    } else if (!f64 && !mfix) {
+      line = p.tile_rows <= (p.scheme == DUGKS_T3S3 ? 4 : 6) ? 2280 : (c4 ? 1575 : 0);
+    }
+    take = take || n16 <= line || (f64 && (wide(p.recon) || (c4 && !mfix))) ||
+           (!mfix && p.tile_rows <= 3);
+  }
+  // a launch holds fewer than 2^32 threads
+  const int64_t blocks = (int64_t)nstrips * ((p.ny + rows - 1) / rows);
+  if (blocks * LANES * tile_cell_rows(p.recon, rows) >= INT64_C(1) << 32) return 0;
+  return take ? rows : 0;
 }
 
 // ------------------------------------------------------------ launches

@@ -138,8 +138,16 @@ __host__ __device__ constexpr int step_waves(int esize, int recon, bool mfix) {
                      : (esize == 8 ? 2 : ((recon == DUGKS_CENTRAL4 || mfix) ? 3 : 4));
 }
 
-// The tile kernel (dugks_tile.h) takes tiles of up to this many rows; the
-// register budgets of its variants, in wavefronts per SIMD.
+// Cell rows (and wavefronts) of a tile of TR rows of the tile kernel
+// (dugks_tile.h): the faces of its rows and of the row below reach 2 (3) rows
+// down and up.
+__host__ __device__ constexpr int tile_cell_rows(int recon, int TR) {
+  return TR + 2 * (wide(recon) ? 3 : 2);
+}
+
+// Requested tile heights up to this one ask for the tile kernel, which takes 4, 8
+// or 10 rows by its own rule (see tile_kernel_rows); the register budgets of its
+// variants, in wavefronts per SIMD.
 constexpr int TILE_MAX_ROWS = 8;
 // (stage_b: T3S3's second stage, which holds a row of Q as well.)
 __host__ __device__ constexpr int tile_waves(int esize, int recon, int TR, bool stage_b) {

@@ -36,12 +36,6 @@
 
 namespace dugks {
 
-// cell rows of a tile of TR rows: the faces of its rows and of the row below
-// reach LAG rows down and up
-__host__ __device__ constexpr int tile_cell_rows(int recon, int TR) {
-  return TR + 2 * (wide(recon) ? 3 : 2);
-}
-
 // the face values of row k, velocity by velocity from I on: pn of the north
 // faces, de of the east less the west ones, and their sums over the velocities
 template <bool EAST, int I = 0, typename M, typename T>

@@ -197,6 +197,43 @@ def graph_lifetime(C, trace):
     assert not live
 
 
+# (nx, ny, precision, recon, flags, scheme, tile_rows): rows of a marching tile, or 0
+# for the tile kernel; both sides of each line (default and requested heights)
+KERNELS = [
+    # corrected FP64: one round of 512 blocks of 8 rows
+    (448, 448, 0, 1, 2, 0, 0, 0), (512, 512, 0, 1, 2, 0, 0, 8), (768, 768, 0, 0, 2, 0, 0, 8),
+    (512, 512, 0, 0, 2, 1, 0, 8), (768, 768, 0, 2, 2, 0, 0, 0),
+    # corrected upwind-5
+    (768, 768, 1, 3, 2, 0, 0, 0), (900, 900, 1, 3, 2, 0, 0, 16), (832, 832, 0, 3, 2, 0, 0, 0),
+    (940, 940, 0, 3, 2, 0, 0, 16), (1000, 1000, 0, 3, 2, 0, 0, 0), (1000, 1300, 0, 3, 0, 0, 0, 24),
+    (1100, 1100, 0, 3, 0, 0, 0, 0),
+    # 8 rows asked for on large grids: marched at that height, as a height of 16 is
+    (2048, 2048, 1, 1, 0, 0, 8, 8), (2048, 2048, 1, 1, 2, 0, 8, 8), (2048, 2048, 0, 1, 0, 0, 8, 8),
+    (2048, 2048, 0, 1, 0, 1, 8, 8), (2500, 2500, 1, 3, 0, 0, 8, 8), (2048, 2048, 1, 1, 0, 0, 6, 6),
+    (2048, 2048, 1, 1, 2, 0, 1, 8), (2048, 2048, 0, 1, 0, 0, 16, 16),
+    # where the tile kernel beats that
+    (2048, 2048, 0, 2, 0, 0, 8, 0), (2500, 2500, 0, 3, 2, 0, 8, 0), (1024, 1024, 0, 1, 0, 0, 8, 0),
+    (2048, 2048, 1, 1, 0, 0, 2, 0), (150, 400, 0, 1, 0, 0, 8, 0),
+    # more than 2^32 threads in 4-row tiles
+    (60000, 60000, 1, 1, 0, 0, 3, 3),
+]
+
+
+def kernels(C, trace):
+    for nx, ny, precision, recon, flags, scheme, asked, rows in KERNELS:
+        p = plan(C, nx, ny, precision, recon, flags, scheme, asked)
+        trace.clear()
+        C.dugks_step(p, 256, 0, 1, 0)
+        case = (nx, ny, precision, recon, flags, scheme, asked, rows)
+        assert all(e.blocks * e.threads < 1 << 32 for e in trace), case
+        march = trace.kernels("11step_kernel")
+        assert bool(march) == (rows > 0) and bool(trace.kernels("tile_kernel")) == (rows == 0), case
+        if rows:   # whole segments per XCD from 32 on, else whole tiles; not for upwind-5
+            strips, segs = -(-nx // 58), -(-ny // rows)
+            least = 8 * -(-segs // 8) * strips if segs >= 32 and recon != 3 else strips * segs
+            assert all(least <= e.blocks < least + 8 * strips + 8 for e in march), case
+
+
 # --------------------------------------------------------------------- tests
 @pytest.mark.parametrize("precision,flags,scheme", [(0, 0, 0), (1, 2, 0), (0, 0, 1), (1, 0, 0)])
 @pytest.mark.parametrize("sizes", sorted(LISTS))
@@ -211,6 +248,10 @@ def test_batch_spreads_what_goes_on_over_the_xcds(stub, precision, flags, scheme
 
 def test_replaced_graphs_outlive_their_replays(stub):
     run(stub, "graph_lifetime")
+
+
+def test_kernel_and_height_of_a_step(stub):
+    run(stub, "kernels")
 
 
 if __name__ == "__main__":
