@@ -260,31 +260,42 @@ int whole_round_rows(const dugks_params& p, int nstrips) {
 // 0.5 + 0.5 f of that (few wavefronts run faster, to half the time), and a row
 // costs 0.6 % more for every row of height beyond 16 (the wavefronts of
 // neighbouring strips fall out of step, and lines they share leave the caches).
-// FP32 without the correction has 4 wavefronts per SIMD but is bound by VALU from
-// 2 on.  The estimate orders the heights as measured within 3-5 %; us per step at
+// FP32 without the correction has 3 or 4 wavefronts per SIMD but is bound by VALU
+// from 2 on, with velocity arrays from 3 on; there and in central-4 a part of a
+// round steps with its wavefronts per SIMD, 0.5 + 0.4 f + 0.1 from the first to the
+// last of them.  The estimate orders the heights as measured within 3-5 %; us per step at
 // its choice / at the lowest multiple of 8 that makes whole rounds of the chip:
 // FP64 upwind-3 1024^2 51.7 (10 rows) / 54.9, 1400^2 83 (18) / 92, 1900^2 139
 // (16) / 187 (32 rows: 8 segments in some bands, and a second round there),
 // 4096^2 602 (16) / 692 (72); central-4 1900^2 203 (14) / 216; FP32 corrected
-// 2000^2 105 (32) / 125 (24), 4096^2 358 (32) / 469 (96); T3S3 1900^2 400 / 509.
+// 2000^2 105 (32) / 125 (24), 4096^2 358 (32) / 469 (96); T3S3 1900^2 400 / 509;
+// FP32 arrays, against the choice for 2 wavefronts per SIMD, central-4 1900^2 110
+// (22) / 129 (34), 1024 x 8192 245 (16) / 294 (40), upwind-3 1900^2 101 (22) / 114 (34).
 // Upwind-5, one wavefront per SIMD in FP64, keeps whole rounds (2048^2 377
 // against 432 at 16).
 int default_tile_rows(const dugks_params& p, int nstrips) {
   if (p.recon == DUGKS_UPWIND5) return whole_round_rows(p, nstrips);
   const bool fix = (p.flags & DUGKS_FLAG_MASS_FIX) != 0;
   long resident = resident_wavefronts(p);
-  if (p.precision == DUGKS_F32 && !fix) resident = std::min(resident, 2048L);
-  const double c = resident / 8.0;
+  const bool arrays = p.vel_kind == DUGKS_VEL_ARRAYS;
+  double step = 0.0;
+  if (p.precision == DUGKS_F32 && !fix) {
+    resident = std::min(resident, arrays ? 3072L : 2048L);
+    if (arrays || p.recon == DUGKS_CENTRAL4) step = 0.1;
+  }
+  const double c = resident / 8.0, simds = 128.0;   // of an XCD
   auto cost = [&](int seg) {
     const int nsegs = (p.ny + seg - 1) / seg;
     const double t = segment_bands(nsegs, p.recon) ? (double)((nsegs + 7) / 8) * nstrips
                                                    : (double)(((long)nstrips * nsegs + 7) / 8);
     const double n = t / c, whole = floor(n), f = n - whole;
-    return (whole + (f > 0.0 ? 0.5 + 0.5 * f : 0.0)) * (seg + 5) * (1.0 + 0.006 * (seg - 16));
+    double part = 0.5 + (0.5 - step) * f;
+    if (step > 0.0) part += step * (ceil((t - whole * c) / simds) - 1.0) / (ceil(c / simds) - 1.0);
+    return (whole + (f > 0.0 ? part : 0.0)) * (seg + 5) * (1.0 + 0.006 * (seg - 16));
   };
   // every height where there are few rounds, else the multiples of 8 from 16 on
   const long tiles16 = (long)nstrips * ((p.ny + 15) / 16);
-  const bool few = tiles16 < 4 * resident;
+  const bool few = tiles16 < (fix ? 4 * resident : std::min(4 * resident, 8192L));
   int best = 16;
   for (int seg = few ? 8 : 16; seg <= 40; seg += few && !fix ? 1 : MASS_GROUP)
     if (cost(seg) < cost(best)) best = seg;

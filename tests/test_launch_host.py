@@ -69,9 +69,10 @@ class Trace(list):
         return [e for e in self if name in e.what]
 
 
-def plan(C, nx, ny, precision=0, recon=1, flags=0, scheme=0, rows=0):
+def plan(C, nx, ny, precision=0, recon=1, flags=0, scheme=0, rows=0, vel=0):
     return C.dugks_plan_create(C.make_params(nx, ny, 0.02, 4.0, 0.5, recon, precision=precision,
-                                             flags=flags, scheme=scheme, tile_rows=rows))
+                                             vel_kind=vel, flags=flags, scheme=scheme,
+                                             tile_rows=rows))
 
 
 LISTS = {"one 512": [512], "one 1000": [1000], "one 2048": [2048], "uneven": [512, 32, 40, 64],
@@ -216,12 +217,15 @@ KERNELS = [
     (2048, 2048, 1, 1, 0, 0, 2, 0), (150, 400, 0, 1, 0, 0, 8, 0),
     # more than 2^32 threads in 4-row tiles
     (60000, 60000, 1, 1, 0, 0, 3, 3),
+    # default heights: FP32 with velocity arrays has 3 wavefronts per SIMD to fill
+    (1900, 1900, 1, 2, 0, 0, 0, 22, 4), (1900, 1900, 1, 1, 0, 0, 0, 22, 4),
+    (1024, 8192, 1, 2, 0, 0, 0, 16, 4), (1900, 1900, 1, 1, 0, 0, 0, 34, 0),
 ]
 
 
 def kernels(C, trace):
-    for nx, ny, precision, recon, flags, scheme, asked, rows in KERNELS:
-        p = plan(C, nx, ny, precision, recon, flags, scheme, asked)
+    for nx, ny, precision, recon, flags, scheme, asked, rows, *vel in KERNELS:
+        p = plan(C, nx, ny, precision, recon, flags, scheme, asked, *vel)
         trace.clear()
         C.dugks_step(p, 256, 0, 1, 0)
         case = (nx, ny, precision, recon, flags, scheme, asked, rows)
