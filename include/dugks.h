@@ -333,17 +333,19 @@ int dugks_batch_status(const dugks_batch *batch, int32_t *out, void *stream);
  * that are one tile high).  Until it is set each commit chooses it, and whether
  * block tiles of up to 8 rows are taken instead (batches too small to fill the
  * chip with marching wavefronts).  set: EINVAL unless 8 <= rows <= 65536 and
- * rows % 8 == 0 (8: block tiles); takes effect at the next commit. */
+ * rows % 8 == 0; takes effect at the next commit.  8 asks for block tiles (marched
+ * 8 rows where the grids are too many for those), more for the march. */
 int dugks_batch_tile_rows(const dugks_batch *batch);
 int dugks_batch_set_tile_rows(dugks_batch *batch, int32_t rows);
-/* Autotuner: time the persistent step kernel over the attached, active grids
- * (`reps` launches per candidate tile height from 16 to 256 rows, HIP events
- * on `stream`), keep the fastest and commit it; where the block tiles are
- * faster still, the batch takes those, and rows_out is the best marching
- * height.  The timed launches write only
+/* Autotuner: time the step kernel over the attached, active grids with the
+ * batch's own choice of tiles and with marching tiles of 16 to 256 rows (`reps`
+ * launches each, HIP events on `stream`), keep the fastest and commit it.
+ * rows_out: the height of the marching tiles; where block tiles won, the batch
+ * keeps to those while its grids are few, and rows_out is the best marching
+ * height (setting that height asks for the march).  The timed launches write only
  * each grid's next-step buffer and mass partials, which the next real step
  * overwrites, so the states and results are unchanged.  Blocks until done.
- * Errors: EINVAL, EDEVICE. */
+ * Errors: EINVAL, EDEVICE (the batch's heights are then as before). */
 int dugks_batch_tune(dugks_batch *batch, int32_t reps, int32_t *rows_out,
                      void *stream);
 

@@ -19,7 +19,7 @@ namespace {
 
 constexpr int NSTAGE = 3;   // pinned staging buffers in flight
 
-// Tile heights the autotuner tries (whole mass groups; 0: the block tiles).
+// Tile heights the autotuner tries (whole mass groups; 0: the batch's own choice).
 constexpr int TUNE_ROWS[] = {0, 16, 24, 32, 48, 64, 96, 128, 192, 256};
 constexpr int DEFAULT_ROWS = 64;   // reported until the first commit chooses
 
@@ -136,8 +136,9 @@ struct dugks_batch {
   int64_t done = 0;                   // steps issued
   int rows = DEFAULT_ROWS;            // height of the marching tiles
   int tile = 0;                       // rows of the list's block tiles; 0: marching tiles
-  bool given = false;                 // height and kind are the caller's (or the
-  bool given_tile = false;            // autotuner's) choice; else each commit chooses
+  bool given = false;                 // the height is the caller's (or the autotuner's)
+  bool given_tile = false;            // choice, with block tiles while the grids are
+                                      // few; else each commit chooses
   int grid_blocks = 0;                // resident wavefronts of the persistent kernel
   int tile_blocks = 0;                // NQUEUE x the longest queue of block tiles
   // pinned staging ring: [ctl][desc table][steps][items]
@@ -365,15 +366,16 @@ int batch_launch(dugks_batch* B, hipStream_t s, bool finish, int blocks) {
   return launch_batch(D, B->precision, B->recon, B->mfix, B->scheme, s, finish);
 }
 
-// The kind and height of the tiles, where the caller has given none: as for
-// one grid (see default_tile_rows and tile_kernel_rows in dugks_abi.hip), by
-// the number of 16-row marching tiles of all grids together; 8 rows where those
-// still make one round (24 of a mix of FP32 grids: 45.5 us a step against 52.3
-// at 16).  A batch too small
-// to fill the chip is bound by one tile's latency: us per step with 64-row
-// marching tiles / now, FP32 corrected: one 64^2 grid 164 / 12.5, eight 128^2
-// 176 / 16.6, 16 grids of sides 32-512 178 / 39; 64 of them 175 / 76, 256 239 /
-// 211.
+// The kind and height of the tiles.  Where the caller has given none, as for one
+// grid (see default_tile_rows and tile_kernel_default in dugks_abi.hip), by the
+// number of 16-row marching tiles of all grids together; 8 rows where those still
+// make one round (24 of a mix of FP32 grids: 45.5 us a step against 52.3 at 16).  A
+// batch too small to fill the chip is bound by one tile's latency: us per step with
+// 64-row marching tiles / now, FP32 corrected: one 64^2 grid 164 / 12.5, eight 128^2
+// 176 / 16.6, 16 grids of sides 32-512 178 / 39; 64 of them 175 / 76, 256 239 / 211.
+// A given height of 8 asks for block tiles; of more grids than those are good for it
+// is marched (256 grids of the mix, block tiles / march: FP32 corrected 416 / 340, FP64
+// 598 / 535).
 void choose_tiles(dugks_batch* B) {
   auto count = [B](int rows) {
     int64_t n = 0;
@@ -383,8 +385,8 @@ void choose_tiles(dugks_batch* B) {
   };
   const int rows0 = B->rows, tile0 = B->tile;
   const int64_t n16 = count(16);
-  const bool block = B->given ? B->given_tile
-                              : n16 <= batch_tile_limit(B->precision, B->recon, B->scheme);
+  const bool block = (!B->given || B->given_tile) &&
+                     n16 <= batch_tile_limit(B->precision, B->recon, B->scheme);
   B->tile = block ? block_tile_rows(B->precision == DUGKS_F64 ? 8 : 4, B->recon, B->scheme,
                                     B->mfix, count(4))
                   : 0;
@@ -655,13 +657,15 @@ int dugks_batch_tune(dugks_batch* batch, int32_t reps, int32_t* rows_out, void* 
     return DUGKS_EDEVICE;
   }
   int rc = DUGKS_OK;
-  float best_ms = -1.0f;
-  int best = batch->rows;
-  float best_tile_ms = -1.0f;
-  batch->given = true;
-  // the block tiles (rows 0), then the heights of the march
+  const int rows0 = batch->rows;
+  const bool given0 = batch->given, given_tile0 = batch->given_tile;
+  // the batch's own choice first, then the heights of the march
+  float own_ms = -1.0f, best_ms = -1.0f;
+  int own = 0, best = rows0;
+  bool own_tile = false;
   for (int rows : TUNE_ROWS) {
-    batch->given_tile = rows == 0;
+    batch->given = rows != 0;
+    batch->given_tile = false;
     if (rows) batch->rows = rows;
     batch->desc_dirty = true;
     if ((rc = commit(batch, s))) break;
@@ -686,7 +690,9 @@ int dugks_batch_tune(dugks_batch* batch, int32_t reps, int32_t* rows_out, void* 
     float ms = 0.0f;
     (void)hipEventElapsedTime(&ms, e0, e1);
     if (!rows) {
-      best_tile_ms = ms;
+      own_ms = ms;
+      own_tile = batch->tile != 0;
+      own = batch->rows;
     } else if (best_ms < 0.0f || ms < best_ms) {
       best_ms = ms;
       best = rows;
@@ -694,8 +700,16 @@ int dugks_batch_tune(dugks_batch* batch, int32_t reps, int32_t* rows_out, void* 
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  batch->rows = best;
-  batch->given_tile = best_ms >= 0.0f && best_tile_ms < best_ms;
+  if (rc) {   // as it was
+    batch->rows = rows0;
+    batch->given = given0;
+    batch->given_tile = given_tile0;
+  } else {
+    batch->given = true;
+    batch->given_tile = own_tile && own_ms <= best_ms;
+    batch->rows = !own_tile && own_ms <= best_ms ? own : best;
+    best = batch->rows;
+  }
   batch->desc_dirty = true;
   int rc2 = commit(batch, s);
   if (!rc) rc = rc2;

@@ -71,7 +71,8 @@ int hipEventCreateWithFlags(void **e, unsigned f) { *e = handle(); return 0; }
 int hipEventCreate(void **e) { return hipEventCreateWithFlags(e, 0); }
 int hipEventDestroy(void *e) { return tell("event_destroy", e); }
 int hipEventRecord(void *e, void *st) { return tell("event_record", e); }
-int hipEventSynchronize(void *e) { return tell("event_sync", e); }
+int stub_event_sync_rc;
+int hipEventSynchronize(void *e) { tell("event_sync", e); return stub_event_sync_rc; }
 int hipEventQuery(void *e) { tell("event_query", e); return 600; }        /* not ready */
 int hipEventElapsedTime(float *ms, void *a, void *b) {
   *ms = 1.0f;

@@ -63,7 +63,8 @@ class Trace(list):
                 self.error = self.error or x
 
         self.hook = HOOK(hook)
-        ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL).stub_set_hook(self.hook)
+        self.lib = ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL)
+        self.lib.stub_set_hook(self.hook)
 
     def kernels(self, name):
         return [e for e in self if name in e.what]
@@ -238,6 +239,86 @@ def kernels(C, trace):
             assert all(least <= e.blocks < least + 8 * strips + 8 for e in march), case
 
 
+def batch_of(C, sizes, precision=1, flags=2):
+    b = C.dugks_batch_create(len(sizes), precision, 1, flags)
+    for k, n in enumerate(sizes):
+        C.dugks_batch_set(b, k, plan(C, n, n, precision, 1, flags), 256, 0, 1 << 20)
+    C.dugks_batch_commit(b, 0)
+    return b
+
+
+def listed(C, trace, b):
+    """(kernel, tiles in the list) of the batch's next step."""
+    got = []
+
+    def on(e):
+        for name, k in (("batch_step_kernel", 2), ("batch_tile_kernel", 2)):
+            if name in e.what:
+                ctl = ctypes.cast(ctypes.cast(e.args[k], ctypes.POINTER(ctypes.c_void_p))[0],
+                                  ctypes.POINTER(BatchCtl))[0]
+                got.append((name, ctl.nitems))
+
+    before, trace.on = trace.on, on
+    C.dugks_batch_step(b, 1, 0, 0)
+    trace.on = before
+    return got[0]
+
+
+def batch_tuning(C, trace):
+    """The tuner keeps what measured fastest, the batch's own choice among it, and
+    a tuner that fails leaves the batch's choice as it was."""
+    fastest = [None]
+    state = {}
+
+    def on(e):   # the time of a candidate by the tiles of its list
+        if "batch_step_kernel" in e.what or "batch_tile_kernel" in e.what:
+            ctl = ctypes.cast(ctypes.cast(e.args[2], ctypes.POINTER(ctypes.c_void_p))[0],
+                              ctypes.POINTER(BatchCtl))[0]
+            state["last"] = ("batch_tile_kernel" in e.what, ctl.nitems)
+        elif e.what == "elapsed":
+            ctypes.cast(e.obj, ctypes.POINTER(ctypes.c_float))[0] = \
+                1.0 if state["last"] == fastest[0] else 2.0
+
+    trace.on = on
+    # one grid of 1000^2, corrected FP32: marched 8 rows by default, 18 x 125 tiles
+    b = batch_of(C, [1000])
+    assert listed(C, trace, b) == ("batch_step_kernel", 18 * 125)
+    fastest[0] = (False, 18 * 125)
+    assert C.dugks_batch_tune(b, 1, 0) == 8 == C.dugks_batch_tile_rows(b)
+    assert listed(C, trace, b) == ("batch_step_kernel", 18 * 125)
+    C.dugks_batch_set_tile_rows(b, 8)
+    C.dugks_batch_commit(b, 0)
+    assert listed(C, trace, b) == ("batch_step_kernel", 18 * 125)
+    fastest[0] = (False, 18 * 21)          # 48 rows
+    assert C.dugks_batch_tune(b, 1, 0) == 48
+    assert listed(C, trace, b) == ("batch_step_kernel", 18 * 21)
+    # few grids: block tiles stay while they are few, then the best marching height
+    b = batch_of(C, [64, 64, 64])
+    fastest[0] = (True, 3 * 2 * 8)
+    assert 16 <= C.dugks_batch_tune(b, 1, 0) <= 256
+    assert listed(C, trace, b) == ("batch_tile_kernel", 3 * 2 * 8)
+    C.dugks_batch_set(b, 0, plan(C, 2000, 2000, 1, 1, 2), 256, 0, 1 << 20)
+    C.dugks_batch_commit(b, 0)
+    assert listed(C, trace, b)[0] == "batch_step_kernel"
+    # a device error on the way
+    b = batch_of(C, [64, 64, 64])
+    rc = ctypes.c_int.in_dll(trace.lib, "stub_event_sync_rc")
+    rc.value = 1
+    try:
+        C.dugks_batch_tune(b, 1, 0)
+        raise AssertionError("no error")
+    except RuntimeError:
+        pass
+    rc.value = 0
+    C.dugks_batch_commit(b, 0)
+    assert listed(C, trace, b) == ("batch_tile_kernel", 3 * 2 * 8)
+    # 8 rows asked for on a list too large for block tiles
+    b = batch_of(C, [512] * 40)
+    C.dugks_batch_set_tile_rows(b, 8)
+    C.dugks_batch_commit(b, 0)
+    assert listed(C, trace, b) == ("batch_step_kernel", 40 * 9 * 64)
+
+
 # --------------------------------------------------------------------- tests
 @pytest.mark.parametrize("precision,flags,scheme", [(0, 0, 0), (1, 2, 0), (0, 0, 1), (1, 0, 0)])
 @pytest.mark.parametrize("sizes", sorted(LISTS))
@@ -256,6 +337,10 @@ def test_replaced_graphs_outlive_their_replays(stub):
 
 def test_kernel_and_height_of_a_step(stub):
     run(stub, "kernels")
+
+
+def test_batch_tuner_keeps_the_fastest(stub):
+    run(stub, "batch_tuning")
 
 
 if __name__ == "__main__":
