@@ -364,11 +364,12 @@ int dugks_batch_tune(dugks_batch *batch, int32_t reps, int32_t *rows_out,
  * travel as kernel arguments; no hipMalloc, hipFree, pinned staging or graph.
  *  - plans, states, steps: host arrays of n entries.  Every plan of one
  *    precision, reconstruction, DUGKS_FLAG_MASS_FIX setting and time scheme;
- *    each grid is tiled at its own plan's tile height (block tiles, as a
- *    batch's, where all grids together are few tiles).
+ *    each grid is tiled at its own plan's tile height, of at least 16 rows
+ *    (whatever those are, block tiles as a batch's where all grids together are
+ *    few tiles: results do not depend on the tiles).
  *  - Limits: 1 <= n <= 256 grids and at most 116192 tiles (strips x row
- *    segments) over all grids; beyond them DUGKS_EINVAL, before anything is
- *    launched.
+ *    segments of the height the plan asks for) over all grids; beyond them
+ *    DUGKS_EINVAL, before anything is launched.
  *  - Every call on one GPU shares that GPU's array, which keeps the last
  *    call's contents (each call rewrites what it reads first).  Calls that
  *    overlap on one GPU -- other streams, other threads -- race: the caller

@@ -670,10 +670,11 @@ int dugks_plan_create(const dugks_params* p, dugks_plan** out) {
   P->nsegs = (p->ny + P->seg_rows - 1) / P->seg_rows;
   // dugks_step_many_noalloc: its work list is of a fixed length, so large
   // grids keep the taller tiles of whole rounds, and short ones are not shorter
-  // than 16 rows
-  P->many_rows = rows(p->tile_rows > 0 ? std::max(16, p->tile_rows)
-                                       : whole_round_rows(*p, P->nstrips));
+  // than 16 rows; its limit counts the height asked for
+  const int asked = p->tile_rows > 0 ? p->tile_rows : whole_round_rows(*p, P->nstrips);
+  P->many_rows = rows(std::max(16, asked));
   P->many_segs = (p->ny + P->many_rows - 1) / P->many_rows;
+  P->many_limit_segs = (p->ny + rows(asked) - 1) / rows(asked);
   *out = P;
   return DUGKS_OK;
 }

@@ -262,11 +262,12 @@ int dugks_step_many_noalloc(const dugks_plan* const* plans, void* const* states,
   const int tile = n16 <= batch_tile_limit(precision, recon, scheme)
                        ? block_tile_rows(precision == DUGKS_F64 ? 8 : 4, recon, scheme, mfix, n4)
                        : 0;
-  int64_t total = 0;
+  int64_t total = 0, items = 0;
   for (int j = 0; j < n; j++) {
     const dugks_plan* P = plans[j];
-    total += (int64_t)P->nstrips * (tile ? (P->p.ny + tile - 1) / tile : P->many_segs);
-    if (total > NOALLOC_ITEMS) return DUGKS_EINVAL;   // beyond the array's work list
+    total += (int64_t)P->nstrips * P->many_limit_segs;
+    items += (int64_t)P->nstrips * (tile ? (P->p.ny + tile - 1) / tile : P->many_segs);
+    if (std::max(total, items) > NOALLOC_ITEMS) return DUGKS_EINVAL;   // beyond the work list
   }
   if (nsteps == 0) return DUGKS_OK;
   unsigned char* base = nullptr;

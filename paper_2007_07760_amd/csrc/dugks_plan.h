@@ -29,6 +29,7 @@ struct dugks_plan {
   double compact2[dugks::NCOMPACT];  // T3S3 stage B stencil (compact: stage A)
   int seg_rows, nstrips, nsegs;   // of the march
   int many_rows, many_segs;       // of dugks_step_many_noalloc
+  int many_limit_segs;            // segments its limit counts
   int tile;                  // rows of the tile kernel's tiles (4, 8 or 10); 0: the march
   std::vector<double> tabx, taby;
   // the constant head of every state of this plan (header, coefficient and

@@ -319,6 +319,25 @@ def batch_tuning(C, trace):
     assert listed(C, trace, b) == ("batch_step_kernel", 40 * 9 * 64)
 
 
+def many_limit(C, trace):
+    """dugks_step_many_noalloc: 116192 tiles of the heights the plans ask for."""
+    def status(nx, ny, rows, flags=0):
+        try:
+            C.dugks_step_many_noalloc([plan(C, nx, ny, 1, 1, flags, 0, rows)], [256], [0], 1, 0)
+        except C.DugksError as e:
+            return e.code
+        return C.OK
+
+    strips = 142                        # 8192 columns
+    assert status(8192, 116192 // strips * 8, 8) == C.OK
+    assert status(8192, 116192 // strips * 8 + 8, 8) == C.EINVAL
+    assert status(8192, 116192 // strips * 12, 12) == C.OK
+    assert status(8192, 116192 // strips * 12 + 1, 12) == C.EINVAL
+    assert status(8192, 116192 // strips * 8, 1, C.FLAG_MASS_FIX) == C.OK   # whole groups of 8
+    assert status(8192, 8192, 0) == C.OK
+    assert status(512, 512, 1) == C.OK
+
+
 # --------------------------------------------------------------------- tests
 @pytest.mark.parametrize("precision,flags,scheme", [(0, 0, 0), (1, 2, 0), (0, 0, 1), (1, 0, 0)])
 @pytest.mark.parametrize("sizes", sorted(LISTS))
@@ -341,6 +360,10 @@ def test_kernel_and_height_of_a_step(stub):
 
 def test_batch_tuner_keeps_the_fastest(stub):
     run(stub, "batch_tuning")
+
+
+def test_allocation_free_step_limit(stub):
+    run(stub, "many_limit")
 
 
 if __name__ == "__main__":
