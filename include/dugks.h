@@ -367,7 +367,7 @@ int dugks_batch_tune(dugks_batch *batch, int32_t reps, int32_t *rows_out,
  *    each grid is tiled at its own plan's tile height, of at least 16 rows
  *    (whatever those are, block tiles as a batch's where all grids together are
  *    few tiles: results do not depend on the tiles).
- *  - Limits: 1 <= n <= 256 grids and at most 116192 tiles (strips x row
+ *  - Limits: 1 <= n <= 256 grids and at most 115680 tiles (strips x row
  *    segments of the height the plan asks for) over all grids; beyond them
  *    DUGKS_EINVAL, before anything is launched.
  *  - Every call on one GPU shares that GPU's array, which keeps the last

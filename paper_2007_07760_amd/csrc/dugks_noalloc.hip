@@ -30,6 +30,7 @@ constexpr size_t NA_ITEMS =
     (NA_DESC + NOALLOC_GRIDS * sizeof(GridDesc<double>) + 255) / 256 * 256;
 constexpr int64_t NOALLOC_ITEMS = (int64_t)((NOALLOC_BYTES - NA_ITEMS) / sizeof(BatchItem));
 static_assert(sizeof(GridDesc<double>) >= sizeof(GridDesc<float>), "descriptor sizes");
+static_assert(NOALLOC_ITEMS == 115680, "the limit include/dugks.h states");
 static_assert(sizeof(BatchCtl) <= NA_HEAD - NA_CTL, "control block");
 static_assert(NA_STEPS % 256 == 0, "alignment");
 

@@ -320,7 +320,7 @@ def batch_tuning(C, trace):
 
 
 def many_limit(C, trace):
-    """dugks_step_many_noalloc: 116192 tiles of the heights the plans ask for."""
+    """dugks_step_many_noalloc: 115680 tiles of the heights the plans ask for."""
     def status(nx, ny, rows, flags=0):
         try:
             C.dugks_step_many_noalloc([plan(C, nx, ny, 1, 1, flags, 0, rows)], [256], [0], 1, 0)
@@ -329,11 +329,11 @@ def many_limit(C, trace):
         return C.OK
 
     strips = 142                        # 8192 columns
-    assert status(8192, 116192 // strips * 8, 8) == C.OK
-    assert status(8192, 116192 // strips * 8 + 8, 8) == C.EINVAL
-    assert status(8192, 116192 // strips * 12, 12) == C.OK
-    assert status(8192, 116192 // strips * 12 + 1, 12) == C.EINVAL
-    assert status(8192, 116192 // strips * 8, 1, C.FLAG_MASS_FIX) == C.OK   # whole groups of 8
+    assert status(8192, 115680 // strips * 8, 8) == C.OK
+    assert status(8192, 115680 // strips * 8 + 8, 8) == C.EINVAL
+    assert status(8192, 115680 // strips * 12, 12) == C.OK
+    assert status(8192, 115680 // strips * 12 + 1, 12) == C.EINVAL
+    assert status(8192, 115680 // strips * 8, 1, C.FLAG_MASS_FIX) == C.OK   # whole groups of 8
     assert status(8192, 8192, 0) == C.OK
     assert status(512, 512, 1) == C.OK
 
