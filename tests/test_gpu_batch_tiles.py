@@ -66,3 +66,18 @@ def test_block_tiles_equal_marching_tiles(lib, precision, recon, flags, scheme):
         for r in results:
             assert torch.equal(r[k][0], alone[0]) and torch.equal(r[k][1], alone[1]), g
             assert r[k][2] == alone[2], g
+
+
+@pytest.mark.parametrize("precision,recon,flags,scheme", [(1, 2, 2, 0), (0, 0, 0, 0), (0, 2, 0, 1)])
+def test_allocation_free_step_over_block_tiles(lib, precision, recon, flags, scheme):
+    import torch
+    print(f"case noalloc prec={precision} recon={recon} flags={flags} scheme={scheme}", flush=True)
+    many, alone = ([_solver(lib, g, precision, recon, flags, scheme) for g in GRIDS]
+                   for _ in range(2))
+    lib.dugks_step_many_noalloc([s.plan for s in many], [s.state.data_ptr() for s in many],
+                                [0] * len(many), 9, torch.cuda.current_stream().cuda_stream)
+    for s, o, g in zip(many, alone, GRIDS):
+        s.step_index = 9
+        o.step(9)
+        assert torch.equal(s.distributions(), o.distributions()), g
+        assert torch.equal(s.history(), o.history()) and s.mass() == o.mass(), g

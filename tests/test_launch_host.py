@@ -218,6 +218,11 @@ KERNELS = [
     (2048, 2048, 1, 1, 0, 0, 2, 0), (150, 400, 0, 1, 0, 0, 8, 0),
     # more than 2^32 threads in 4-row tiles
     (60000, 60000, 1, 1, 0, 0, 3, 3),
+    # the tilings of test_gpu_march_heights.py
+    (150, 401, 0, 1, 0, 0, 9, 9), (150, 401, 1, 1, 0, 0, 12, 12), (800, 905, 1, 1, 2, 0, 8, 8),
+    (75, 402, 0, 2, 0, 0, 9, 9, 4), (700, 563, 0, 1, 0, 1, 5, 5), (1003, 903, 0, 1, 2, 0, 1, 8),
+    (1003, 903, 1, 1, 2, 0, 1, 8), (800, 803, 1, 3, 0, 0, 7, 7), (262, 221, 0, 0, 0, 0, 8, 0),
+    (262, 222, 0, 1, 0, 0, 8, 0, 4), (301, 229, 0, 3, 0, 0, 8, 0), (301, 229, 1, 3, 0, 0, 8, 0),
     # default heights: FP32 with velocity arrays has 3 wavefronts per SIMD to fill
     (1900, 1900, 1, 2, 0, 0, 0, 22, 4), (1900, 1900, 1, 1, 0, 0, 0, 22, 4),
     (1024, 8192, 1, 2, 0, 0, 0, 16, 4), (1900, 1900, 1, 1, 0, 0, 0, 34, 0),
