@@ -272,9 +272,13 @@ int whole_round_rows(const dugks_params& p, int nstrips) {
 // FP32 arrays, against the choice for 2 wavefronts per SIMD, central-4 1900^2 110
 // (22) / 129 (34), 1024 x 8192 245 (16) / 294 (40), upwind-3 1900^2 101 (22) / 114 (34).
 // Upwind-5, one wavefront per SIMD in FP64, keeps whole rounds (2048^2 377
-// against 432 at 16).
+// against 432 at 16); in FP32 also that of 8-row tiles (900^2 42 against 57 at 16,
+// corrected 51 against 73).
 int default_tile_rows(const dugks_params& p, int nstrips) {
-  if (p.recon == DUGKS_UPWIND5) return whole_round_rows(p, nstrips);
+  if (p.recon == DUGKS_UPWIND5) {
+    const bool one = p.precision == DUGKS_F32 && (long)nstrips * ((p.ny + 7) / 8) <= 2048;
+    return one ? 8 : whole_round_rows(p, nstrips);
+  }
   const bool fix = (p.flags & DUGKS_FLAG_MASS_FIX) != 0;
   long resident = resident_wavefronts(p);
   const bool arrays = p.vel_kind == DUGKS_VEL_ARRAYS;
@@ -328,7 +332,8 @@ int tile_rows_of(const dugks_params& p, int nstrips) {
 // upwind-3 768^2 33.0 / 35.2, 896^2 43.0 / 40.2; central-4 768^2 43.3 / 45.8,
 // 896^2 56.0 / 54.5; central-2 900^2 38.4 / 40.9, 1000^2 45.1 / 44.3; velocity
 // arrays 768^2 34.5 / 38.4, 896^2 45.2 / 43.7; T3S3 640^2 66.3 / 60.9; FP32 corrected 768^2 29.0 / 30.8, 896^2 34.9 / 32.3, central-4
-// 896^2 37.6 / 37.6, upwind-5 768^2 66 / 69, 832^2 76 / 71.  The corrected FP64
+// 896^2 37.6 / 37.6, upwind-5 704^2 35 / 40, 768^2 43 / 40, corrected 576^2 37 / 42,
+// 704^2 57 / 48.  The corrected FP64
 // kernels of the 3-point patches have room for one round of 512 blocks: upwind-3
 // 448^2 27 / 33, 512^2 38 / 34; central-2 26 / 27, 37 / 27; T3S3 46 / 62, 69 / 65;
 // with arrays upwind-3 576^2 36 / 38, 640^2 42 / 40.
@@ -349,7 +354,7 @@ bool tile_kernel_default(const dugks_params& p, int nstrips, int rows) {
            (double)((tiles + 1023) / 1024) * (h + 4) * (mfix ? 5.35 : 4.45);
   }
   const long n16 = (long)nstrips * ((p.ny + 15) / 16);
-  const long limit = wide(p.recon)                ? (mfix ? 740 : 1000)
+  const long limit = wide(p.recon)                ? (mfix ? 450 : 620)
                      : p.recon == DUGKS_CENTRAL4  ? (f64 ? 840 : 900)
                      : f64 && mfix                ? (arrays ? 400 : 256)
                      : f64 && p.scheme == DUGKS_T3S3 ? 400
@@ -368,9 +373,9 @@ bool tile_kernel_default(const dugks_params& p, int nstrips, int rows) {
 // forms (8 rows: upwind-3 1024^2 54 / 62, 1448^2 103 / 103, 2500^2 298 / 273;
 // corrected central-4 1200^2 120 / 129, 1448^2 167 / 149) and in uncorrected FP32 (6
 // rows: upwind-3 1200^2 47.0 / 49.3, 2500^2 199 / 165, T3S3 900^2 67 / 63; 8 rows:
-// central-4 1200^2 51.4 / 58.2, 1448^2 71.2 / 68.5).  Elsewhere they are marched (8 rows: 2500^2 FP32 upwind-3
-// 199 / 159, corrected 224 / 183, upwind-5 363 / 268; T3S3 1448^2 285 / 259), FP32
-// upwind-5 from 740^2 on (704^2 35 / 40, 768^2 43 / 40), corrected 640^2.  Where the
+// central-4 1200^2 51.4 / 58.2, 1448^2 71.2 / 68.5).  Elsewhere they are marched (8
+// rows: 2500^2 FP32 upwind-3
+// 199 / 159, corrected 224 / 183, upwind-5 363 / 268; T3S3 1448^2 285 / 259).  Where the
 // march's default is 8 rows too, asking for 8 gives the default.
 int tile_kernel_rows(const dugks_params& p, int nstrips) {
   if (p.tile_rows > TILE_MAX_ROWS) return 0;
@@ -382,12 +387,11 @@ int tile_kernel_rows(const dugks_params& p, int nstrips) {
     const long n16 = (long)nstrips * ((p.ny + 15) / 16);
     if (!take && p.tile_rows == 8 && default_tile_rows(p, nstrips) == 8) return 0;
     long line = 0;
-    if (wide(p.recon)) {
-      if (!f64 && p.tile_rows > (mfix ? 0 : 6)) take = n16 <= (mfix ? 450 : 620);
-    } else if (f64 && p.scheme == DUGKS_T2) {
+    if (f64 && p.scheme == DUGKS_T2) {
       line = !mfix ? 2280 : (c4 ? 1680 : 0);
     } else if (!f64 && !mfix) {
-      line = p.tile_rows <= (p.scheme == DUGKS_T3S3 ? 4 : 6) ? 2280 : (c4 ? 1575 : 0);
+      const int most = p.scheme == DUGKS_T3S3 ? 4 : 6;
+      line = p.tile_rows <= most ? (wide(p.recon) ? 1000 : 2280) : (c4 ? 1575 : 0);
     }
     take = take || n16 <= line || (f64 && (wide(p.recon) || (c4 && !mfix))) ||
            (!mfix && p.tile_rows <= 3);

@@ -164,7 +164,7 @@ __host__ __device__ constexpr int tile_waves(int esize, int recon, int TR, bool 
 // forms whose 8-row blocks do not fit a compute unit twice keep 4 (FP64
 // central-4 512^2 20.9 / 25.8, T3S3 45.0 / 51.4), and so does FP32, which gains
 // nothing (upwind-3 512^2 10.7 / 12.1).  Upwind-5 may take 10 (see
-// tile_kernel_rows).  Blocks of 10 or 14 wavefronts do not pack two to a compute
+// tile_rows_of).  Blocks of 10 or 14 wavefronts do not pack two to a compute
 // unit, so heights between lose: central-4 512^2 28.0 with 6 rows at 5
 // wavefronts per SIMD, arrays 20.7 with 10 at 7 (18.6 with 8).
 __host__ __device__ constexpr bool tall_tiles(int esize, int recon, int scheme) {

@@ -13,8 +13,8 @@
 // 79, 8.7): a wavefront issues for a quarter of its life there and waits for
 // loads, LDS and barriers for most of the rest.  On larger grids VALU (a third
 // of it lane shifts) is busy half the time, and TR rows take the cell terms of
-// TR + 4 (6), so the march wins from ~800^2 on, upwind-5 from ~1300^2 (see
-// tile_kernel_rows; the rows of a tile: block_tile_rows).
+// TR + 4 (6), so the march wins from ~800^2 on, upwind-5 from ~1400^2 (corrected
+// FP64 from ~500^2; see tile_kernel_default; the rows of a tile: block_tile_rows).
 //
 // Two stages in one launch (two T2 steps, or both of T3S3's) were slower: per
 // step 64^2 6.2 us against 6.0, 200^2 7.8 against 6.7, T3S3 200^2 15.8 against

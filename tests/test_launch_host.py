@@ -206,12 +206,14 @@ KERNELS = [
     (448, 448, 0, 1, 2, 0, 0, 0), (512, 512, 0, 1, 2, 0, 0, 8), (768, 768, 0, 0, 2, 0, 0, 8),
     (512, 512, 0, 0, 2, 1, 0, 8), (768, 768, 0, 2, 2, 0, 0, 0),
     # corrected upwind-5
-    (768, 768, 1, 3, 2, 0, 0, 0), (900, 900, 1, 3, 2, 0, 0, 16), (832, 832, 0, 3, 2, 0, 0, 0),
+    (576, 576, 1, 3, 2, 0, 0, 0), (704, 704, 1, 3, 2, 0, 0, 8), (900, 900, 1, 3, 2, 0, 0, 8),
+    (704, 704, 1, 3, 0, 0, 0, 0), (768, 768, 1, 3, 0, 0, 0, 8), (980, 980, 1, 3, 0, 0, 0, 16),
+    (832, 832, 0, 3, 2, 0, 0, 0),
     (940, 940, 0, 3, 2, 0, 0, 16), (1000, 1000, 0, 3, 2, 0, 0, 0), (1000, 1300, 0, 3, 0, 0, 0, 24),
     (1100, 1100, 0, 3, 0, 0, 0, 0),
     # 8 rows asked for on large grids: marched at that height, as a height of 16 is
     (2048, 2048, 1, 1, 0, 0, 8, 8), (2048, 2048, 1, 1, 2, 0, 8, 8), (2048, 2048, 0, 1, 0, 0, 8, 8),
-    (2048, 2048, 0, 1, 0, 1, 8, 8), (2500, 2500, 1, 3, 0, 0, 8, 8), (2048, 2048, 1, 1, 0, 0, 6, 6),
+    (2048, 2048, 0, 1, 0, 1, 8, 8), (2500, 2500, 1, 3, 0, 0, 8, 8), (768, 768, 1, 3, 0, 0, 8, 8), (2048, 2048, 1, 1, 0, 0, 6, 6),
     (2048, 2048, 1, 1, 2, 0, 1, 8), (2048, 2048, 0, 1, 0, 0, 16, 16),
     # where the tile kernel beats that
     (2048, 2048, 0, 2, 0, 0, 8, 0), (2500, 2500, 0, 3, 2, 0, 8, 0), (1024, 1024, 0, 1, 0, 0, 8, 0),
