@@ -259,7 +259,8 @@ int whole_round_rows(const dugks_params& p, int nstrips) {
 // n = t / c rounds.  A full round takes seg + 5 rows' time, a part f of one
 // 0.5 + 0.5 f of that (few wavefronts run faster, to half the time), and a row
 // costs 0.6 % more for every row of height beyond 16 (the wavefronts of
-// neighbouring strips fall out of step, and lines they share leave the caches).
+// neighbouring strips fall out of step, and lines they share leave the caches; 1 %
+// in FP32 with velocity arrays).
 // FP32 without the correction has 3 or 4 wavefronts per SIMD but is bound by VALU
 // from 2 on, with velocity arrays from 3 on; there and in central-4 a part of a
 // round steps with its wavefronts per SIMD, 0.5 + 0.4 f + 0.1 from the first to the
@@ -270,7 +271,8 @@ int whole_round_rows(const dugks_params& p, int nstrips) {
 // 4096^2 602 (16) / 692 (72); central-4 1900^2 203 (14) / 216; FP32 corrected
 // 2000^2 105 (32) / 125 (24), 4096^2 358 (32) / 469 (96); T3S3 1900^2 400 / 509;
 // FP32 arrays, against the choice for 2 wavefronts per SIMD, central-4 1900^2 110
-// (22) / 129 (34), 1024 x 8192 245 (16) / 294 (40), upwind-3 1900^2 101 (22) / 114 (34).
+// (22) / 129 (34), 1024 x 8192 245 (16) / 294 (40), upwind-3 1900^2 101 (22) / 114 (34);
+// 3000^2 246 (16) / 262 (32 at 0.6 %).
 // Upwind-5, one wavefront per SIMD in FP64, keeps whole rounds (2048^2 377
 // against 432 at 16); in FP32 also that of 8-row tiles (900^2 42 against 57 at 16,
 // corrected 51 against 73).
@@ -282,10 +284,11 @@ int default_tile_rows(const dugks_params& p, int nstrips) {
   const bool fix = (p.flags & DUGKS_FLAG_MASS_FIX) != 0;
   long resident = resident_wavefronts(p);
   const bool arrays = p.vel_kind == DUGKS_VEL_ARRAYS;
-  double step = 0.0;
+  double step = 0.0, drift = 0.006;
   if (p.precision == DUGKS_F32 && !fix) {
     resident = std::min(resident, arrays ? 3072L : 2048L);
     if (arrays || p.recon == DUGKS_CENTRAL4) step = 0.1;
+    if (arrays) drift = 0.01;
   }
   const double c = resident / 8.0, simds = 128.0;   // of an XCD
   auto cost = [&](int seg) {
@@ -295,7 +298,7 @@ int default_tile_rows(const dugks_params& p, int nstrips) {
     const double n = t / c, whole = floor(n), f = n - whole;
     double part = 0.5 + (0.5 - step) * f;
     if (step > 0.0) part += step * (ceil((t - whole * c) / simds) - 1.0) / (ceil(c / simds) - 1.0);
-    return (whole + (f > 0.0 ? part : 0.0)) * (seg + 5) * (1.0 + 0.006 * (seg - 16));
+    return (whole + (f > 0.0 ? part : 0.0)) * (seg + 5) * (1.0 + drift * (seg - 16));
   };
   // every height where there are few rounds, else the multiples of 8 from 16 on
   const long tiles16 = (long)nstrips * ((p.ny + 15) / 16);

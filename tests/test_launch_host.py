@@ -227,7 +227,7 @@ KERNELS = [
     (262, 222, 0, 1, 0, 0, 8, 0, 4), (301, 229, 0, 3, 0, 0, 8, 0), (301, 229, 1, 3, 0, 0, 8, 0),
     # default heights: FP32 with velocity arrays has 3 wavefronts per SIMD to fill
     (1900, 1900, 1, 2, 0, 0, 0, 22, 4), (1900, 1900, 1, 1, 0, 0, 0, 22, 4),
-    (1024, 8192, 1, 2, 0, 0, 0, 16, 4), (1900, 1900, 1, 1, 0, 0, 0, 34, 0),
+    (1024, 8192, 1, 2, 0, 0, 0, 16, 4), (3000, 3000, 1, 1, 0, 0, 0, 16, 4), (1900, 1900, 1, 1, 0, 0, 0, 34, 0),
 ]
 
 
